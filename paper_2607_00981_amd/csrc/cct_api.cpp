@@ -61,6 +61,7 @@ const char* kErr[] = {"ok", "invalid argument", "out of device memory", "device 
 }  // namespace
 
 struct cct_ctx {
+  StageUser stage_user;  // keeps the pinned buffers of copy_to_host
   cct_alloc_fn alloc_fn = nullptr;  // the caller's device allocator (both null: hipMalloc / hipFree)
   cct_free_fn free_fn = nullptr;
   void* alloc_user = nullptr;
@@ -3056,10 +3057,9 @@ int cct_set_amplitudes(cct_ctx* ctx, const double* t1, const double* t2, const d
 int cct_get_amplitudes(cct_ctx* ctx, double* t1, double* t2, double* t3p) {
   if (!ctx) return CCT_EINVAL;
   const long long ov = (long long)ctx->o * ctx->v;
-  if (t1) HIPCK(hipMemcpyAsync(t1, ctx->t1, ov * 8, hipMemcpyDeviceToHost, ctx->s));
-  if (t2) HIPCK(hipMemcpyAsync(t2, ctx->t2, ov * ov * 8, hipMemcpyDeviceToHost, ctx->s));
-  if (t3p) HIPCK(hipMemcpyAsync(t3p, ctx->t3, ctx->ntri * ctx->v3 * 8, hipMemcpyDeviceToHost, ctx->s));
-  HIPCK(hipStreamSynchronize(ctx->s));
+  if (t1) HIPCK(copy_to_host(t1, ctx->t1, ov * 8, ctx->dev, ctx->s));
+  if (t2) HIPCK(copy_to_host(t2, ctx->t2, ov * ov * 8, ctx->dev, ctx->s));
+  if (t3p) HIPCK(copy_to_host(t3p, ctx->t3, ctx->ntri * ctx->v3 * 8, ctx->dev, ctx->s));
   return CCT_OK;
 }
 
@@ -3070,10 +3070,9 @@ int cct_residual(cct_ctx* ctx, unsigned term_mask, double* r1, double* r2, doubl
   int rc = compute(ctx, term_mask, false, nr);
   if (rc != CCT_OK && rc != CCT_ENUMERIC) return rc;
   const long long ov = (long long)ctx->o * ctx->v;
-  if (r1) HIPCK(hipMemcpyAsync(r1, ctx->r1, ov * 8, hipMemcpyDeviceToHost, ctx->s));
-  if (r2) HIPCK(hipMemcpyAsync(r2, ctx->r2, ov * ov * 8, hipMemcpyDeviceToHost, ctx->s));
-  if (r3p) HIPCK(hipMemcpyAsync(r3p, ctx->r3, ctx->ntri * ctx->v3 * 8, hipMemcpyDeviceToHost, ctx->s));
-  HIPCK(hipStreamSynchronize(ctx->s));
+  if (r1) HIPCK(copy_to_host(r1, ctx->r1, ov * 8, ctx->dev, ctx->s));
+  if (r2) HIPCK(copy_to_host(r2, ctx->r2, ov * ov * 8, ctx->dev, ctx->s));
+  if (r3p) HIPCK(copy_to_host(r3p, ctx->r3, ctx->ntri * ctx->v3 * 8, ctx->dev, ctx->s));
   if (norms) for (int i = 0; i < 3; ++i) norms[i] = nr[i];
   return rc;
 }
@@ -3081,8 +3080,7 @@ int cct_residual(cct_ctx* ctx, unsigned term_mask, double* r1, double* r2, doubl
 int cct_copy_r3(cct_ctx* ctx, int64_t first, int64_t count, double* out) {
   if (!ctx || !out || first < 0 || count < 0 || first + count > ctx->ntri * ctx->v3) return CCT_EINVAL;
   if (!ctx->have_res) { ctx->err = "no residual computed yet"; return CCT_ESTATE; }
-  HIPCK(hipMemcpyAsync(out, ctx->r3 + first, (size_t)count * 8, hipMemcpyDeviceToHost, ctx->s));
-  HIPCK(hipStreamSynchronize(ctx->s));
+  HIPCK(copy_to_host(out, ctx->r3 + first, (size_t)count * 8, ctx->dev, ctx->s));
   return CCT_OK;
 }
 

@@ -9,6 +9,17 @@
 
 namespace cct {
 
+// Synchronous device-to-host copy on stream s (of device dev), through a pool
+// of pinned buffers and a few threads where dst is pageable and large.  Every
+// object that may copy holds a StageUser; the pool goes with the last of them.
+struct StageUser {
+  StageUser();
+  ~StageUser();
+  StageUser(const StageUser&) = delete;
+  StageUser& operator=(const StageUser&) = delete;
+};
+hipError_t copy_to_host(void* dst, const void* src, size_t bytes, int dev, hipStream_t s);
+
 // Two-level index map: i -> (i / inner) * s_hi + (i % inner) * s_lo.
 // inner == 0 means one level: i -> i * s_lo.
 struct Idx2 {

@@ -27,6 +27,7 @@
 using namespace cct;
 
 struct cct_quad {
+  StageUser stage_user;  // keeps the pinned buffers of copy_to_host
   cct_alloc_fn alloc_fn = nullptr;
   cct_free_fn free_fn = nullptr;
   void* alloc_user = nullptr;
@@ -34,6 +35,7 @@ struct cct_quad {
   long long nq = 0, v4 = 0;
   Prec prec = Prec::F64;
   hipStream_t s = nullptr;
+  int dev = 0;  // the stream's device
   bool timers = false, have_w = false, have_t4 = false, have_r = false;
   double* W = nullptr;   // [a][b][e][f] = W^{ab}_{ef}
   double* t4 = nullptr;  // [nq][v^4]
@@ -238,6 +240,10 @@ int cct_quad_create(int nocc, int nvir, cct_precision prec, const char* opts_jso
   q->v4 = v2 * v2;
   q->prec = (Prec)prec;
   q->s = (hipStream_t)hip_stream;
+  if ((q->s ? hipStreamGetDevice(q->s, &q->dev) : hipGetDevice(&q->dev)) != hipSuccess) {
+    delete q;
+    return CCT_EDEVICE;
+  }
   if (opts_json) {
     const std::string js(opts_json);
     q->timers = js.find("\"timers\": true") != std::string::npos || js.find("\"timers\":true") != std::string::npos;
@@ -328,8 +334,8 @@ int cct_quad_ladder(cct_quad* q, double* r4p, double* norm2) {
   double h = 0.0;
   QHIP(weighted_dot_t3(q->r4, q->r4, q->blk, (int)q->nq, q->v4, q->v4, q->scal, q->red, q->s));
   QHIP(hipMemcpyAsync(&h, q->scal, sizeof(double), hipMemcpyDeviceToHost, q->s));
-  if (r4p) QHIP(hipMemcpyAsync(r4p, q->r4, (size_t)(q->nq * q->v4) * 8, hipMemcpyDeviceToHost, q->s));
   QHIP(hipStreamSynchronize(q->s));
+  if (r4p) QHIP(copy_to_host(r4p, q->r4, (size_t)(q->nq * q->v4) * 8, q->dev, q->s));
   q->have_r = true;
   if (norm2) *norm2 = h;
   if (!std::isfinite(h)) {
@@ -345,8 +351,7 @@ int cct_quad_copy_r4(cct_quad* q, int64_t first, int64_t count, double* out) {
     q->err = "no residual yet (cct_quad_ladder)";
     return CCT_ESTATE;
   }
-  QHIP(hipMemcpyAsync(out, q->r4 + first, (size_t)count * 8, hipMemcpyDeviceToHost, q->s));
-  QHIP(hipStreamSynchronize(q->s));
+  QHIP(copy_to_host(out, q->r4 + first, (size_t)count * 8, q->dev, q->s));
   return CCT_OK;
 }
 

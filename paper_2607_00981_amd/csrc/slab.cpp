@@ -25,12 +25,14 @@
 using namespace cct;
 
 struct cct_slab {
+  StageUser stage_user;  // keeps the pinned buffers of copy_to_host
   cct_alloc_fn alloc_fn = nullptr;  // the caller's device allocator (both null: hipMalloc / hipFree)
   cct_free_fn free_fn = nullptr;
   void* alloc_user = nullptr;
   int o = 0, v = 0, n = 0, naux = 0, first = 0, count = 0, ntri_all = 0;
   Prec prec = Prec::F64;
   hipStream_t s = nullptr;
+  int dev = 0;    // the stream's device
   int panel = 0;  // rows a per W panel
   bool have_ims = false, have_t3 = false, timers = false;
   long long v3 = 0;
@@ -452,6 +454,10 @@ int cct_slab_create(int nocc, int nvir, int naux, int first, int count, cct_prec
   sl->first = first; sl->count = count; sl->ntri_all = (int)ntri;
   sl->prec = (Prec)prec;
   sl->s = (hipStream_t)hip_stream;
+  if ((sl->s ? hipStreamGetDevice(sl->s, &sl->dev) : hipGetDevice(&sl->dev)) != hipSuccess) {
+    delete sl;
+    return CCT_EDEVICE;
+  }
   sl->v3 = (long long)nvir * nvir * nvir;
   sl->panel = std::max(1, std::min(nvir, 8));
   if (opts_json) {
@@ -628,13 +634,13 @@ int cct_slab_residual(cct_slab* sl, unsigned term_mask, double* r3slab, double* 
   sl->macs[4] = (term_mask & CCT_TERM_D2) ? 6.0 * nb_ * o_ * std::pow(v_, 3) : 0.0;
   if (!std::isfinite(h)) { sl->err = "non-finite residual norm"; return CCT_ENUMERIC; }
   if (norm2) *norm2 = h;
-  if (r3slab) SHIP(hipMemcpy(r3slab, sl->r3, (size_t)(nb * v3) * 8, hipMemcpyDeviceToHost));
+  if (r3slab) SHIP(copy_to_host(r3slab, sl->r3, (size_t)(nb * v3) * 8, sl->dev, sl->s));
   return CCT_OK;
 }
 
 int cct_slab_copy_r3(cct_slab* sl, int64_t first, int64_t count, double* out) {
   if (!sl || !out || first < 0 || count < 0 || first + count > (int64_t)sl->count * sl->v3) return CCT_EINVAL;
-  SHIP(hipMemcpy(out, sl->r3 + first, (size_t)count * 8, hipMemcpyDeviceToHost));
+  SHIP(copy_to_host(out, sl->r3 + first, (size_t)count * 8, sl->dev, sl->s));
   return CCT_OK;
 }
 
