@@ -80,6 +80,8 @@ struct cct_ctx {
   bool have_f = false, have_B = false, have_res = false;
 
   std::vector<void*> owned;
+  void* q_keep = nullptr;  // memory of cct_energy_q kept between calls
+  size_t q_keep_bytes = 0;
   // inputs
   double *f = nullptr, *B = nullptr, *eps = nullptr, *fov = nullptr;
   double *vbare_c = nullptr;  // 2 v^{ij}_{ab} - v^{ij}_{ba} (bare), [i][j][a][b]
@@ -1549,15 +1551,11 @@ int energy_dev(cct_ctx* ctx, double* e) {
 // E_(Q) of the (Q) appendix (Eq. ener-pt-q with Eq. resi-pt-q), by the
 // occupied-tuple traversal of the "IJK-based algorithm" section: one task per
 // i <= j <= k <= l (no three equal: those blocks of the spin-summed quadruples
-// vanish).  With G = X + Y and A = X + V, the task accumulates
-//   R[w]    = sum over the 24 column permutations s of G_{o.s}[w.s]
-//   Abar[w] = sum over the distinct orderings q = o.s of A_q[w.s]
-// and contributes <Abar, S(R) / eps_o>, S the full spin summation; since S
-// commutes with column permutations and z = P(X + V), this equals the
-// task's share of 1/24 sum z tchk.  The blocks X_q, Y_q of an ordered tuple q
-// cost two dense contractions of 2 v^5 (X from T3, Y from the resident
-// Wbar_ejk^abc) plus two of 2 o v^4; all orderings of a task stay resident
-// and one permuted-combine pass writes R and Abar.
+// vanish).  The task accumulates, in the frame of its tuple,
+//   Xt[w], Yt[w] = the sums over the 24 column permutations of X and Y
+// and contributes nq/24 <Xt + Vt, S(Xt + Yt) / eps_o>, S the full spin
+// summation, Vt the same sum of V and nq the number of distinct orderings
+// (qo_plan says how the sums are formed, qo_energy how they are contracted).
 DT Vview(cct_ctx* c, double* base, const char* blk) {
   DT t = Vv(c, blk);
   t.p = base + (t.p - c->V);
@@ -1600,6 +1598,218 @@ struct QMem {
 
 long long q_task_count(int o) { return (long long)o * (o + 1) * (o + 2) * (o + 3) / 24; }
 
+// The sums over the 24 column permutations of X and Y of one occupied tuple,
+// in the frame of the tuple (virtual axis k paired with occupied label o_k).
+// A permutation p puts the labels of axes p_0..p_3 in the columns a, b, c, d of
+// the term.  T3 is symmetric in (k,c)(l,d) of both X terms, Wbar_ejk^abc in
+// (j,b)(k,c) and Wbar_ijk^abm in (i,a)(j,b), so each term has 12 distinct
+// contractions of weight 2, named by an ordered pair of axes: X1 and X2 by
+// (a, b), Y1 by (a, d), Y2 by (c, d).  Those with the same output rows are one
+// product with up to four K segments:
+//   X1 (K = v) and Y2 (K = o): rows the axes {x, y}, columns {z, w}, for the
+//     three pairings 01|23, 02|13, 12|03;
+//   X2 (K = o): rows the axis a, columns the other three;
+//   Y1 (K = v): rows the other three, columns the axis d.
+// With equal occupied labels (stabiliser G of the tuple, acting on the axes)
+// the contractions of one orbit of G are images of each other: one
+// representative is kept, with weight |orbit| / |G|, and the energy sums over
+// G (qo_energy).  Each item writes its accumulators 7 + 7 times at most,
+// against 24 + 24 blocks written, updated and read 24 times by one product per
+// ordered tuple (o = 6, v = 48: 196 -> 51.6 ms per evaluation).
+constexpr int kQoLaunches = 14;
+// (Q) memory that may stay with a context between calls.
+constexpr size_t kQKeep = (size_t)4 << 30;
+// Position of (q <= r) among the o(o+1)/2 such pairs; qo_pair(o, o, o) is their number.
+long long qo_pair(long long o, long long q, long long r) { return q * o - q * (q - 1) / 2 + (r - q); }
+struct QoOperands {
+  const double *VVVO, *VVVOt, *VVVOk, *VVVOkt, *VOOO, *Wv, *Wo, *Wok, *T3u, *t2, *T2r, *T2l;
+};
+struct QoLaunch {
+  QoGemm g;
+  bool y;         // into Y (else X)
+  size_t first;   // position of its items in the table
+};
+
+// Items of the 14 launches for the listed tasks (each writes slot t of the
+// accumulators).  false: an operand would be read out of range.
+bool qo_plan(int o, int v, const std::vector<int4>& tasks, const QoOperands& w, std::vector<QoItem>& items,
+             QoLaunch ls[kQoLaunches]) {
+  const long long v2 = (long long)v * v, v3 = v2 * v, v4 = v2 * v2, o2 = (long long)o * o;
+  const long long st[4] = {v3, v2, v, 1};
+  static const int PAIR[3][4] = {{0, 1, 2, 3}, {0, 2, 1, 3}, {1, 2, 0, 3}};  // rows x, y | columns z, w
+  auto pairing = [](int a, int b) {
+    const int m = (1 << a) | (1 << b);
+    return m == 3 || m == 12 ? 0 : (m == 5 || m == 10 ? 1 : 2);
+  };
+  bool ok = true;
+  auto seg = [&](QoItem& it, const double* a, const double* abase, long long alen, long long areach, int rs0, int rs1,
+                 int rs2, const double* b, const double* bbase, long long blen, long long ldb, int K, long long N,
+                 double coef) {
+    ok = ok && it.nseg < QO_SEG && a >= abase && (a - abase) + areach + K <= alen && b >= bbase &&
+         (b - bbase) + (K - 1) * ldb + N <= blen;
+    if (!ok) return;
+    QoSeg& sg = it.seg[it.nseg++];
+    sg.a = a; sg.b = b; sg.ldb = ldb; sg.coef = coef;
+    sg.rs0 = rs0; sg.rs1 = rs1; sg.rs2 = rs2;
+  };
+  const long long n_vvvo = o * v3, n_t3 = o2 * o * v3, n_t2 = o2 * v2, n_wo = o2 * o2 * v2;
+  // stabiliser of a task on the axes, and whether the ordered pair (p, q) is
+  // the representative of its orbit (smallest `rank`), with its weight
+  struct Stab { int n; int t[4][4]; };
+  auto stabiliser = [](const int oc[4]) {
+    Stab s{1, {{0, 1, 2, 3}}};
+    int p[4] = {0, 1, 2, 3};
+    while (std::next_permutation(p, p + 4))
+      if (oc[p[0]] == oc[0] && oc[p[1]] == oc[1] && oc[p[2]] == oc[2] && oc[p[3]] == oc[3]) {
+        if (s.n < 4)
+          for (int k = 0; k < 4; ++k) s.t[s.n][k] = p[k];
+        ++s.n;
+      }
+    return s;
+  };
+  auto weight = [](const Stab& g, int p, int q, auto rank) -> double {
+    int seen[4], n = 0;
+    const int mine = rank(p, q);
+    for (int k = 0; k < g.n; ++k) {
+      const int pp = g.t[k][p], qq = g.t[k][q], r = rank(pp, qq);
+      if (r < mine) return 0.0;
+      int x = 0;
+      while (x < n && seen[x] != r) ++x;
+      if (x == n) seen[n++] = r;
+    }
+    return (double)n / g.n;
+  };
+  auto pair_rank = [&](int p, int q) { return pairing(p, q) * 16 + p * 4 + q; };
+  auto first_rank = [](int p, int q) { return p * 4 + q; };          // X2: the smallest row axis
+  auto last_rank = [](int p, int q) { return (3 - q) * 4 + p; };     // Y1 (a, d): the largest column axis
+  std::vector<Stab> gs(tasks.size());
+  for (size_t t = 0; t < tasks.size(); ++t) {
+    const int oc[4] = {tasks[t].x, tasks[t].y, tasks[t].z, tasks[t].w};
+    gs[t] = stabiliser(oc);
+    if (gs[t].n > 4) return false;  // three equal labels: not a task
+  }
+  items.clear();
+  int nl = 0;
+  auto open = [&](bool y, int M, int N, int K, int n1, bool vec, bool swap, Idx4 cm, Idx4 cn, int acc) -> QoLaunch& {
+    QoLaunch& l = ls[nl++];
+    l = QoLaunch{};
+    l.y = y;
+    l.first = items.size();
+    l.g.M = M; l.g.N = N; l.g.K = K; l.g.n1 = l.g.n2 = n1;
+    l.g.vec = vec; l.g.swap = swap; l.g.cm = cm; l.g.cn = cn; l.g.accumulate = acc;
+    return l;
+  };
+  auto close = [&](QoLaunch& l) { l.g.nitems = (int)(items.size() - l.first); };
+  auto lin = [](long long s0) { return Idx4{1, 1, 1, s0, 0, 0, 0}; };
+  auto pair_map = [&](int a, int b) { return Idx4{1, 1, v, st[a], 0, 0, st[b]}; };
+  auto trip_map = [&](int a, int b, int c) { return Idx4{1, v, v, st[a], 0, st[b], st[c]}; };
+  const bool ev = v % 2 == 0, eo = ev && o % 2 == 0;
+  const long long m2 = (v2 - 1);
+  for (int pr = 0; pr < 3; ++pr) {
+    const int x = PAIR[pr][0], y = PAIR[pr][1], z = PAIR[pr][2], u = PAIR[pr][3];
+    // X1 = 1/2 sum_e v^{ab}_{e,o_b} t_{o_a o_c o_d}^{e c d}
+    QoLaunch& l = open(false, (int)v2, (int)v2, v, 1, ev, false, pair_map(x, y), pair_map(z, u), pr > 0);
+    for (size_t t = 0; t < tasks.size(); ++t) {
+      const long long oc[4] = {tasks[t].x, tasks[t].y, tasks[t].z, tasks[t].w};
+      QoItem it{};
+      it.c = (long long)t * v4;
+      auto T3 = [&](long long m, long long r, long long q) { return w.T3u + ((r * o + q) * o + m) * v3; };  // t_{m r q}
+      auto add = [&](int a, int b, const double* A, const double* abase, long long alen, const double* B,
+                     const double* bbase, long long blen) {
+        const double c = weight(gs[t], a, b, pair_rank);
+        if (c != 0.0) seg(it, A, abase, alen, m2 * v, v, 0, 0, B, bbase, blen, v2, v, v2, c);
+      };
+      add(x, y, w.VVVO + oc[y] * v3, w.VVVO, n_vvvo, T3(oc[x], oc[z], oc[u]), w.T3u, n_t3);
+      add(y, x, w.VVVOt + oc[x] * v3, w.VVVOt, n_vvvo, T3(oc[y], oc[z], oc[u]), w.T3u, n_t3);
+      // t_{o_a o_x o_y}^{e x y} = t_{o_x o_y o_a}^{x y e}
+      add(z, u, T3(oc[x], oc[y], oc[z]), w.T3u, n_t3, w.VVVOk + oc[u] * v3, w.VVVOk, n_vvvo);
+      add(u, z, T3(oc[x], oc[y], oc[u]), w.T3u, n_t3, w.VVVOkt + oc[z] * v3, w.VVVOkt, n_vvvo);
+      if (it.nseg > 0 || pr == 0) items.push_back(it);
+    }
+    close(l);
+  }
+  for (int a = 0; a < 4; ++a) {
+    int r[3], n = 0;
+    for (int k = 0; k < 4; ++k)
+      if (k != a) r[n++] = k;
+    // X2 = -1/2 sum_m v^{am}_{o_a o_b} t_{m o_c o_d}^{b c d}
+    QoLaunch& l = open(false, v, (int)v3, o, 1, eo, a == 3, lin(st[a]), trip_map(r[0], r[1], r[2]), 1);
+    for (size_t t = 0; t < tasks.size(); ++t) {
+      const long long oc[4] = {tasks[t].x, tasks[t].y, tasks[t].z, tasks[t].w};
+      QoItem it{};
+      it.c = (long long)t * v4;
+      for (int k = 0; k < 3; ++k) {
+        const double c = weight(gs[t], a, r[k], first_rank);
+        if (c == 0.0) continue;
+        const double* B;
+        long long ld;
+        if (k == 0) {
+          B = w.T3u + (oc[r[1]] * o + oc[r[2]]) * o * v3;  // t_{m o_y o_z}: m the stored first label
+          ld = v3;
+        } else if (k == 1) {
+          B = w.T3u + oc[r[2]] * o * v3 + oc[r[0]] * v3;   // t_{o_x m o_z}
+          ld = o2 * v3;
+        } else {
+          B = w.T3u + oc[r[1]] * o2 * v3 + oc[r[0]] * v3;  // t_{o_x o_y m}
+          ld = (long long)o * v3;
+        }
+        seg(it, w.VOOO + (oc[a] * o + oc[r[k]]) * v * o, w.VOOO, o2 * o * v, (long long)(v - 1) * o, o, 0, 0, B, w.T3u,
+            n_t3, ld, o, v3, -c);
+      }
+      if (it.nseg > 0) items.push_back(it);
+    }
+    close(l);
+  }
+  for (int pr = 0; pr < 3; ++pr) {
+    const int x = PAIR[pr][0], y = PAIR[pr][1], z = PAIR[pr][2], u = PAIR[pr][3];
+    // Y2 = -1/2 sum_m Wbar_{o_a o_b o_c}^{a b m} t_{m o_d}^{c d}
+    QoLaunch& l = open(true, (int)v2, (int)v2, o, 1, eo, false, pair_map(x, y), pair_map(z, u), pr > 0);
+    for (size_t t = 0; t < tasks.size(); ++t) {
+      const long long oc[4] = {tasks[t].x, tasks[t].y, tasks[t].z, tasks[t].w};
+      QoItem it{};
+      it.c = (long long)t * v4;
+      auto add = [&](int c, int d, const double* A, const double* abase, long long alen, const double* B,
+                     const double* bbase, long long blen, long long ld) {
+        const double wt = weight(gs[t], c, d, pair_rank);
+        if (wt != 0.0) seg(it, A, abase, alen, m2 * o, o, 0, 0, B, bbase, blen, ld, o, v2, -wt);
+      };
+      auto W3 = [&](const double* p, int i, int j, int k) { return p + ((oc[i] * o + oc[j]) * o + oc[k]) * o * v2; };
+      add(z, u, W3(w.Wo, x, y, z), w.Wo, n_wo, w.t2 + oc[u] * v2, w.t2, n_t2, o * v2);
+      add(u, z, W3(w.Wo, x, y, u), w.Wo, n_wo, w.t2 + oc[z] * o * v2, w.t2, n_t2, v2);  // t_{m o_z}^{u z} = t_{o_z m}^{z u}
+      add(x, y, w.T2r + oc[y] * o * v2, w.T2r, n_t2, W3(w.Wok, z, u, x), w.Wok, n_wo, v2);
+      add(y, x, w.T2l + oc[x] * o * v2, w.T2l, n_t2, W3(w.Wok, z, u, y), w.Wok, n_wo, v2);
+      if (it.nseg > 0 || pr == 0) items.push_back(it);
+    }
+    close(l);
+  }
+  for (int d = 3; d >= 0; --d) {
+    int r[3], n = 0;
+    for (int k = 0; k < 4; ++k)
+      if (k != d) r[n++] = k;
+    // Y1 = 1/2 sum_e Wbar_{e o_b o_c}^{a b c} t_{o_a o_d}^{e d}
+    QoLaunch& l = open(true, (int)v3, v, v, v, ev, d != 3, trip_map(r[0], r[1], r[2]), lin(st[d]), 1);
+    for (size_t t = 0; t < tasks.size(); ++t) {
+      const long long oc[4] = {tasks[t].x, tasks[t].y, tasks[t].z, tasks[t].w};
+      QoItem it{};
+      it.c = (long long)t * v4;
+      for (int k = 0; k < 3; ++k) {
+        const double c = weight(gs[t], r[k], d, last_rank);
+        if (c == 0.0) continue;
+        const int b1 = k == 0 ? 1 : 0, c1 = k == 2 ? 1 : 2;  // positions of b < c among the rows
+        int rs[3];
+        rs[k] = (int)v3;
+        rs[b1] = (int)v2;
+        rs[c1] = v;
+        seg(it, w.Wv + qo_pair(o, oc[r[b1]], oc[r[c1]]) * v4, w.Wv, qo_pair(o, o, o) * v4,
+            (long long)(v - 1) * (v3 + v2 + v), rs[0], rs[1], rs[2], w.t2 + (oc[r[k]] * o + oc[d]) * v2, w.t2, n_t2, v, v, v, c);
+      }
+      if (it.nseg > 0) items.push_back(it);
+    }
+    close(l);
+  }
+  return ok && nl == kQoLaunches;
+}
+
 // region / region_bytes: a fixed device region to take every buffer from
 // (no allocation); nullptr: the context's allocator, or hipMalloc.
 int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* region = nullptr,
@@ -1616,54 +1826,100 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
   if (v3 > INT_MAX || o2 * o * v3 > LLONG_MAX / 8) { ctx->err = "energy_q: nvir too large"; return CCT_EINVAL; }
   hipStream_t s = ctx->s;
   const long long arena_n = std::max(v4, o2 * o2 * v2) + (8LL << 20);
-  // even v with o <= 16: the K=o updates write tile-major copies of the task
-  // blocks (XT, GT), which the permuted combine reads as contiguous tiles
-  const bool tl = (v % 2) == 0 && o <= 16;
-  const long long T4 = tiled_len(v);
+  const long long v8 = (v + 7) / 8, v4p = v8 * v8 * v8 * v8 * 4096;
+  const bool even = (v % 2) == 0 && o <= 16;  // more room for accumulators
   const long long need = n4 + v4 + (long long)o * v3 + o2 * o * v + o2 * v2 + o2 * v4 + 2 * o2 * o2 * v2 +
-                         o2 * o * v3 + 50 * v4 + (tl ? 48 * T4 : 0) + ntask + 1 + arena_n;
+                         o2 * o * v3 + 50 * v4 + (even ? 48 * v4p : 0) + ntask + 1 + arena_n;
   if (!ctx->alloc_fn && !region) {
     size_t fr = 0, tot = 0;
     HIPCK(hipMemGetInfo(&fr, &tot));
+    fr += ctx->q_keep_bytes;
     if ((double)need * 8.0 + 256e6 > (double)fr) {
       ctx->err = "energy_q: needs " + std::to_string(need * 8.0 / 1e9) + " GB of device memory, " +
                  std::to_string(fr / 1e9) + " GB free";
       return CCT_ENOMEM;
     }
   }
+  if (region) {
+    // what a call needs with every buffer at its full size
+    const size_t all = (size_t)(n4 + v4 + (long long)o * v3 + o2 * o * v + o2 * v2 + o2 * v4 + 2 * o2 * o2 * v2 +
+                                o2 * o * v3 + (even ? 27 * v4 + 48 * v4p : 50 * v4) + 24 * v2 + ntask + 1 + arena_n +
+                                o2) * 8;
+    if (all > region_bytes) {  // nothing has been launched yet
+      ctx->err = "energy_q: this system needs " + std::to_string(all >> 20) + " MiB of device scratch, the " +
+                 "fixed scratch region holds " + std::to_string(region_bytes >> 20) + " MiB";
+      return CCT_ENOMEM;
+    }
+  }
+  const long long npair = (long long)o * (o + 1) / 2;  // (q <= r): the Wbar_eqr^abc that the tasks read
+  // One block of scratch: relaid copies of v^{ab}_{ej} and T2, the item tables,
+  // and the accumulators X and Y of as many tasks as fit beside them.
+  const long long norb = qo_orbits(v);
+  const long long item_n = (long long)(sizeof(QoItem) / 8);
+  auto up = [](long long x) { return (x + 31) / 32 * 32; };
+  const long long fixed_n = 3 * up(o * v3) + 2 * up(o2 * v2) + up(2 * npair * item_n) + up((norb + 1) / 2) + 9 * 32;
+  const long long per_task = 2 * v4 + norb + kQoLaunches * item_n + 8;
+  // planner scratch: the context's workspace (idle here) when it holds the
+  // largest temporary
+  const bool use_ws = ctx->ws.available() / 8 >= (size_t)(std::max(v4, o2 * o2 * v2) + 65536);
+  const long long other_n = (use_ws ? 0 : up(arena_n)) + up(n4) + up(v4) + up(o * v3) + up(o2 * o * v) + up(o2 * v2) + up(npair * v4) +
+                            2 * up(o2 * o2 * v2) + up(o2 * o * v3) + up(ntask + 1) + up(o2);
+  long long ntb = std::min<long long>(ntask, 4096);
+  if (region) {
+    ntb = std::min(ntb, ((long long)(region_bytes / 8) - other_n - fixed_n) / per_task);
+  } else {
+    // Memory that stays with the context from call to call when it is at most
+    // kQKeep (allocated and freed per call it costs more than the products of a
+    // small system once the device has no cleared memory at hand: o = 4, v = 20
+    // 1.5 ms per call at first, 6 to 12 ms after some thousand calls); a larger
+    // system takes room for at most the tasks of the documented need.
+    const long long keep_n = (long long)(kQKeep / 8);
+    const long long fit = (keep_n - other_n - fixed_n) / per_task;
+    if (!ctx->alloc_fn && fit >= std::min<long long>(ntb, 16)) {
+      ntb = std::min(ntb, fit);
+      const size_t bytes = (size_t)(other_n + fixed_n + ntb * per_task) * 8;
+      if (ctx->q_keep_bytes < bytes) {
+        if (ctx->q_keep) {
+          HIPCK(hipStreamSynchronize(s));
+          dev_free(ctx, ctx->q_keep);
+          ctx->q_keep = nullptr;
+          ctx->q_keep_bytes = 0;
+        }
+        RCK(dev_alloc(ctx, &ctx->q_keep, bytes));
+        ctx->q_keep_bytes = bytes;
+      }
+      region = (char*)ctx->q_keep;
+      region_bytes = ctx->q_keep_bytes;
+    } else {
+      ntb = std::min(ntb, ((even ? 27 * v4 + 48 * v4p : 50 * v4) - fixed_n) / per_task);
+    }
+  }
+  ntb = std::max<long long>(ntb, 1);
+  const long long scratch_n = fixed_n - 32 + ntb * per_task;  // the last 32: its end rounded up
   QMem mem(ctx, region, region_bytes);
-  double *Vb, *VVVV, *VVVO, *VOOO, *VVOO, *Wv, *g, *Wo, *T3u, *Xb, *Gb, *Rb, *Ab, *et, *ar;
+  double *Vb, *VVVV, *VVVO, *VOOO, *VVOO, *Wv, *g, *Wo, *T3u, *et, *scratch;
   int2* slots;
   RCK(mem.get(&Vb, n4));
   RCK(mem.get(&VVVV, v4));
   RCK(mem.get(&VVVO, (long long)o * v3));
   RCK(mem.get(&VOOO, o2 * o * v));
   RCK(mem.get(&VVOO, o2 * v2));
-  RCK(mem.get(&Wv, o2 * v4));
+  RCK(mem.get(&Wv, npair * v4));
   RCK(mem.get(&g, o2 * o2 * v2));
   RCK(mem.get(&Wo, o2 * o2 * v2));
   RCK(mem.get(&T3u, o2 * o * v3));
-  RCK(mem.get(&Xb, (tl ? 1 : 24) * v4));  // X of each distinct ordering of a task (tiled path: one scratch block)
-  RCK(mem.get(&Gb, 24 * v4));  // Y of each distinct ordering
-  RCK(mem.get(&Rb, v4));
-  RCK(mem.get(&Ab, v4));
+  RCK(mem.get(&scratch, scratch_n));
   RCK(mem.get(&et, ntask + 1));
-  RCK(mem.get(&ar, arena_n));
   RCK(mem.get(&slots, o2));
-  double* Bc;
-  RCK(mem.get(&Bc, 24 * v2));  // t2 blocks of the orderings sharing one Y1 product
-  double *XT = nullptr, *GT = nullptr;
-  if (tl) {
-    RCK(mem.get(&XT, 24 * T4));
-    RCK(mem.get(&GT, 24 * T4));
+  Arena own;
+  Arena* qa = &ctx->ws;
+  if (!use_ws) {
+    double* ar = nullptr;
+    RCK(mem.get(&ar, arena_n));
+    own.init((char*)ar, (size_t)arena_n * 8);
+    qa = &own;
   }
-  if (!mem.fits()) {  // nothing has been launched yet
-    ctx->err = "energy_q: this system needs " + std::to_string(mem.used >> 20) + " MiB of device scratch, the " +
-               "fixed scratch region holds " + std::to_string(mem.cap >> 20) + " MiB";
-    return CCT_ENOMEM;
-  }
-  Arena qa;
-  qa.init((char*)ar, (size_t)arena_n * 8);
+  if (!mem.fits()) { ctx->err = "energy_q: scratch plan"; return CCT_EDEVICE; }
   const Prec F = Prec::F64;
 
   // bare integrals v^{pq}_{rs} = (pr|qs), stored like the dressed ones
@@ -1681,24 +1937,66 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
   STCK(accumulate(s, 1.0, Vview(ctx, Vb, "vvvo"), "abej", 0.0, dense(VVVO, {o, v, v, v}), "jabe"));
   STCK(accumulate(s, 1.0, Vview(ctx, Vb, "vooo"), "amij", 0.0, dense(VOOO, {o, o, v, o}), "ijam"));
   STCK(accumulate(s, 1.0, Vview(ctx, Vb, "vvoo"), "abij", 0.0, dense(VVOO, {o, o, v, v}), "ijab"));
-  // Wbar_eqr^abc (Eq. q_w_vvv_voo) as Wv[q][r][a][b][c][e], one (q, r) at a time
-  for (int q = 0; q < o; ++q)
-    for (int r = 0; r < o; ++r) {
-      const DT w = dense(Wv + ((long long)q * o + r) * v4, {v, v, v, v});
-      STCK(contract(qa, s, F, 0.5, dense(VVVV, {v, v, v, v}), "abef", dense(ctx->t2 + ((long long)q * o + r) * v2, {v, v}),
-                    "fc", 0.0, w, "abce"));
-      STCK(contract(qa, s, F, 0.5, dense(VVVV, {v, v, v, v}), "acef", dense(ctx->t2 + ((long long)r * o + q) * v2, {v, v}),
-                    "fb", 1.0, w, "abce"));
-    }
+  long long top = 0;
+  auto carve = [&](long long cnt) {
+    double* q = scratch + top;
+    top += up(cnt);
+    return q;
+  };
+  // v^{ab}_{ej} as VVVO[j][a][b][e], and with its labels in the orders that
+  // make every X1 operand K- or N-contiguous
+  double* VVVOt = carve(o * v3);   // [j][b][a][e]
+  double* VVVOk = carve(o * v3);   // [j][e][a][b]
+  double* VVVOkt = carve(o * v3);  // [j][e][b][a]
+  double* T2r = carve(o2 * v2);    // [j][x][y][m] = t_{m j}^{xy}
+  double* T2l = carve(o2 * v2);    // [i][x][y][m] = t_{i m}^{xy}
+  QoItem* wv_items = (QoItem*)carve(2 * npair * item_n);
+  unsigned* orbits = (unsigned*)carve((norb + 1) / 2);
+  HIPCK(qo_orbit_table(orbits, v, s));
+  STCK(accumulate(s, 1.0, dense(VVVO, {o, v, v, v}), "jabe", 0.0, dense(VVVOt, {o, v, v, v}), "jbae"));
+  STCK(accumulate(s, 1.0, dense(VVVO, {o, v, v, v}), "jabe", 0.0, dense(VVVOk, {o, v, v, v}), "jeab"));
+  STCK(accumulate(s, 1.0, dense(VVVO, {o, v, v, v}), "jabe", 0.0, dense(VVVOkt, {o, v, v, v}), "jeba"));
+  STCK(accumulate(s, 1.0, dense(ctx->t2, {o, o, v, v}), "mjxy", 0.0, dense(T2r, {o, v, v, o}), "jxym"));
+  STCK(accumulate(s, 1.0, dense(ctx->t2, {o, o, v, v}), "imxy", 0.0, dense(T2l, {o, v, v, o}), "ixym"));
+  // Wbar_eqr^abc (Eq. q_w_vvv_voo) as Wv[(q <= r)][a][b][c][e]: rows (a,b,e) and
+  // (a,c,e) of v^{..}_{ef} times t2 blocks, every (q, r) in one launch
+  std::vector<QoItem> wvh((size_t)(2 * npair));
+  for (long long q = 0; q < o; ++q)
+    for (long long r = q; r < o; ++r)
+      for (int w = 0; w < 2; ++w) {
+        QoItem& it = wvh[(size_t)(w * npair + qo_pair(o, q, r))];
+        it = QoItem{};
+        it.c = qo_pair(o, q, r) * v4;
+        it.nseg = 1;
+        it.seg[0].a = VVVV;
+        it.seg[0].b = ctx->t2 + (w == 0 ? q * o + r : r * o + q) * v2;
+        it.seg[0].ldb = v;
+        it.seg[0].coef = 0.5;
+        it.seg[0].rs0 = v;
+      }
+  HIPCK(hipMemcpyAsync(wv_items, wvh.data(), sizeof(QoItem) * wvh.size(), hipMemcpyHostToDevice, s));
+  for (int w = 0; w < 2; ++w) {
+    QoGemm ga{};
+    ga.M = (int)v3; ga.N = v; ga.K = v; ga.n1 = ga.n2 = 1; ga.nitems = (int)npair;
+    ga.vec = (v % 2) == 0; ga.swap = true;
+    ga.items = wv_items + w * npair;
+    ga.C = Wv;
+    ga.cm = Idx4{1, v, v, v3, 0, w == 0 ? v2 : (long long)v, 1};
+    ga.cn = Idx4{1, 1, 1, w == 0 ? (long long)v : v2, 0, 0, 0};
+    ga.accumulate = w;
+    HIPCK(qo_gemm(ga, s));
+  }
   // Wbar_ijk^abm (Eq. q_w_vvo_ooo) as Wo[i][j][k][a][b][m]
   {
     const DT t2 = dense(ctx->t2, {o, o, v, v});
     const DT gd = dense(g, {o, o, o, v, v, o}), wd = dense(Wo, {o, o, o, v, v, o});
-    STCK(contract(qa, s, F, 1.0, Vview(ctx, Vb, "ovvo"), "maei", t2, "jkbe", 0.0, gd, "ijkabm"));
-    STCK(contract(qa, s, F, 1.0, Vview(ctx, Vb, "ovov"), "make", t2, "jibe", 1.0, gd, "ijkabm"));
-    STCK(contract(qa, s, F, -0.5, Vview(ctx, Vb, "oooo"), "mnki", t2, "njab", 1.0, gd, "ijkabm"));
+    STCK(contract(*qa, s, F, 1.0, Vview(ctx, Vb, "ovvo"), "maei", t2, "jkbe", 0.0, gd, "ijkabm"));
+    STCK(contract(*qa, s, F, 1.0, Vview(ctx, Vb, "ovov"), "make", t2, "jibe", 1.0, gd, "ijkabm"));
+    STCK(contract(*qa, s, F, -0.5, Vview(ctx, Vb, "oooo"), "mnki", t2, "njab", 1.0, gd, "ijkabm"));
     STCK(accumulate(s, 1.0, gd, "ijkabm", 0.0, wd, "ijkabm"));
     STCK(accumulate(s, 1.0, gd, "jikbam", 1.0, wd, "ijkabm"));
+    // and with m ahead of the virtual pair, in the place of the bracket
+    STCK(accumulate(s, 1.0, wd, "ijkabm", 0.0, dense(g, {o, o, o, o, v, v}), "ijkmab"));
   }
   // T3u[r][s][m] = t_{m r s}^{xyz} (full v^3 blocks) for every ordered (r, s)
   {
@@ -1717,196 +2015,58 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
   }
   HIPCK(fill(et, 0.0, ntask + 1, s));
 
-  std::vector<double> eps((size_t)n);
-  HIPCK(hipMemcpyAsync(eps.data(), ctx->eps, sizeof(double) * n, hipMemcpyDeviceToHost, s));
-  HIPCK(hipStreamSynchronize(s));
-  const bool nt_ok = (v % 2) == 0;  // K-contiguous MFMA kernel: even K and 16-byte aligned rows
-  auto gemm_x1_y1 = [&](const double* A, long long lda, const double* Bm, long long ldb, double* C, long long M,
-                        long long N, double alpha) -> int {
-    // C[M][N] = alpha * sum_e A[m][e] B[e][n], K = v
-    if (nt_ok) {
-      NtArgs na{};
-      na.M = (int)M; na.N = (int)N; na.K = v; na.batch = 1;
-      na.A = A; na.lda = lda; na.B = Bm; na.ldb = ldb; na.b_kn = 1;
-      na.C = C; na.cm = idx1(N); na.cn = idx1(1);
-      na.alpha = alpha; na.beta = 0.0;
-      na.a_len = M * lda; na.b_len = (long long)v * ldb; na.c_len = M * N;
-      HIPCK(gemm_nt(na, F, s));
-    } else {
-      GemmArgs ga{};
-      ga.M = (int)M; ga.N = (int)N; ga.K = v; ga.batch = 1;
-      ga.A = A; ga.am = idx1(lda); ga.ak = idx1(1);
-      ga.B = Bm; ga.bk = idx1(ldb); ga.bn = idx1(1);
-      ga.C = C; ga.cm = idx1(N); ga.cn = idx1(1);
-      ga.alpha = alpha; ga.beta = 0.0;
-      ga.a_len = M * lda; ga.b_len = (long long)v * ldb; ga.c_len = M * N;
-      HIPCK(gemm(ga, F, s));
+  // Batches of tasks: 14 launches accumulate X and Y of every task of the
+  // batch, one more evaluates their energies.
+  double* XS = carve(ntb * v4);
+  double* YS = carve(ntb * v4);
+  double* part = carve(ntb * norb);
+  QoItem* d_items = (QoItem*)carve(kQoLaunches * ntb * item_n);
+  int4* d_tasks = (int4*)carve(2 * ntb);
+  int* d_at = (int*)carve((ntb + 1) / 2);
+  if (top > scratch_n) { ctx->err = "energy_q: scratch plan"; return CCT_EDEVICE; }
+  const QoOperands ops{VVVO, VVVOt, VVVOk, VVVOkt, VOOO, Wv, Wo, g, T3u, ctx->t2, T2r, T2l};
+  std::vector<int4> th;
+  std::vector<int> ah;
+  std::vector<QoItem> ih;
+  bool first = true;
+  auto flush = [&]() -> int {
+    if (th.empty()) return CCT_OK;
+    std::vector<QoItem> items;
+    QoLaunch ls[kQoLaunches];
+    if (!qo_plan(o, v, th, ops, items, ls)) {
+      ctx->err = "energy_q: operand out of range";
+      return CCT_EDEVICE;
     }
+    if (!first) HIPCK(hipStreamSynchronize(s));  // the host tables of the previous batch have been read
+    first = false;
+    ih.swap(items);
+    HIPCK(hipMemcpyAsync(d_items, ih.data(), sizeof(QoItem) * ih.size(), hipMemcpyHostToDevice, s));
+    HIPCK(hipMemcpyAsync(d_tasks, th.data(), sizeof(int4) * th.size(), hipMemcpyHostToDevice, s));
+    HIPCK(hipMemcpyAsync(d_at, ah.data(), sizeof(int) * ah.size(), hipMemcpyHostToDevice, s));
+    for (const QoLaunch& l : ls) {
+      QoGemm ga = l.g;
+      ga.items = d_items + l.first;
+      ga.C = l.y ? YS : XS;
+      HIPCK(qo_gemm(ga, s));
+    }
+    HIPCK(qo_energy(XS, YS, VVOO, ctx->t2, ctx->eps, d_tasks, d_at, (int)th.size(), orbits, o, v, part, et, s));
+    HIPCK(hipStreamSynchronize(s));
+    th.clear();
+    ah.clear();
     return CCT_OK;
   };
-  auto gemm_k_o = [&](const double* A, const double* Bm, long long bk, double* C, long long M, long long N) -> int {
-    // C[M][N] += -1/2 sum_m A[m][k] B[k][n], K = o, A rows of o, B rows at stride bk
-    if (nt_ok && o <= 16) {  // a streaming read-modify-write of C (even v: aligned pairs)
-      HIPCK(rank_k_update(C, N, A, o, Bm, bk, (int)M, N, o, -0.5, s));
-      return CCT_OK;
-    }
-    GemmArgs ga{};
-    ga.M = (int)M; ga.N = (int)N; ga.K = o; ga.batch = 1;
-    ga.A = A; ga.am = idx1(o); ga.ak = idx1(1);
-    ga.B = Bm; ga.bk = idx1(bk); ga.bn = idx1(1);
-    ga.C = C; ga.cm = idx1(N); ga.cn = idx1(1);
-    ga.alpha = -0.5; ga.beta = 1.0;
-    ga.a_len = M * o; ga.b_len = (long long)(o - 1) * bk + N; ga.c_len = M * N;
-    HIPCK(gemm(ga, F, s));
-    return CCT_OK;
-  };
-  static const int P24[24][4] = {{0, 1, 2, 3}, {0, 1, 3, 2}, {0, 2, 1, 3}, {0, 2, 3, 1}, {0, 3, 1, 2}, {0, 3, 2, 1},
-                                 {1, 0, 2, 3}, {1, 0, 3, 2}, {1, 2, 0, 3}, {1, 2, 3, 0}, {1, 3, 0, 2}, {1, 3, 2, 0},
-                                 {2, 0, 1, 3}, {2, 0, 3, 1}, {2, 1, 0, 3}, {2, 1, 3, 0}, {2, 3, 0, 1}, {2, 3, 1, 0},
-                                 {3, 0, 1, 2}, {3, 0, 2, 1}, {3, 1, 0, 2}, {3, 1, 2, 0}, {3, 2, 0, 1}, {3, 2, 1, 0}};
-  auto term = [](const double* in, const int* pm, double coef) {
-    QPermTerm t{};
-    t.in = in;
-    t.dst = 1;
-    for (int k = 0; k < 4; ++k) t.perm[k] = pm[k];
-    t.coef = coef;
-    return t;
-  };
-  static const int ID[4] = {0, 1, 2, 3};
-  long long task = -1;
+  int task = -1;
   for (int i = 0; i < o; ++i)
     for (int j = i; j < o; ++j)
       for (int k = j; k < o; ++k)
         for (int l = k; l < o; ++l) {
           ++task;
           if ((i == j && j == k) || (j == k && k == l)) continue;
-          const int oc[4] = {i, j, k, l};
-          // distinct orderings q = o.s with the permutations that reach them
-          std::vector<std::array<int, 4>> qs;
-          std::vector<std::vector<int>> sig;
-          for (int p = 0; p < 24; ++p) {
-            const std::array<int, 4> q = {oc[P24[p][0]], oc[P24[p][1]], oc[P24[p][2]], oc[P24[p][3]]};
-            size_t x = 0;
-            while (x < qs.size() && qs[x] != q) ++x;
-            if (x == qs.size()) {
-              qs.push_back(q);
-              sig.emplace_back();
-            }
-            sig[x].push_back(p);
-          }
-          // slots in (q1, q2) order: orderings that share Wbar_{e q1 q2}^{abc}
-          // sit in adjacent slots and take one Y1 product between them
-          {
-            std::vector<size_t> ord(qs.size());
-            for (size_t x = 0; x < ord.size(); ++x) ord[x] = x;
-            std::stable_sort(ord.begin(), ord.end(), [&](size_t a1, size_t b1) {
-              return std::make_pair(qs[a1][1], qs[a1][2]) < std::make_pair(qs[b1][1], qs[b1][2]);
-            });
-            std::vector<std::array<int, 4>> qs2;
-            std::vector<std::vector<int>> sig2;
-            for (size_t x : ord) {
-              qs2.push_back(qs[x]);
-              sig2.push_back(sig[x]);
-            }
-            qs.swap(qs2);
-            sig.swap(sig2);
-          }
-          QCombineArgs cr{};
-          cr.v = v; cr.beta = 0.0; cr.tiled = tl ? 1 : 0;
-          for (size_t x = 0; x < qs.size(); ++x) {
-            const long long q0 = qs[x][0], q1 = qs[x][1], q2 = qs[x][2], q3 = qs[x][3];
-            double* X = Xb + (long long)x * v4;
-            double* G = Gb + (long long)x * v4;
-            // Y1 = 1/2 sum_e Wbar_{e q1 q2}^{abc} t_{q0 q3}^{ed} for this ordering and
-            // the following ones with the same (q1, q2): their t2 blocks side by side
-            // as the [e][(member, d)] operand, outputs to their adjacent slots
-            if (x == 0 || qs[x - 1][1] != q1 || qs[x - 1][2] != q2) {
-              size_t k = 1;
-              while (x + k < qs.size() && qs[x + k][1] == q1 && qs[x + k][2] == q2) ++k;
-              const double* Bm = ctx->t2 + (q0 * o + q3) * v2;
-              long long ldb = v;
-              if (k > 1) {
-                for (size_t j = 0; j < k; ++j)
-                  HIPCK(hipMemcpy2DAsync(Bc + (long long)j * v, sizeof(double) * k * v,
-                                         ctx->t2 + ((long long)qs[x + j][0] * o + qs[x + j][3]) * v2,
-                                         sizeof(double) * v, sizeof(double) * v, v, hipMemcpyDeviceToDevice, s));
-                Bm = Bc;
-                ldb = (long long)k * v;
-              }
-              const long long N = (long long)k * v;
-              const Idx2 cn = idx2(v, v4, 1);
-              const long long c_len = (24 - (long long)x) * v4;
-              if (nt_ok) {
-                NtArgs na{};
-                na.M = (int)v3; na.N = (int)N; na.K = v; na.batch = 1;
-                na.A = Wv + (q1 * o + q2) * v4; na.lda = v; na.B = Bm; na.ldb = ldb; na.b_kn = 1;
-                na.C = G; na.cm = idx1(v); na.cn = cn;
-                na.alpha = 0.5; na.beta = 0.0;
-                na.a_len = v4; na.b_len = (long long)v * ldb; na.c_len = c_len;
-                HIPCK(gemm_nt(na, F, s));
-              } else {
-                GemmArgs ga{};
-                ga.M = (int)v3; ga.N = (int)N; ga.K = v; ga.batch = 1;
-                ga.A = Wv + (q1 * o + q2) * v4; ga.am = idx1(v); ga.ak = idx1(1);
-                ga.B = Bm; ga.bk = idx1(ldb); ga.bn = idx1(1);
-                ga.C = G; ga.cm = idx1(v); ga.cn = cn;
-                ga.alpha = 0.5; ga.beta = 0.0;
-                ga.a_len = v4; ga.b_len = (long long)v * ldb; ga.c_len = c_len;
-                HIPCK(gemm(ga, F, s));
-              }
-            }
-            // X = 1/2 sum_e v^{ab}_{e q1} t_{q0 q2 q3}^{ecd} - 1/2 sum_m v^{am}_{q0 q1} t_{m q2 q3}^{bcd}
-            const double* t3r = T3u + (q2 * o + q3) * o * v3;
-            if (tl) X = Xb;  // one plain-layout scratch block; the sum goes to XT[x]
-            RCK(gemm_x1_y1(VVVO + q1 * v3, v, t3r + q0 * v3, v2, X, v2, v2, 0.5));
-            const double* VO = VOOO + (q0 * o + q1) * v * o;
-            // Y2 = -1/2 sum_m Wbar_{q0 q1 q2}^{abm} t_{m q3}^{cd}
-            const double* WO = Wo + ((q0 * o + q1) * o + q2) * v2 * o;
-            if (tl) {
-              HIPCK(rank_k_update_tiled(X, XT + (long long)x * T4, v, 1, VO, o, t3r, v3, o, -0.5, s));
-              HIPCK(rank_k_update_tiled(G, GT + (long long)x * T4, v, 2, WO, o, ctx->t2 + q3 * v2, o * v2, o, -0.5, s));
-              X = XT + (long long)x * T4;
-              G = GT + (long long)x * T4;
-            } else {
-              RCK(gemm_k_o(VO, t3r, v3, X, v, v3));
-              RCK(gemm_k_o(WO, ctx->t2 + q3 * v2, o * v2, G, v2, v2));
-            }
-            // R gets X + Y under every permutation reaching q; Abar gets
-            // X + 1/4 v^{ab}_{q0 q1} t_{q2 q3}^{cd} under the first of them
-            for (size_t k = 0; k < sig[x].size(); ++k) {
-              QPermTerm tx = term(X, P24[sig[x][k]], 1.0);
-              if (k == 0) {
-                tx.dst = 3;
-                tx.va = VVOO + (q0 * o + q1) * v2;
-                tx.vb = ctx->t2 + (q2 * o + q3) * v2;
-                tx.vcoef = 0.25;
-              }
-              cr.t[cr.nterms++] = tx;
-              cr.t[cr.nterms++] = term(G, P24[sig[x][k]], 1.0);
-            }
-          }
-          // one pass writes R and Abar (24 permutations: 48 terms, QMAXT)
-          HIPCK(perm_combine(Rb, Ab, cr, s));
-          // S(R) / eps_o: S = 2 (2 - P_cd) (2 - P_bc - P_bd) (2 - P_ab - P_ac - P_ad)
-          static const int Sab[4] = {1, 0, 2, 3}, Sac[4] = {2, 1, 0, 3}, Sad[4] = {3, 1, 2, 0};
-          static const int Sbc[4] = {0, 2, 1, 3}, Sbd[4] = {0, 3, 2, 1}, Scd[4] = {0, 1, 3, 2};
-          QCombineArgs c1{};
-          c1.v = v; c1.nterms = 4; c1.beta = 0.0;
-          c1.t[0] = term(Rb, ID, 2.0); c1.t[1] = term(Rb, Sab, -1.0);
-          c1.t[2] = term(Rb, Sac, -1.0); c1.t[3] = term(Rb, Sad, -1.0);
-          HIPCK(perm_combine(Xb, nullptr, c1, s));
-          QCombineArgs c2{};
-          c2.v = v; c2.nterms = 3; c2.beta = 0.0;
-          c2.t[0] = term(Xb, ID, 2.0); c2.t[1] = term(Xb, Sbc, -1.0); c2.t[2] = term(Xb, Sbd, -1.0);
-          HIPCK(perm_combine(Gb, nullptr, c2, s));
-          QCombineArgs c3{};
-          c3.v = v; c3.nterms = 2; c3.beta = 0.0;
-          c3.t[0] = term(Gb, ID, 4.0); c3.t[1] = term(Gb, Scd, -2.0);
-          c3.eps_v = ctx->eps + o;
-          c3.eps_occ = eps[i] + eps[j] + eps[k] + eps[l];
-          HIPCK(perm_combine(Rb, nullptr, c3, s));
-          HIPCK(dot(Ab, Rb, v4, et + task, ctx->red, s));
+          th.push_back(int4{i, j, k, l});
+          ah.push_back(task);
+          if ((long long)th.size() == ntb) RCK(flush());
         }
+  RCK(flush());
   HIPCK(reduce_sum(et, ntask, et + ntask, ctx->red, s));
   std::vector<double> h((size_t)ntask + 1);
   HIPCK(hipMemcpyAsync(h.data(), et, sizeof(double) * h.size(), hipMemcpyDeviceToHost, s));
@@ -2820,6 +2980,7 @@ void cct_destroy(cct_ctx* ctx) {
   (void)hipStreamSynchronize(ctx->s);  // nothing in flight may touch what is freed below
   for (void* p : ctx->owned) dev_free(ctx, p);
   dev_free(ctx, ctx->wsbuf);
+  dev_free(ctx, ctx->q_keep);
   for (int i = 0; i <= PH_N; ++i)
     if (ctx->ev[i]) (void)hipEventDestroy(ctx->ev[i]);
   for (hipEvent_t e : ctx->lad_ev) (void)hipEventDestroy(e);

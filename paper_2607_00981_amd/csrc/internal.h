@@ -279,51 +279,6 @@ hipError_t jacobi_t1t2(double* t1, const double* r1, double* t2, const double* r
 // W_diag: add c * F[a][d] on the (b == e) diagonal and c * F[b][e] on (a == d) for a [x][y][x][y] tensor.
 hipError_t add_pair_diag(double* W, const double* F, long long ldF, int nx, double c, hipStream_t s);
 
-// Permuted combination of v^4 virtual blocks (perturbative quadruples):
-//   out[w]  = beta * out[w]  + f(w) * sum_{t: dst_t & 1} coef_t * x_t(w)
-//   out2[w] = beta * out2[w] +        sum_{t: dst_t & 2} coef_t * (x_t(w) + vcoef_t * va_t[y0 v + y1] * vb_t[y2 v + y3])
-// with y = (w_{perm_t[0]}, .., w_{perm_t[3]}) and x_t(w) = in_t[y0][y1][y2][y3]
-// (row-major, w in [0, v)^4); f(w) = 1 / (eps_occ - sum_k eps_v[w_k]) when
-// eps_v is set, else 1.  out2 may be null (then no term may have dst & 2);
-// no input may be an output.
-constexpr int QMAXT = 48;
-struct QPermTerm {
-  const double* in;
-  int perm[4];
-  double coef;
-  int dst;            // 1: out, 2: out2, 3: both
-  const double* va;   // optional rank-one addend of the out2 contribution (nullptr: none)
-  const double* vb;
-  double vcoef;
-};
-struct QCombineArgs {
-  int v, nterms;
-  QPermTerm t[QMAXT];
-  double beta;
-  const double* eps_v;  // device, v virtual orbital energies (nullptr: no division)
-  double eps_occ;       // sum of the four occupied orbital energies
-  int tiled;            // 1: every input is tile-major (see rank_k_update_tiled)
-};
-hipError_t perm_combine(double* out, double* out2, const QCombineArgs& a, hipStream_t s);
-// C[m][n] += alpha * sum_{k<K} A[m*lda + k] * B[k*ldb + n], m < M, n < N, C
-// row stride ldc: streaming update for K <= 16.  Requires N, ldc, ldb even
-// and 16-byte aligned C and B (hipErrorInvalidValue otherwise).
-hipError_t rank_k_update(double* C, long long ldc, const double* A, long long lda, const double* B, long long ldb,
-                         int M, long long N, int K, double alpha, hipStream_t s);
-// The same update of a v^4 block C (row-major [a][b][c][d]; rows m cover the
-// first rsplit of the four axes, columns n the rest) written to D in the
-// tile-major layout instead of back to C: 8^4 tiles of 4096 consecutive
-// doubles, tiles in row-major order over ceil(v/8)^4, elements inside a tile
-// row-major; padding positions are not written.  Requires v even.
-hipError_t rank_k_update_tiled(const double* C, double* D, int v, int rsplit, const double* A, long long lda,
-                               const double* B, long long ldb, int K, double alpha, hipStream_t s);
-// Elements of a tile-major v^4 block (padded to whole tiles).
-static inline long long tiled_len(int v) {
-  const long long nt = (v + 7) / 8;
-  return nt * nt * nt * nt * 4096;
-}
-
-// --- perturbative quadruples in the virtual-tuple order --------------------
 // Four-level index map: i = ((d0 n1 + d1) n2 + d2) n3 + d3 -> sum_k d_k s_k
 // (n1, n2, n3 >= 1).
 struct Idx4 {
@@ -331,6 +286,49 @@ struct Idx4 {
   long long s0, s1, s2, s3;
 };
 
+// --- perturbative quadruples in the occupied-tuple order ----------------------
+// Segmented product over a device table of items:
+//   C_z(m, n) (+)= sum_s coef_s sum_{k < K} A_s(m, k) B_s(k, n)
+// A_s is K-contiguous, row m = (d0 n1 + d1) n2 + d2 at a + d0 rs0 + d1 rs1 +
+// d2 rs2; B_s is N-contiguous, row k at b + k ldb.  An item without segments
+// writes zeros (or adds nothing).  C through the four-level maps.
+constexpr int QO_SEG = 4;
+struct QoSeg {
+  const double *a, *b;
+  long long ldb;
+  double coef;
+  int rs0, rs1, rs2, pad;
+};
+struct QoItem {
+  long long c;  // offset of the item's output from C
+  int nseg, pad;
+  QoSeg seg[QO_SEG];
+};
+struct QoGemm {
+  int M, N, K, n1, n2, nitems;
+  bool vec;   // every segment allows 16-byte loads (even K, N, strides; aligned bases)
+  bool swap;  // the unit-stride axis of C lies in the rows
+  const QoItem* items;  // device
+  double* C;
+  Idx4 cm, cn;
+  int accumulate;
+};
+hipError_t qo_gemm(const QoGemm& g, hipStream_t s);
+// Energies of ntasks occupied tuples (i, j, k, l) = tasks[y] from their
+// accumulators X and Y ([y][v^4]; with equal occupied labels the sum over one
+// representative of each coset of the tuple's stabiliser G):
+//   etask[at[y]] = sum_w (X(w) + V(w) / |G|) U(w),
+//   U = (1/den) sum_pi c_pi R(w o pi), R = sum_{tau in G} (X + Y) o tau,
+// VVOO[i][j][a][b] = v^{ab}_{ij}, V the six v t splits.  part: ntasks x
+// qo_orbits(v) doubles.
+long long qo_orbits(int v);
+hipError_t qo_energy(const double* X, const double* Y, const double* VVOO, const double* t2, const double* eps,
+                     const int4* tasks, const int* at, int ntasks, const unsigned* orbits, int o, int v, double* part,
+                     double* etask, hipStream_t s);
+// The qo_orbits(v) block orbits that qo_energy walks (one word each).
+hipError_t qo_orbit_table(unsigned* orbits, int v, hipStream_t s);
+
+// --- perturbative quadruples in the virtual-tuple order --------------------
 // Segmented, digit-batched FP64 product on the matrix cores:
 //   C[z](m, n) (+)= alpha * sum_s sum_{k < K_s} A_s[z](m, k) B_s[z](k, n)
 // The batch index z (gridDim.z) is split into nd digits of radices rad (the
