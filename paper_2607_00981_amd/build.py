@@ -50,12 +50,16 @@ def build(verbose=False, jobs=4):
                 cmd += ["-x", "hip"]
             cmd += ["-c", os.path.join(CSRC, src), "-o", obj]
             objs.append(obj)
-            procs.append((src, cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)))
+            # a file, not a pipe: a compiler that warns once per kernel fills a pipe that nobody reads yet
+            log = open(obj + ".log", "w+b")
+            procs.append((src, log, subprocess.Popen(cmd, stdout=log, stderr=subprocess.STDOUT)))
             if len([p for p in procs if p[2].poll() is None]) >= jobs:
                 procs[0][2].wait()
-        for src, cmd, p in procs:
-            out, _ = p.communicate()
-            text = out.decode(errors="replace")
+        for src, log, p in procs:
+            p.wait()
+            with log:
+                log.seek(0)
+                text = log.read().decode(errors="replace")
             text = "\n".join(l for l in text.splitlines() if "packed-fp32-ops" not in l and l.strip())
             if p.returncode != 0:
                 raise RuntimeError(f"hipcc failed on {src}:\n{text}")
