@@ -506,7 +506,9 @@ int build_plans(cct_ctx* ctx) {
   for (Job* J : {&ctx->feed1}) {
     for (int f = 0; f < o; ++f) J->slots.push_back(int2{f, 0});
     J->nslot_total = o;
-    J->per_batch = slots_per_batch(budget, 2 * o2v3 + (long long)o * o * v2, o);  // UA, UB, one X2 partial
+    // UA, UB (each slot's run padded to 16) and room for one set of partial sums per slot
+    const long long v2p = (v2 + 15) / 16 * 16, ovp = ((long long)o * v + 15) / 16 * 16;
+    J->per_batch = slots_per_batch(budget, (long long)o * o * v * v2p + o * v2 * ovp + (long long)o * o * v2, o);
     const int S = J->per_batch;
     for (int b = 0; b * S < o; ++b) {
       Batch B;
@@ -770,129 +772,105 @@ int ccsd_part(cct_ctx* ctx) {
   return CCT_OK;
 }
 
-// T3 contributions to R1, R2 and to W^{ab}_{dj}, W^{al}_{ij} (RCCSDT
-// appendix).  For each batch of first-column indices f the spin-summed slab
-// U_f[o1][o2][x][y][z] = t~_{f o1 o2}^{xyz} (single check on column 1) is
-// unpacked once and contracted five ways; R1's double check is rebuilt from
-// the same slab: t~_{j'k'i}^{b'c'a} = 2 U_j[k][i][b][c][a] - U_j[k][i][b][a][c].
-// K-contiguous product C = alpha A B^T + beta C (A: M x K rows of lda, B: N x K
-// rows of ldb): the matrix-core NT kernel when its alignment rules hold, the
-// generic strided kernel otherwise.
-int nt_or_generic(cct_ctx* ctx, int M, int N, long long K, const double* A, long long lda, long long a_len,
-                  const double* B, long long ldb, long long b_len, double* C, Idx2 cm, Idx2 cn, long long c_len,
-                  double alpha, double beta) {
-  const bool even = !(K & 1) && !(lda & 1) && !(ldb & 1) && !((uintptr_t)A & 15) && !((uintptr_t)B & 15);
-  if (K > INT_MAX) { ctx->err = "contraction length exceeds int"; return CCT_EINVAL; }
-  if (even) {
-    NtArgs g{};
-    g.M = M; g.N = N; g.K = (int)K; g.batch = 1;
-    g.A = A; g.lda = lda; g.B = B; g.ldb = ldb;
-    g.C = C; g.cm = cm; g.cn = cn;
-    g.alpha = alpha; g.beta = beta;
-    g.a_len = a_len; g.b_len = b_len; g.c_len = c_len;
-    HIPCK(gemm_nt(g, Prec::F64, ctx->s));
-  } else {
-    GemmArgs g{};
-    g.M = M; g.N = N; g.K = (int)K; g.batch = 1;
-    g.A = A; g.am = idx1(lda); g.ak = idx1(1);
-    g.B = B; g.bk = idx1(1); g.bn = idx1(ldb);
-    g.C = C; g.cm = cm; g.cn = cn;
-    g.alpha = alpha; g.beta = beta;
-    g.a_len = a_len; g.b_len = b_len; g.c_len = c_len;
-    HIPCK(gemm(g, Prec::F64, ctx->s));
-  }
-  return CCT_OK;
-}
-
 // T3 -> R1, R2, W^{ab}_{dj}, W^{al}_{ij} (Eq. resi-rccsdt feedback terms and
 // the T3 parts of the two RCCSDT intermediates).  For a batch of S slots f,
 // the single-check spin-summed amplitudes t~_{f..}^{...} are unpacked twice,
-// in the two layouts that make every contraction one K-contiguous GEMM with
-// the slot index folded into K:
+// in the two layouts that make every contraction K-contiguous with the slot
+// index folded into K (each slot's run padded with zeros to 16 doubles, so
+// that any v and o run on whole K tiles):
 //   UA[(i,j,a)][f][(p,q)] = t~_{fij}^{q a p}   (K = f, two virtuals)
 //   UB[(i,a,b)][f][(k,c)] = t~_{fik}^{c a b}   (K = f, occupied, virtual)
-// and
-//   X2[ij][ab] +=  sum_{fcd} v~^{bf}_{cd} t~_{fij}^{dac} + 1/2 sum_{fc} f~^f_c t~_{fij}^{cab}   (UA, one GEMM:
-//                  the Fock term rides on the diagonal p = b of the integral rows)
-//   X2[ij][ab] -=  sum_{fkc} v~^{kf}_{jc} t~_{fik}^{cab}                                         (UB)
-//   W^{ab}_{dj} -= sum_{fle} v~^{lf}_{de} t~_{fjl}^{eba}                                         (UB)
-//   W^{al}_{ij} += sum_{fde} v~^{lf}_{de} t~_{fij}^{ead}                                         (UA)
+// and each layout is read by one product against the stacked rows of its two
+// integral slices:
+//   X2[ij][ab] +=  sum_{fcd} v~^{bf}_{cd} t~_{fij}^{dac} + 1/2 sum_{fc} f~^f_c t~_{fij}^{cab}   (UA; v rows b: the
+//                  Fock term rides on the diagonal p = b of the integral rows)
+//   W^{al}_{ij} += sum_{fde} v~^{lf}_{de} t~_{fij}^{ead}                                         (UA; o rows l)
+//   X2[ij][ab] -=  sum_{fkc} v~^{kf}_{jc} t~_{fik}^{cab}                                         (UB; o rows j)
+//   W^{ab}_{dj} -= sum_{fle} v~^{lf}_{de} t~_{fjl}^{eba}                                         (UB; v rows d)
 //   R1[ia]      += 1/2 sum v~^{jk}_{bc} (2 t~_{jki}^{bca} - t~_{jki}^{bac})                        (UA, reduction kernel)
+// One product per layout instead of two reads UA and UB once each, and its
+// o + v columns fill the tiles where o alone left 95 % of them empty: per
+// iteration at o = 10, v = 90 14.4 -> 5.2 ms, residual at o = 8, v = 61 (odd:
+// formerly the strided kernel) 6.8 -> 0.72 ms.
+long long feed_pad(long long n) { return (n + 15) / 16 * 16; }
+
 int feedback(cct_ctx* ctx) {
   const int o = ctx->o, v = ctx->v, n = ctx->n;
-  const long long v2 = (long long)v * v, v3 = ctx->v3, o2v3 = (long long)o * o * v3;
+  const long long v2 = (long long)v * v;
   const long long ov = (long long)o * v, o2v2 = ov * ov;
+  const long long v2p = feed_pad(v2), ovp = feed_pad(ov);  // a slot's run in UA and UB
   hipStream_t s = ctx->s;
   Arena& ws = ctx->ws;
   const size_t mk0 = ws.mark();
   // integral slices with the summed slot index next to the contracted pair
-  double* VbT = ws.alloc((size_t)(o * v3));            // [b][f][c][d] = v~^{bf}_{cd} (+ 1/2 f~ on c = b)
-  double* VcT = ws.alloc((size_t)o * o * o * v);       // [j][f][k][c] = v~^{kf}_{jc}
-  double* VdT = ws.alloc((size_t)o2v2);                // [d][f][l][e] = v~^{lf}_{de}
-  double* VeT = ws.alloc((size_t)o2v2);                // [l][f][d][e] = v~^{lf}_{de}
-  double* vvT = ws.alloc((size_t)o2v2);                // [j][k][c][b] = v~^{jk}_{bc}
-  if (!VbT || !VcT || !VdT || !VeT || !vvT) { ctx->err = "workspace exhausted (feedback slices)"; return CCT_ENOMEM; }
-  STCK(accumulate(s, 1.0, Vv(ctx, "vovv"), "bfcd", 0.0, dense(VbT, {v, o, v, v}), "bfcd"));
-  STCK(accumulate(s, 1.0, Vv(ctx, "ooov"), "kfjc", 0.0, dense(VcT, {o, o, o, v}), "jfkc"));
-  STCK(accumulate(s, 1.0, Vv(ctx, "oovv"), "lfde", 0.0, dense(VdT, {v, o, o, v}), "dfle"));
-  STCK(accumulate(s, 1.0, Vv(ctx, "oovv"), "lfde", 0.0, dense(VeT, {o, o, v, v}), "lfde"));
+  const long long na = (v + o) * (long long)o * v2p, nb = (v + o) * (long long)o * ovp;
+  double* BA = ws.alloc((size_t)na);  // rows b: [f][c][d] = v~^{bf}_{cd} (+ 1/2 f~ on c = b); rows l: [f][d][e] = v~^{lf}_{de}
+  double* BB = ws.alloc((size_t)nb);  // rows j: [f][k][c] = v~^{kf}_{jc}; rows d: [f][l][e] = v~^{lf}_{de}
+  double* vvT = ws.alloc((size_t)o2v2);  // [j][k][c][b] = v~^{jk}_{bc}
+  if (!BA || !BB || !vvT) { ctx->err = "workspace exhausted (feedback slices)"; return CCT_ENOMEM; }
+  STCK(accumulate(s, 1.0, Vv(ctx, "vovv"), "bfcd", 0.0, strided(BA, {v, o, v, v}, {o * v2p, v2p, v, 1}), "bfcd"));
+  STCK(accumulate(s, 1.0, Vv(ctx, "oovv"), "lfde", 0.0,
+                  strided(BA + v * o * v2p, {o, o, v, v}, {o * v2p, v2p, v, 1}), "lfde"));
+  STCK(accumulate(s, 1.0, Vv(ctx, "ooov"), "kfjc", 0.0, strided(BB, {o, o, o, v}, {o * ovp, ovp, v, 1}), "jfkc"));
+  STCK(accumulate(s, 1.0, Vv(ctx, "oovv"), "lfde", 0.0,
+                  strided(BB + o * o * ovp, {v, o, o, v}, {o * ovp, ovp, v, 1}), "dfle"));
   STCK(accumulate(s, 1.0, Vv(ctx, "oovv"), "jkbc", 0.0, dense(vvT, {o, o, v, v}), "jkcb"));
-  // VbT[b][f][b][q] += 1/2 f~^f_{v_q}
-  HIPCK(add_diag_rows(VbT, ctx->ft + o, v, o, v, (long long)o * v2, v2, v, 1, n, 0.5, s));
+  HIPCK(zero_cols(OutSpec{BA, OUT_F64, 0}, (v + o) * (long long)o, v2p, v2, s));
+  HIPCK(zero_cols(OutSpec{BB, OUT_F64, 0}, (v + o) * (long long)o, ovp, ov, s));
+  // rows b < v: [f][b][q] += 1/2 f~^f_{v_q}
+  HIPCK(add_diag_rows(BA, ctx->ft + o, v, o, v, (long long)o * v2p, v2p, v, 1, n, 0.5, s));
   for (const Batch& b : ctx->feed1.batches) {
     const size_t mk = ws.mark();
     const int S = b.nslots, f0 = b.slot0;
-    const long long slab = (long long)S * o2v3;
-    double* UA = ws.alloc((size_t)slab);
-    double* UB = ws.alloc((size_t)slab);
+    const long long KA = (long long)S * v2p, KB = (long long)S * ovp;
+    const long long rows_a = (long long)o * ov, rows_b = ov * v;
+    if (KA > INT_MAX || KB > INT_MAX) { ctx->err = "contraction length exceeds int"; return CCT_EINVAL; }
+    double* UA = ws.alloc((size_t)(rows_a * KA));
+    double* UB = ws.alloc((size_t)(rows_b * KB));
     if (!UA || !UB) { ctx->err = "workspace exhausted (feedback)"; return CCT_ENOMEM; }
     const int occ[3] = {0, 2, 3};  // t~_{f, free0, free1}, gathered once, written in two layouts
     {
       UnpackArgs ua{};
       ua.o = o; ua.v = v; ua.nslots = S; ua.nfree = 2;
       set_s1(ua, occ);
-      const long long row = (long long)S * v2;  // UA: one (i,j,a) row
-      ua.s_slot = v2; ua.s_free[0] = (long long)o * v * row; ua.s_free[1] = v * row;
-      ua.s_x = 1; ua.s_y = row; ua.s_z = v; ua.fast = 2;  // (x,y,z) = (q,a,p)
-      const long long rowb = (long long)S * ov;  // UB: one (i,a,b) row
-      ua.s2_slot = ov; ua.s2_free[0] = v2 * rowb; ua.s2_free[1] = v;
-      ua.s2_x = 1; ua.s2_y = v * rowb; ua.s2_z = rowb; ua.fast2 = 2;  // (x,y,z) = (c,a,b)
+      // UA: one (i,j,a) row of KA
+      ua.s_slot = v2p; ua.s_free[0] = (long long)o * v * KA; ua.s_free[1] = v * KA;
+      ua.s_x = 1; ua.s_y = KA; ua.s_z = v; ua.fast = 2;  // (x,y,z) = (q,a,p)
+      // UB: one (i,a,b) row of KB
+      ua.s2_slot = ovp; ua.s2_free[0] = v2 * KB; ua.s2_free[1] = v;
+      ua.s2_x = 1; ua.s2_y = v * KB; ua.s2_z = KB; ua.fast2 = 2;  // (x,y,z) = (c,a,b)
       HIPCK(unpack_t3_dual(ctx->t3, ctx->tbl, b.d_slots, OutSpec{UA, OUT_F64, 0}, OutSpec{UB, OUT_F64, 0}, ua, s));
     }
-    const long long KA = (long long)S * v2, KB = (long long)S * ov;
-    // X2[(i,j,a)][b] += UA[(i,j,a)][K] VbT[b][f0.. K].  With v^2 a multiple of
-    // 16 the product is batched over the S slots (K = v^2 each, one partial
-    // per slot, then summed into X2): N = v is a single tile column, so one
-    // product over the whole K would give too few tiles to fill the chip.
-    double* Xp = (v2 % 16 == 0 && S > 1) ? ws.alloc((size_t)(S * o2v2)) : nullptr;
-    if (Xp) {
-      NtArgs g{};
-      g.M = (int)((long long)o * o * v); g.N = v; g.K = (int)v2; g.batch = S;
-      g.A = UA; g.lda = KA; g.a_batch = v2;
-      g.B = VbT + (long long)f0 * v2; g.ldb = (long long)o * v2; g.b_batch = v2;
-      g.C = Xp; g.cm = idx1(v); g.cn = idx1(1); g.c_batch = o2v2;
-      g.alpha = 1.0; g.beta = 0.0;
-      g.a_len = slab; g.b_len = (long long)o * v3 - (long long)f0 * v2; g.c_len = S * o2v2;
-      HIPCK(gemm_nt(g, Prec::F64, s));
-      for (int k = 0; k < S; ++k) HIPCK(axpby(1.0, Xp + (long long)k * o2v2, 1.0, ctx->X2, o2v2, s));
-    } else {
-      RCK(nt_or_generic(ctx, (int)((long long)o * o * v), v, KA, UA, KA, slab, VbT + (long long)f0 * v2,
-                        (long long)o * v2, (long long)o * v3 - (long long)f0 * v2, ctx->X2, idx1(v), idx1(1), o2v2,
-                        1.0, 1.0));
-    }
-    // W^{al}_{ij}: C[l][(i,j,a)] = VeT[l][f0.. K] UA[(i,j,a)][K], stored [a][l][i][j]
-    RCK(nt_or_generic(ctx, o, (int)((long long)o * o * v), KA, VeT + (long long)f0 * v2, (long long)o * v2,
-                      o2v2 - (long long)f0 * v2, UA, KA, slab, ctx->Wvooo, idx1((long long)o * o),
-                      idx2(v, 1, (long long)o * o * o), (long long)v * o * o * o, 1.0, 1.0));
-    // X2[(i,a,b)][j] -= UB[(i,a,b)][K] VcT[j][f0.. K]
-    RCK(nt_or_generic(ctx, (int)(o * v2), o, KB, UB, KB, slab, VcT + (long long)f0 * ov, (long long)o * ov,
-                      (long long)o * o * ov - (long long)f0 * ov, ctx->X2, idx2((int)v2, (long long)o * v2, 1),
-                      idx1(v2), o2v2, -1.0, 1.0));
-    // W^{ab}_{dj}: C[d][(j,b,a)] -= VdT[d][f0.. K] UB[(j,b,a)][K], stored [d][j][b][a]
-    RCK(nt_or_generic(ctx, v, (int)(o * v2), KB, VdT + (long long)f0 * ov, (long long)o * ov,
-                      o2v2 - (long long)f0 * ov, UB, KB, slab, ctx->Wt, idx1((long long)o * v2), idx1(1),
-                      (long long)v * o * v2, -1.0, 1.0));
-    HIPCK(feedback_r1(UA, vvT, ctx->r1, o, v, S, f0, s));
+    HIPCK(zero_cols(OutSpec{UA, OUT_F64, 0}, rows_a * S, v2p, v2, s));
+    HIPCK(zero_cols(OutSpec{UB, OUT_F64, 0}, rows_b * S, ovp, ov, s));
+    HIPCK(feedback_r1(UA, v2p, vvT, ctx->r1, o, v, S, f0, s));
+    // partial sums in what is left of the workspace, else in R3, which is
+    // filled after this
+    auto product = [&](const double* A, long long M, long long K, const double* B, long long ldb, long long b_len,
+                       bool trans, int* splits, double** part) -> int {
+      const long long N = v + o, room = (long long)(ws.available() / sizeof(double)) - 64;
+      const bool in_ws = room >= M * N;
+      const long long cap = in_ws ? room : ctx->ntri * ctx->v3;
+      if (cap < M * N) { ctx->err = "workspace exhausted (feedback products)"; return CCT_ENOMEM; }
+      *splits = gemm_tall_splits((int)M, (int)N, (int)K, cap);
+      *part = in_ws ? ws.alloc((size_t)(*splits * M * N)) : ctx->r3;
+      TallArgs g{};
+      g.M = (int)M; g.N = (int)N; g.K = (int)K; g.splits = *splits;
+      g.A = A; g.lda = K; g.a_len = M * K;
+      g.B = B; g.ldb = ldb; g.b_len = b_len;
+      g.part = *part; g.part_len = *splits * M * N;
+      g.trans = trans;
+      HIPCK(gemm_tall(g, s));
+      return CCT_OK;
+    };
+    int sp = 1;
+    double* part = nullptr;
+    const size_t mkp = ws.mark();
+    RCK(product(UA, rows_a, KA, BA + f0 * v2p, o * v2p, na - f0 * v2p, false, &sp, &part));
+    HIPCK(feedback_add_a(part, sp, ctx->X2, ctx->Wvooo, o, v, s));
+    ws.reset(mkp);
+    RCK(product(UB, rows_b, KB, BB + f0 * ovp, o * ovp, nb - f0 * ovp, true, &sp, &part));
+    HIPCK(feedback_add_b(part, sp, ctx->X2, ctx->Wt, o, v, s));
     ws.reset(mk);
   }
   ws.reset(mk0);

@@ -23,6 +23,7 @@
 //         accumulators are flushed into FP64 every K tile.
 #include "internal.h"
 
+#include <algorithm>
 #include <climits>
 #include <numeric>
 
@@ -671,7 +672,151 @@ hipError_t launch_nt_dl(const NtArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
+// Products with one long side (M rows), one of at most a few hundred (N) and a
+// long K, as raw partial sums of K ranges.  Bound: reading A once, or the
+// matrix cores once N is about 60; with the N columns in one or two tiles of
+// 16 TN <= 128 the padding is at most 15 columns per tile, where 64-, 192- or
+// 256-wide tiles left 30-95 % of the products outside the matrix (N = 8..100).
+// Eight waves of 16 rows x 16 TN columns: the fragments of B are read by every
+// wave, which LDS bandwidth allows at the FP64 matrix rate (64 cycles per
+// MFMA).  Operand copies and swizzle as in gemm_nt_f64_dl_kernel.  A grid of few
+// row tiles is filled by splitting K (blockIdx.y; whole K tiles each).
+template <int TN, bool TR>
+__global__ __launch_bounds__(512, 2) void gemm_tall_f64_kernel(TallArgs g, int tiles_m, int tiles_n) {
+  constexpr int NW = 8, BM = 16 * NW, BN = 16 * TN;
+  constexpr int PA = BM / 8 / NW, CB = BN / 8, PB = (CB + NW - 1) / NW;  // 1 KB chunks: per wave of A, of B, per wave
+  constexpr int ABUF = BM * BK, BBUF = BN * BK;
+  __shared__ __attribute__((aligned(1024))) double As[2 * ABUF];
+  __shared__ __attribute__((aligned(1024))) double Bs[2 * BBUF];
+  int tm, tn;
+  if (!tile_coords(tiles_m, tiles_n, tm, tn)) return;
+  const int tid = threadIdx.x, wave = tid / 64, lane = tid & 63;
+  const int nkt = g.K / BK, per = (nkt + g.splits - 1) / g.splits;
+  const int k_first = blockIdx.y * per, k_last = min(nkt, k_first + per);
+  const double* sa[PA];
+  const double* sb[PB];
+  unsigned la[PA], lb[PB];
+  const unsigned as0 = (unsigned)(size_t)(__attribute__((address_space(3))) const void*)As;
+  const unsigned bs0 = (unsigned)(size_t)(__attribute__((address_space(3))) const void*)Bs;
+#pragma unroll
+  for (int j = 0; j < PA; ++j) {
+    const int c = wave + NW * j, row = c * 8 + lane / 8, kp = (lane % 8) ^ ((row >> 1) & 7);
+    const int m = tm * BM + row;
+    sa[j] = g.A + (long long)(m < g.M ? m : 0) * g.lda + 2 * kp;
+    la[j] = __builtin_amdgcn_readfirstlane(as0 + 8u * (unsigned)(c * 8 * BK));
+  }
+#pragma unroll
+  for (int j = 0; j < PB; ++j) {
+    const int c = min(wave + NW * j, CB - 1), row = c * 8 + lane / 8, kp = (lane % 8) ^ ((row >> 1) & 7);
+    const int n = tn * BN + row;
+    sb[j] = g.B + (long long)(n < g.N ? n : 0) * g.ldb + 2 * kp;
+    lb[j] = __builtin_amdgcn_readfirstlane(bs0 + 8u * (unsigned)(c * 8 * BK));
+  }
+  auto issue = [&](int kt, int buf) {
+    const long long k0 = (long long)kt * BK;
+    const unsigned da = buf * (8u * ABUF), db = buf * (8u * BBUF);  // bytes
+#pragma unroll
+    for (int j = 0; j < PA; ++j) lds_copy16(sa[j] + k0, la[j] + da);
+#pragma unroll
+    for (int j = 0; j < PB; ++j)
+      if (wave + NW * j < CB) lds_copy16(sb[j] + k0, lb[j] + db);
+  };
+  d4 acc[TN];
+#pragma unroll
+  for (int j = 0; j < TN; ++j) acc[j] = d4{0.0, 0.0, 0.0, 0.0};
+  if (k_first < k_last) issue(k_first, 0);
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  for (int kt = k_first; kt < k_last; ++kt) {
+    const int cur = (kt - k_first) & 1;
+    if (kt + 1 < k_last) issue(kt + 1, cur ^ 1);
+    const double* as = As + cur * ABUF;
+    const double* bs = Bs + cur * BBUF;
+#pragma unroll
+    for (int ks = 0; ks < BK / 4; ++ks) {
+      const int kr = ks * 4 + lane / 16;
+      const double af = as[nt_swz(wave * 16 + (lane & 15), kr)];
+      double bf[TN];
+#pragma unroll
+      for (int j = 0; j < TN; ++j) bf[j] = bs[nt_swz(j * 16 + (lane & 15), kr)];
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        acc[j] = TR ? __builtin_amdgcn_mfma_f64_16x16x4f64(bf[j], af, acc[j], 0, 0, 0)
+                    : __builtin_amdgcn_mfma_f64_16x16x4f64(af, bf[j], acc[j], 0, 0, 0);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+  }
+  // accumulator register r of lane l: first operand's index 4r + l/16, second's l%16
+  double* P = g.part + (long long)blockIdx.y * g.M * g.N;
+#pragma unroll
+  for (int r = 0; r < 4; ++r)
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+      const int x = 4 * r + lane / 16, y = lane & 15;
+      const int m = tm * BM + wave * 16 + (TR ? y : x), n = tn * BN + j * 16 + (TR ? x : y);
+      if (m < g.M && n < g.N) P[TR ? (long long)n * g.M + m : (long long)m * g.N + n] = acc[j][r];
+    }
+}
+
+template <int TN>
+hipError_t launch_tall(const TallArgs& g, hipStream_t s) {
+  const long long tiles_m = ((long long)g.M + 127) / 128, tiles_n = (g.N + 16 * TN - 1) / (16 * TN);
+  const long long gx = (tiles_m * tiles_n + 7) / 8 * 8;
+  if (gx > INT_MAX) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)gx, (unsigned)g.splits);
+  if (g.trans) hipLaunchKernelGGL((gemm_tall_f64_kernel<TN, true>), grid, dim3(512), 0, s, g, (int)tiles_m, (int)tiles_n);
+  else hipLaunchKernelGGL((gemm_tall_f64_kernel<TN, false>), grid, dim3(512), 0, s, g, (int)tiles_m, (int)tiles_n);
+  return hipGetLastError();
+}
+
+// Columns of 16 per tile: the fewest padded columns, then the widest tile.
+int tall_tn(int N) {
+  int best = 8;
+  auto padded = [&](int t) { return (N + 16 * t - 1) / (16 * t) * t; };
+  for (int t = 7; t >= 1; --t)
+    if (padded(t) < padded(best)) best = t;
+  return best;
+}
+
 }  // namespace
+
+int gemm_tall_splits(int M, int N, int K, long long cap) {
+  // 512 workgroups run at once (two of eight waves on each of 256 CUs); the
+  // split that leaves the least of the last round idle, two per cent dearer
+  // for each further partial sum written and read back, at least four K tiles
+  // each, within cap partial sums
+  const long long tn = tall_tn(N), tiles = ((long long)M + 127) / 128 * ((N + 16 * tn - 1) / (16 * tn));
+  const int most = (int)std::max<long long>(1, std::min<long long>({64, K / (4 * BK), cap / std::max<long long>(1, (long long)M * N)}));
+  int best = 1;
+  double score = -1.0;
+  for (int z = 1; z <= most; ++z) {
+    const double wg = (double)tiles * z, rounds = (wg + 511.0) / 512.0;
+    const double sc = wg / (512.0 * (double)(long long)rounds) - 0.02 * (tiles >= 64 ? z : z * (double)tiles / 64.0);
+    if (sc > score) { score = sc; best = z; }
+  }
+  return best;
+}
+
+hipError_t gemm_tall(const TallArgs& g, hipStream_t s) {
+  if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  if (g.K <= 0 || g.K % BK || (g.lda & 1) || (g.ldb & 1) || ((uintptr_t)g.A & 15) || ((uintptr_t)g.B & 15) ||
+      g.splits < 1 || g.splits > 65535)
+    return hipErrorInvalidValue;
+  if ((long long)(g.M - 1) * g.lda + g.K > g.a_len || (long long)(g.N - 1) * g.ldb + g.K > g.b_len ||
+      (long long)g.splits * g.M * g.N > g.part_len)
+    return hipErrorInvalidValue;
+  switch (tall_tn(g.N)) {
+    case 1: return launch_tall<1>(g, s);
+    case 2: return launch_tall<2>(g, s);
+    case 3: return launch_tall<3>(g, s);
+    case 4: return launch_tall<4>(g, s);
+    case 5: return launch_tall<5>(g, s);
+    case 6: return launch_tall<6>(g, s);
+    case 7: return launch_tall<7>(g, s);
+    default: return launch_tall<8>(g, s);
+  }
+}
 
 hipError_t gemm_nt(const NtArgs& g, Prec prec, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.batch <= 0) return hipSuccess;

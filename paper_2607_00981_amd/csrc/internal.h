@@ -84,6 +84,22 @@ struct NtArgs {
 };
 hipError_t gemm_nt(const NtArgs& g, Prec prec, hipStream_t s);
 
+// Raw partial sums of C = A B^T over K ranges, both operands K-contiguous:
+//   part[z][m][n] (trans: part[z][n][m]) = sum over range z of A[m lda + k] B[n ldb + k],
+// z < splits, ranges of whole K tiles in order.  K a multiple of 16, even
+// strides, 16-byte aligned operands.  For a long M against an N of up to a few
+// hundred.
+struct TallArgs {
+  int M, N, K, splits;
+  const double* A; long long lda, a_len;
+  const double* B; long long ldb, b_len;
+  double* part; long long part_len;
+  bool trans;
+};
+// The number of ranges for a product of this shape (at most cap doubles of partial sums).
+int gemm_tall_splits(int M, int N, int K, long long cap);
+hipError_t gemm_tall(const TallArgs& g, hipStream_t s);
+
 // Y = alpha * X + beta * Y over an index space of up to 6 dimensions.
 struct PermArgs {
   int nd;
@@ -215,8 +231,15 @@ hipError_t t3_subcube(double* T, double* sub, long long ntri, int v, int sv, boo
 hipError_t axpby(double a, const double* x, double b, double* y, long long n, hipStream_t s);
 hipError_t fill(double* y, double val, long long n, hipStream_t s);
 // R1[i][a] += 1/2 sum_{j in [f0, f0+S), k, b, c} vvT[j][k][c][b] (2 U[(k,i,c)][j-f0][a][b] - U[(k,i,a)][j-f0][c][b])
-// with U[(k,i,x)][j'][p][q] the single-check spin-summed slab t~_{j k i}^{q x p} (one block per (i,a)).
-hipError_t feedback_r1(const double* U, const double* vvT, double* r1, int o, int v, int S, int f0, hipStream_t s);
+// with U[(k,i,x)][j'][p][q] the single-check spin-summed slab t~_{j k i}^{q x p} (slots of ldu >= v^2
+// doubles; one block per (i,a)).
+hipError_t feedback_r1(const double* U, long long ldu, const double* vvT, double* r1, int o, int v, int S, int f0,
+                       hipStream_t s);
+// Partial sums of the two feedback products added up (in order) and into place:
+//   part[z][(i,j,a)][n]: X2[(i,j,a)][n] += for n < v, W[a][n - v][(i,j)] += for the o after them;
+//   part[z][n][(i,x,y)]: X2[i][n][(x,y)] -= for n < o, W[n - o][(i,x,y)] -= for the v after them.
+hipError_t feedback_add_a(const double* part, int splits, double* X2, double* Wvooo, int o, int v, hipStream_t s);
+hipError_t feedback_add_b(const double* part, int splits, double* X2, double* Wt, int o, int v, hipStream_t s);
 // Symmetric / antisymmetric pair split of one v x v matrix per row r (element
 // (d,e) at in + off(r) + d*sd + e, off(r) = src[r] if src else map2(rmap, r)):
 //   plus [r*pitch_p + p(d,e)] = M[d][e] + M[e][d] (d < e), diag_scale*2*M[d][d] (d = e)

@@ -917,18 +917,18 @@ hipError_t pair_combine_cols(const float* CpT, const float* CmT, long long ncol,
 // ---------------------------------------------------------------------------
 namespace {
 
-__global__ void r1_feedback_kernel(const double* __restrict__ U, const double* __restrict__ vvT,
+__global__ void r1_feedback_kernel(const double* __restrict__ U, long long ldu, const double* __restrict__ vvT,
                                    double* __restrict__ r1, int o, int v, int S, int f0) {
   __shared__ double red[TPB];
   const int ia = blockIdx.x;
   const int i = ia / v, a = ia - (ia / v) * v;
-  const long long v2 = (long long)v * v, rowS = (long long)S * v2;
+  const long long v2 = (long long)v * v, rowS = (long long)S * ldu;
   double acc = 0.0;
   for (int jj = 0; jj < S; ++jj) {
     for (int k = 0; k < o; ++k) {
       const double* M = vvT + ((long long)(f0 + jj) * o + k) * v2;            // [c][b]
-      const double* U1 = U + ((long long)(k * o + i) * v) * rowS + jj * v2 + (long long)a * v;  // + c rowS + b
-      const double* U2 = U + ((long long)(k * o + i) * v + a) * rowS + jj * v2;              // + c v + b
+      const double* U1 = U + ((long long)(k * o + i) * v) * rowS + jj * ldu + (long long)a * v;  // + c rowS + b
+      const double* U2 = U + ((long long)(k * o + i) * v + a) * rowS + jj * ldu;             // + c v + b
       for (long long e = threadIdx.x; e < v2; e += TPB) {
         const int c = (int)(e / v), b = (int)(e - (long long)c * v);
         acc += M[e] * (2.0 * U1[(long long)c * rowS + b] - U2[e]);
@@ -944,7 +944,41 @@ __global__ void r1_feedback_kernel(const double* __restrict__ U, const double* _
   if (threadIdx.x == 0) r1[ia] += 0.5 * red[0];
 }
 
-// Y[b*sb + f*sf + b*sp + q*sq] += alpha * X[f*xf + q] for b < nb, f < nf, q < nq.
+__global__ void feedback_add_a_kernel(const double* __restrict__ part, int splits, double* __restrict__ X2,
+                                      double* __restrict__ Wvooo, int o, int v, long long total) {
+  const int nn = v + o;
+  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < total;
+       e += (long long)gridDim.x * blockDim.x) {
+    double x = 0.0;
+    for (int z = 0; z < splits; ++z) x += part[z * total + e];
+    const long long row = e / nn;
+    const int n = (int)(e - row * nn);
+    if (n < v) {
+      X2[row * v + n] += x;
+    } else {
+      const long long ij = row / v, a = row - ij * v;
+      Wvooo[(a * o + (n - v)) * ((long long)o * o) + ij] += x;
+    }
+  }
+}
+
+__global__ void feedback_add_b_kernel(const double* __restrict__ part, int splits, double* __restrict__ X2,
+                                      double* __restrict__ Wt, int o, int v, long long total) {
+  const long long v2 = (long long)v * v, rows = (long long)o * v2;
+  for (long long e = (long long)blockIdx.x * blockDim.x + threadIdx.x; e < total;
+       e += (long long)gridDim.x * blockDim.x) {
+    double x = 0.0;
+    for (int z = 0; z < splits; ++z) x += part[z * total + e];
+    const long long n = e / rows, row = e - n * rows;
+    if (n < o) {
+      const long long i = row / v2;
+      X2[(i * o + n) * v2 + (row - i * v2)] -= x;
+    } else {
+      Wt[(n - o) * rows + row] -= x;
+    }
+  }
+}
+
 __global__ void gather_rows_kernel(const double* __restrict__ in, long long ld_in, const int* __restrict__ rows,
                                    int nrows, long long ncols, double* __restrict__ out, long long ld_out) {
   const long long total = (long long)nrows * ncols;
@@ -955,6 +989,7 @@ __global__ void gather_rows_kernel(const double* __restrict__ in, long long ld_i
   }
 }
 
+// Y[b*sb + f*sf + b*sp + q*sq] += alpha * X[f*xf + q] for b < nb, f < nf, q < nq.
 __global__ void add_diag_rows_kernel(double* __restrict__ Y, const double* __restrict__ X, int nb, int nf, int nq,
                                      long long sb, long long sf, long long sp, long long sq, long long xf,
                                      double alpha) {
@@ -971,10 +1006,24 @@ __global__ void add_diag_rows_kernel(double* __restrict__ Y, const double* __res
 
 }  // namespace
 
-hipError_t feedback_r1(const double* U, const double* vvT, double* r1, int o, int v, int S, int f0,
+hipError_t feedback_r1(const double* U, long long ldu, const double* vvT, double* r1, int o, int v, int S, int f0,
                        hipStream_t s) {
   if (S <= 0) return hipSuccess;
-  hipLaunchKernelGGL(r1_feedback_kernel, dim3((unsigned)(o * v)), dim3(TPB), 0, s, U, vvT, r1, o, v, S, f0);
+  hipLaunchKernelGGL(r1_feedback_kernel, dim3((unsigned)(o * v)), dim3(TPB), 0, s, U, ldu, vvT, r1, o, v, S, f0);
+  return hipGetLastError();
+}
+
+hipError_t feedback_add_a(const double* part, int splits, double* X2, double* Wvooo, int o, int v, hipStream_t s) {
+  const long long total = (long long)o * o * v * (v + o);
+  hipLaunchKernelGGL(feedback_add_a_kernel, dim3(blocks_for(total, TPB)), dim3(TPB), 0, s, part, splits, X2, Wvooo, o,
+                     v, total);
+  return hipGetLastError();
+}
+
+hipError_t feedback_add_b(const double* part, int splits, double* X2, double* Wt, int o, int v, hipStream_t s) {
+  const long long total = (long long)o * v * v * (v + o);
+  hipLaunchKernelGGL(feedback_add_b_kernel, dim3(blocks_for(total, TPB)), dim3(TPB), 0, s, part, splits, X2, Wt, o, v,
+                     total);
   return hipGetLastError();
 }
 
