@@ -316,14 +316,15 @@ void cct_batch_destroy(cct_batch* b);
  * redundancies in RCC amplitudes".  This is one process's share of a run
  * sharded by packed triples; T1, T2 and the intermediates are replicated
  * inputs.  W^{ab}_{de} = sum_P B~^P_{ad} B~^P_{be} + sum_lm v~^{lm}_{de}
- * t_lm^ab is rebuilt in panels of opts "panel" rows a (default 8) and never
- * stored whole.  Ladder operands in the working precision (FP32, or hi+lo
+ * t_lm^ab is rebuilt in panels of opts "panel" rows a, stored whole only where
+ * it is small.  Ladder operands in the working precision (FP32, or hi+lo
  * BF16 when v^2 is a multiple of 4 or 8; FP64 otherwise); F_vv term and
  * drivers in FP64; R3 in FP64. */
 typedef struct cct_slab cct_slab;
 
 /* first + count <= nocc(nocc+1)(nocc+2)/6, count <= 65535.  opts_json:
- * "panel" (rows a per W panel, 1..nvir), "timers" (true: per-phase times
+ * "panel" (rows a per W panel, 1..nvir; default 8, or more while a panel
+ * takes at most 1 GiB), "timers" (true: per-phase times
  * in cct_slab_get_counters).  alloc/free_fn/alloc_user: as for cct_create.
  * Errors: CCT_EINVAL, CCT_ENOMEM. */
 int cct_slab_create(int nocc, int nvir, int naux, int first, int count, cct_precision prec, const char* opts_json,

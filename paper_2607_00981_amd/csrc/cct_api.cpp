@@ -1603,14 +1603,14 @@ struct QoOperands {
   const double *VVVO, *VVVOt, *VVVOk, *VVVOkt, *VOOO, *Wv, *Wo, *Wok, *T3u, *t2, *T2r, *T2l;
 };
 struct QoLaunch {
-  QoGemm g;
+  SegGemm g;
   bool y;         // into Y (else X)
   size_t first;   // position of its items in the table
 };
 
 // Items of the 14 launches for the listed tasks (each writes slot t of the
 // accumulators).  false: an operand would be read out of range.
-bool qo_plan(int o, int v, const std::vector<int4>& tasks, const QoOperands& w, std::vector<QoItem>& items,
+bool qo_plan(int o, int v, const std::vector<int4>& tasks, const QoOperands& w, std::vector<SegItem>& items,
              QoLaunch ls[kQoLaunches]) {
   const long long v2 = (long long)v * v, v3 = v2 * v, v4 = v2 * v2, o2 = (long long)o * o;
   const long long st[4] = {v3, v2, v, 1};
@@ -1620,13 +1620,13 @@ bool qo_plan(int o, int v, const std::vector<int4>& tasks, const QoOperands& w, 
     return m == 3 || m == 12 ? 0 : (m == 5 || m == 10 ? 1 : 2);
   };
   bool ok = true;
-  auto seg = [&](QoItem& it, const double* a, const double* abase, long long alen, long long areach, int rs0, int rs1,
+  auto seg = [&](SegItem& it, const double* a, const double* abase, long long alen, long long areach, int rs0, int rs1,
                  int rs2, const double* b, const double* bbase, long long blen, long long ldb, int K, long long N,
                  double coef) {
-    ok = ok && it.nseg < QO_SEG && a >= abase && (a - abase) + areach + K <= alen && b >= bbase &&
+    ok = ok && it.nseg < SEG_MAX && a >= abase && (a - abase) + areach + K <= alen && b >= bbase &&
          (b - bbase) + (K - 1) * ldb + N <= blen;
     if (!ok) return;
-    QoSeg& sg = it.seg[it.nseg++];
+    SegOp& sg = it.seg[it.nseg++];
     sg.a = a; sg.b = b; sg.ldb = ldb; sg.coef = coef;
     sg.rs0 = rs0; sg.rs1 = rs1; sg.rs2 = rs2;
   };
@@ -1673,7 +1673,7 @@ bool qo_plan(int o, int v, const std::vector<int4>& tasks, const QoOperands& w, 
     l = QoLaunch{};
     l.y = y;
     l.first = items.size();
-    l.g.M = M; l.g.N = N; l.g.K = K; l.g.n1 = l.g.n2 = n1;
+    l.g.M = M; l.g.N = N; l.g.K = l.g.kb = K; l.g.n1 = l.g.n2 = n1;
     l.g.vec = vec; l.g.swap = swap; l.g.cm = cm; l.g.cn = cn; l.g.accumulate = acc;
     return l;
   };
@@ -1689,7 +1689,7 @@ bool qo_plan(int o, int v, const std::vector<int4>& tasks, const QoOperands& w, 
     QoLaunch& l = open(false, (int)v2, (int)v2, v, 1, ev, false, pair_map(x, y), pair_map(z, u), pr > 0);
     for (size_t t = 0; t < tasks.size(); ++t) {
       const long long oc[4] = {tasks[t].x, tasks[t].y, tasks[t].z, tasks[t].w};
-      QoItem it{};
+      SegItem it{};
       it.c = (long long)t * v4;
       auto T3 = [&](long long m, long long r, long long q) { return w.T3u + ((r * o + q) * o + m) * v3; };  // t_{m r q}
       auto add = [&](int a, int b, const double* A, const double* abase, long long alen, const double* B,
@@ -1714,7 +1714,7 @@ bool qo_plan(int o, int v, const std::vector<int4>& tasks, const QoOperands& w, 
     QoLaunch& l = open(false, v, (int)v3, o, 1, eo, a == 3, lin(st[a]), trip_map(r[0], r[1], r[2]), 1);
     for (size_t t = 0; t < tasks.size(); ++t) {
       const long long oc[4] = {tasks[t].x, tasks[t].y, tasks[t].z, tasks[t].w};
-      QoItem it{};
+      SegItem it{};
       it.c = (long long)t * v4;
       for (int k = 0; k < 3; ++k) {
         const double c = weight(gs[t], a, r[k], first_rank);
@@ -1744,7 +1744,7 @@ bool qo_plan(int o, int v, const std::vector<int4>& tasks, const QoOperands& w, 
     QoLaunch& l = open(true, (int)v2, (int)v2, o, 1, eo, false, pair_map(x, y), pair_map(z, u), pr > 0);
     for (size_t t = 0; t < tasks.size(); ++t) {
       const long long oc[4] = {tasks[t].x, tasks[t].y, tasks[t].z, tasks[t].w};
-      QoItem it{};
+      SegItem it{};
       it.c = (long long)t * v4;
       auto add = [&](int c, int d, const double* A, const double* abase, long long alen, const double* B,
                      const double* bbase, long long blen, long long ld) {
@@ -1768,7 +1768,7 @@ bool qo_plan(int o, int v, const std::vector<int4>& tasks, const QoOperands& w, 
     QoLaunch& l = open(true, (int)v3, v, v, v, ev, d != 3, trip_map(r[0], r[1], r[2]), lin(st[d]), 1);
     for (size_t t = 0; t < tasks.size(); ++t) {
       const long long oc[4] = {tasks[t].x, tasks[t].y, tasks[t].z, tasks[t].w};
-      QoItem it{};
+      SegItem it{};
       it.c = (long long)t * v4;
       for (int k = 0; k < 3; ++k) {
         const double c = weight(gs[t], r[k], d, last_rank);
@@ -1833,7 +1833,7 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
   // One block of scratch: relaid copies of v^{ab}_{ej} and T2, the item tables,
   // and the accumulators X and Y of as many tasks as fit beside them.
   const long long norb = qo_orbits(v);
-  const long long item_n = (long long)(sizeof(QoItem) / 8);
+  const long long item_n = (long long)(sizeof(SegItem) / 8);
   auto up = [](long long x) { return (x + 31) / 32 * 32; };
   const long long fixed_n = 3 * up(o * v3) + 2 * up(o2 * v2) + up(2 * npair * item_n) + up((norb + 1) / 2) + 9 * 32;
   const long long per_task = 2 * v4 + norb + kQoLaunches * item_n + 8;
@@ -1928,7 +1928,7 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
   double* VVVOkt = carve(o * v3);  // [j][e][b][a]
   double* T2r = carve(o2 * v2);    // [j][x][y][m] = t_{m j}^{xy}
   double* T2l = carve(o2 * v2);    // [i][x][y][m] = t_{i m}^{xy}
-  QoItem* wv_items = (QoItem*)carve(2 * npair * item_n);
+  SegItem* wv_items = (SegItem*)carve(2 * npair * item_n);
   unsigned* orbits = (unsigned*)carve((norb + 1) / 2);
   HIPCK(qo_orbit_table(orbits, v, s));
   STCK(accumulate(s, 1.0, dense(VVVO, {o, v, v, v}), "jabe", 0.0, dense(VVVOt, {o, v, v, v}), "jbae"));
@@ -1938,12 +1938,12 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
   STCK(accumulate(s, 1.0, dense(ctx->t2, {o, o, v, v}), "imxy", 0.0, dense(T2l, {o, v, v, o}), "ixym"));
   // Wbar_eqr^abc (Eq. q_w_vvv_voo) as Wv[(q <= r)][a][b][c][e]: rows (a,b,e) and
   // (a,c,e) of v^{..}_{ef} times t2 blocks, every (q, r) in one launch
-  std::vector<QoItem> wvh((size_t)(2 * npair));
+  std::vector<SegItem> wvh((size_t)(2 * npair));
   for (long long q = 0; q < o; ++q)
     for (long long r = q; r < o; ++r)
       for (int w = 0; w < 2; ++w) {
-        QoItem& it = wvh[(size_t)(w * npair + qo_pair(o, q, r))];
-        it = QoItem{};
+        SegItem& it = wvh[(size_t)(w * npair + qo_pair(o, q, r))];
+        it = SegItem{};
         it.c = qo_pair(o, q, r) * v4;
         it.nseg = 1;
         it.seg[0].a = VVVV;
@@ -1952,17 +1952,17 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
         it.seg[0].coef = 0.5;
         it.seg[0].rs0 = v;
       }
-  HIPCK(hipMemcpyAsync(wv_items, wvh.data(), sizeof(QoItem) * wvh.size(), hipMemcpyHostToDevice, s));
+  HIPCK(hipMemcpyAsync(wv_items, wvh.data(), sizeof(SegItem) * wvh.size(), hipMemcpyHostToDevice, s));
   for (int w = 0; w < 2; ++w) {
-    QoGemm ga{};
-    ga.M = (int)v3; ga.N = v; ga.K = v; ga.n1 = ga.n2 = 1; ga.nitems = (int)npair;
+    SegGemm ga{};
+    ga.M = (int)v3; ga.N = v; ga.K = ga.kb = v; ga.n1 = ga.n2 = 1; ga.nitems = (int)npair;
     ga.vec = (v % 2) == 0; ga.swap = true;
     ga.items = wv_items + w * npair;
     ga.C = Wv;
     ga.cm = Idx4{1, v, v, v3, 0, w == 0 ? v2 : (long long)v, 1};
     ga.cn = Idx4{1, 1, 1, w == 0 ? (long long)v : v2, 0, 0, 0};
     ga.accumulate = w;
-    HIPCK(qo_gemm(ga, s));
+    HIPCK(seg_gemm(ga, s));
   }
   // Wbar_ijk^abm (Eq. q_w_vvo_ooo) as Wo[i][j][k][a][b][m]
   {
@@ -1998,18 +1998,18 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
   double* XS = carve(ntb * v4);
   double* YS = carve(ntb * v4);
   double* part = carve(ntb * norb);
-  QoItem* d_items = (QoItem*)carve(kQoLaunches * ntb * item_n);
+  SegItem* d_items = (SegItem*)carve(kQoLaunches * ntb * item_n);
   int4* d_tasks = (int4*)carve(2 * ntb);
   int* d_at = (int*)carve((ntb + 1) / 2);
   if (top > scratch_n) { ctx->err = "energy_q: scratch plan"; return CCT_EDEVICE; }
   const QoOperands ops{VVVO, VVVOt, VVVOk, VVVOkt, VOOO, Wv, Wo, g, T3u, ctx->t2, T2r, T2l};
   std::vector<int4> th;
   std::vector<int> ah;
-  std::vector<QoItem> ih;
+  std::vector<SegItem> ih;
   bool first = true;
   auto flush = [&]() -> int {
     if (th.empty()) return CCT_OK;
-    std::vector<QoItem> items;
+    std::vector<SegItem> items;
     QoLaunch ls[kQoLaunches];
     if (!qo_plan(o, v, th, ops, items, ls)) {
       ctx->err = "energy_q: operand out of range";
@@ -2018,14 +2018,14 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
     if (!first) HIPCK(hipStreamSynchronize(s));  // the host tables of the previous batch have been read
     first = false;
     ih.swap(items);
-    HIPCK(hipMemcpyAsync(d_items, ih.data(), sizeof(QoItem) * ih.size(), hipMemcpyHostToDevice, s));
+    HIPCK(hipMemcpyAsync(d_items, ih.data(), sizeof(SegItem) * ih.size(), hipMemcpyHostToDevice, s));
     HIPCK(hipMemcpyAsync(d_tasks, th.data(), sizeof(int4) * th.size(), hipMemcpyHostToDevice, s));
     HIPCK(hipMemcpyAsync(d_at, ah.data(), sizeof(int) * ah.size(), hipMemcpyHostToDevice, s));
     for (const QoLaunch& l : ls) {
-      QoGemm ga = l.g;
+      SegGemm ga = l.g;
       ga.items = d_items + l.first;
       ga.C = l.y ? YS : XS;
-      HIPCK(qo_gemm(ga, s));
+      HIPCK(seg_gemm(ga, s));
     }
     HIPCK(qo_energy(XS, YS, VVOO, ctx->t2, ctx->eps, d_tasks, d_at, (int)th.size(), orbits, o, v, part, et, s));
     HIPCK(hipStreamSynchronize(s));

@@ -309,34 +309,36 @@ struct Idx4 {
   long long s0, s1, s2, s3;
 };
 
-// --- perturbative quadruples in the occupied-tuple order ----------------------
-// Segmented product over a device table of items:
+// --- segmented products over a table of items ----------------------------------
 //   C_z(m, n) (+)= sum_s coef_s sum_{k < K} A_s(m, k) B_s(k, n)
 // A_s is K-contiguous, row m = (d0 n1 + d1) n2 + d2 at a + d0 rs0 + d1 rs1 +
-// d2 rs2; B_s is N-contiguous, row k at b + k ldb.  An item without segments
-// writes zeros (or adds nothing).  C through the four-level maps.
-constexpr int QO_SEG = 4;
-struct QoSeg {
+// d2 rs2; B_s is N-contiguous, row k at b + k ldb, rows kb <= k < K read as
+// zero (a K padded to pairs).  An item without segments writes zeros (or adds
+// nothing).  C through the four-level maps.
+constexpr int SEG_MAX = 4;
+struct SegOp {
   const double *a, *b;
   long long ldb;
   double coef;
   int rs0, rs1, rs2, pad;
 };
-struct QoItem {
+struct SegItem {
   long long c;  // offset of the item's output from C
   int nseg, pad;
-  QoSeg seg[QO_SEG];
+  SegOp seg[SEG_MAX];
 };
-struct QoGemm {
-  int M, N, K, n1, n2, nitems;
+struct SegGemm {
+  int M, N, K, kb, n1, n2, nitems;
   bool vec;   // every segment allows 16-byte loads (even K, N, strides; aligned bases)
   bool swap;  // the unit-stride axis of C lies in the rows
-  const QoItem* items;  // device
+  const SegItem* items;  // device
   double* C;
   Idx4 cm, cn;
   int accumulate;
 };
-hipError_t qo_gemm(const QoGemm& g, hipStream_t s);
+hipError_t seg_gemm(const SegGemm& g, hipStream_t s);
+
+// --- perturbative quadruples in the occupied-tuple order ----------------------
 // Energies of ntasks occupied tuples (i, j, k, l) = tasks[y] from their
 // accumulators X and Y ([y][v^4]; with equal occupied labels the sum over one
 // representative of each coset of the tuple's stabiliser G):

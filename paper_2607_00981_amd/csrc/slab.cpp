@@ -43,7 +43,10 @@ struct cct_slab {
   double* t2 = nullptr;    // [i][j][a][b]
   double* Fvv = nullptr;   // [a][d]
   double* Wt = nullptr;    // [j][a][b][d] = W^{ab}_{dj}
-  double* Wvooo = nullptr; // [a][l][i][j] = W^{al}_{ij}
+  double* Wvooo = nullptr; // [i][j][a][l] = W^{al}_{ij}, rows of op values (o padded to even with zeros)
+  long long op = 0;
+  long long v2p = 0;       // FP64 ladder rows: v^2 padded with zeros to 16
+  SegItem* drv = nullptr;  // items of the six driver launches, count each
   double* t3 = nullptr;    // [count][v^3]
   double* r3 = nullptr;    // [count][v^3]
   void* views = nullptr;   // relabelled copies of the slab's T3 (see slab_pp)
@@ -143,7 +146,6 @@ void mark(cct_slab* sl, int i) {
 }
 
 bool lp_ok(const cct_slab* sl) { return sl->prec != Prec::F64; }
-bool nt_ok(const cct_slab* sl) { return sl->prec == Prec::F64 && ((long long)sl->v * sl->v) % 2 == 0; }
 
 // The ladder's three relabelled terms, each a GEMM C[(t,x)][(y,z)] with K = (d,e):
 //   term 2 reads T[t][x][(d,e)] (stored order) and writes R[t][x][y][z]  (W^{bc}_{de} t^{ade});
@@ -168,8 +170,10 @@ int ladder_fmt(const cct_slab* sl) {
 }
 
 // Relabelled copies of the slab's T3: views[term] = [t][x][(d,e)] with x the
-// free axis of that term, in the working precision (FP64 terms 0 and 1 only;
-// term 2 reads T3 itself in FP64).
+// free axis of that term, in the working precision.  FP64 rows are padded with
+// zeros to v2p, whole K tiles of the direct-copy kernel for every v (R3, not
+// yet in use, takes the unpadded copies); a v^2 that needs no padding keeps
+// term 2 in T3 itself.
 int build_views(cct_slab* sl) {
   const int v = sl->v;
   const long long v2 = (long long)v * v, v3 = sl->v3, nb = sl->count;
@@ -183,15 +187,25 @@ int build_views(cct_slab* sl) {
       else if (term == 1) SHIP(swap01_batched(sl->t3, os, nb, v, v, v, sl->s));
       else SHIP(transpose_batched(sl->t3, os, nb, (int)v2, v, sl->s));
     }
-  } else if (nt_ok(sl)) {
-    double* base = (double*)sl->views;
-    SHIP(transpose_batched(sl->t3, OutSpec{base, OUT_F64, 0}, nb, (int)v2, v, sl->s));
-    SHIP(swap01_batched(sl->t3, OutSpec{base + nb * v3, OUT_F64, 0}, nb, v, v, v, sl->s));
+    return CCT_OK;
+  }
+  double* base = (double*)sl->views;
+  const long long len = nb * v * sl->v2p;
+  const bool pad = sl->v2p > v2;
+  double* tmp = pad ? sl->r3 : base;
+  SHIP(transpose_batched(sl->t3, OutSpec{tmp, OUT_F64, 0}, nb, (int)v2, v, sl->s));
+  if (pad) SHIP(copy_pad_rows(tmp, nb * v, v2, OutSpec{base, OUT_F64, 0}, sl->v2p, sl->s));
+  tmp = pad ? sl->r3 : base + len;
+  SHIP(swap01_batched(sl->t3, OutSpec{tmp, OUT_F64, 0}, nb, v, v, v, sl->s));
+  if (pad) {
+    SHIP(copy_pad_rows(tmp, nb * v, v2, OutSpec{base + len, OUT_F64, 0}, sl->v2p, sl->s));
+    SHIP(copy_pad_rows(sl->t3, nb * v, v2, OutSpec{base + 2 * len, OUT_F64, 0}, sl->v2p, sl->s));
   }
   return CCT_OK;
 }
 
-// W panel for rows a in [a0, a0 + na): Wp[a - a0][b][d][e] (FP64).
+// W panel for rows a in [a0, a0 + na): Wp[a - a0][b][(d,e)] (FP64; in the FP64
+// mode rows of v2p, their padding zero).
 int build_panel(cct_slab* sl, int a0, int na) {
   const int o = sl->o, v = sl->v, naux = sl->naux;
   const long long v2 = (long long)v * v, v3 = sl->v3, o2 = (long long)o * o;
@@ -220,24 +234,25 @@ int build_panel(cct_slab* sl, int a0, int na) {
     SHIP(gemm_nt_lp(h, sl->prec, sl->s));
     return CCT_OK;
   }
+  const long long pw = sl->v2p, prow = v * pw, plen = (long long)na * prow;
   // sum_P B~_{ad} B~_{be}: per a, C[d][(b,e)] = sum_P BvvT[a][d][P] BvvT[(b,e)][P]
   if (naux % 2 == 0) {
     NtArgs g{};
     g.M = v; g.N = (int)v2; g.K = naux; g.batch = na;
     g.A = sl->BvvT + (long long)a0 * v * naux; g.lda = naux; g.a_batch = (long long)v * naux;
     g.B = sl->BvvT; g.ldb = naux; g.b_batch = 0;
-    g.C = sl->Wp; g.cm = idx1(v); g.cn = idx2(v, v2, 1); g.c_batch = v3;
+    g.C = sl->Wp; g.cm = idx1(v); g.cn = idx2(v, pw, 1); g.c_batch = prow;
     g.alpha = 1.0; g.beta = 0.0;
-    g.a_len = v2 * naux - (long long)a0 * v * naux; g.b_len = v2 * naux; g.c_len = (long long)na * v3;
+    g.a_len = v2 * naux - (long long)a0 * v * naux; g.b_len = v2 * naux; g.c_len = plen;
     SHIP(gemm_nt(g, Prec::F64, sl->s));
   } else {
     GemmArgs g{};
     g.M = v; g.N = (int)v2; g.K = naux; g.batch = na;
     g.A = sl->BvvT + (long long)a0 * v * naux; g.am = idx1(naux); g.ak = idx1(1); g.a_batch = (long long)v * naux;
     g.B = sl->BvvT; g.bk = idx1(1); g.bn = idx1(naux); g.b_batch = 0;
-    g.C = sl->Wp; g.cm = idx1(v); g.cn = idx2(v, v2, 1); g.c_batch = v3;
+    g.C = sl->Wp; g.cm = idx1(v); g.cn = idx2(v, pw, 1); g.c_batch = prow;
     g.alpha = 1.0; g.beta = 0.0;
-    g.a_len = v2 * naux - (long long)a0 * v * naux; g.b_len = v2 * naux; g.c_len = (long long)na * v3;
+    g.a_len = v2 * naux - (long long)a0 * v * naux; g.b_len = v2 * naux; g.c_len = plen;
     SHIP(gemm(g, Prec::F64, sl->s));
   }
   // + sum_lm t_lm^ab v~^{lm}_{de}: C[(a,b)][(d,e)] = sum_(l,m) t2T[(a,b)][(l,m)] VoT[(d,e)][(l,m)]
@@ -246,20 +261,21 @@ int build_panel(cct_slab* sl, int a0, int na) {
     g.M = (int)((long long)na * v); g.N = (int)v2; g.K = (int)o2; g.batch = 1;
     g.A = sl->t2T + (long long)a0 * v * o2; g.lda = o2;
     g.B = sl->VoT; g.ldb = o2;
-    g.C = sl->Wp; g.cm = idx1(v2); g.cn = idx1(1);
+    g.C = sl->Wp; g.cm = idx1(pw); g.cn = idx1(1);
     g.alpha = 1.0; g.beta = 1.0;
-    g.a_len = v2 * o2 - (long long)a0 * v * o2; g.b_len = v2 * o2; g.c_len = (long long)na * v3;
+    g.a_len = v2 * o2 - (long long)a0 * v * o2; g.b_len = v2 * o2; g.c_len = plen;
     SHIP(gemm_nt(g, Prec::F64, sl->s));
   } else {
     GemmArgs g{};
     g.M = (int)((long long)na * v); g.N = (int)v2; g.K = (int)o2; g.batch = 1;
     g.A = sl->t2T + (long long)a0 * v * o2; g.am = idx1(o2); g.ak = idx1(1);
     g.B = sl->VoT; g.bk = idx1(1); g.bn = idx1(o2);
-    g.C = sl->Wp; g.cm = idx1(v2); g.cn = idx1(1);
+    g.C = sl->Wp; g.cm = idx1(pw); g.cn = idx1(1);
     g.alpha = 1.0; g.beta = 1.0;
-    g.a_len = v2 * o2 - (long long)a0 * v * o2; g.b_len = v2 * o2; g.c_len = (long long)na * v3;
+    g.a_len = v2 * o2 - (long long)a0 * v * o2; g.b_len = v2 * o2; g.c_len = plen;
     SHIP(gemm(g, Prec::F64, sl->s));
   }
+  SHIP(zero_cols(OutSpec{sl->Wp, OUT_F64, 0}, (long long)na * v, pw, v2, sl->s));
   return CCT_OK;
 }
 
@@ -269,9 +285,10 @@ int slab_pp(cct_slab* sl) {
   const long long v2 = (long long)v * v, v3 = sl->v3, nb = sl->count;
   Idx2 cm[3], cn[3];
   ladder_maps(v, cm, cn);
-  const bool lp = lp_ok(sl), nt = nt_ok(sl);
+  const bool lp = lp_ok(sl);
   mark(sl, 0);
   RCK_(build_views(sl));
+  SHIP(fill(sl->r3, 0.0, nb * v3, sl->s));  // after build_views, which stages in it
   mark(sl, 1);
   float t_rebuild = 0.f, t_ladder = 0.f;
   hipEvent_t e0 = nullptr, e1 = nullptr, e2 = nullptr;
@@ -300,27 +317,16 @@ int slab_pp(cct_slab* sl) {
         g.a_len = nb * v3; g.b_len = prow * v2; g.c_len = nb * v3 - coff;
         g.il = ladder_fmt(sl) == OUT_BF16X2I;
         SHIP(gemm_nt_lp(g, sl->prec, sl->s));
-      } else if (nt) {
-        NtArgs g{};
-        g.M = (int)(nb * v); g.N = (int)prow; g.K = (int)v2; g.batch = 1;
-        g.A = term == 2 ? sl->t3 : (const double*)sl->views + (term == 0 ? 0 : nb * v3); g.lda = v2;
-        g.B = sl->Wp; g.ldb = v2;
-        g.C = sl->r3 + coff; g.cm = cm[term]; g.cn = cn[term];
-        g.alpha = 1.0; g.beta = 1.0;
-        g.a_len = nb * v3; g.b_len = prow * v2; g.c_len = nb * v3 - coff;
-        SHIP(gemm_nt(g, Prec::F64, sl->s));
       } else {
-        // generic strided kernel reading the stored blocks in place
-        const Idx2 am[3] = {idx2(v, v3, 1), idx2(v, v3, v), idx2(v, v3, v2)};
-        const Idx2 ak[3] = {idx1(v), idx2(v, v2, 1), idx1(1)};
-        GemmArgs g{};
-        g.M = (int)(nb * v); g.N = (int)prow; g.K = (int)v2; g.batch = 1;
-        g.A = sl->t3; g.am = am[term]; g.ak = ak[term];
-        g.B = sl->Wp; g.bk = idx1(1); g.bn = idx1(v2);
+        const long long kp = sl->v2p, len = nb * v * kp;
+        NtArgs g{};
+        g.M = (int)(nb * v); g.N = (int)prow; g.K = (int)kp; g.batch = 1;
+        g.A = term == 2 && kp == v2 ? sl->t3 : (const double*)sl->views + term * len; g.lda = kp;
+        g.B = sl->Wp; g.ldb = kp;
         g.C = sl->r3 + coff; g.cm = cm[term]; g.cn = cn[term];
         g.alpha = 1.0; g.beta = 1.0;
-        g.a_len = nb * v3; g.b_len = prow * v2; g.c_len = nb * v3 - coff;
-        SHIP(gemm(g, Prec::F64, sl->s));
+        g.a_len = len; g.b_len = prow * kp; g.c_len = nb * v3 - coff;
+        SHIP(gemm_nt(g, Prec::F64, sl->s));
       }
     }
     if (sl->timers) {
@@ -367,61 +373,81 @@ int slab_f1(cct_slab* sl) {
   return CCT_OK;
 }
 
-const int PERM3[6][3] = {{0, 1, 2}, {0, 2, 1}, {1, 0, 2}, {1, 2, 0}, {2, 0, 1}, {2, 1, 0}};
-
-// T2 drivers for every stored block and every simultaneous column permutation
-// sigma: with (p,q,r) = sigma(i,j,k) and (x,y,z) = sigma(a,b,c),
+// T2 drivers: for every stored block and every simultaneous column permutation
+// sigma, with (p,q,r) = sigma(i,j,k) and (x,y,z) = sigma(a,b,c),
 //   R[abc] += sum_d W^{xy}_{dq} t_{pr}^{dz} - sum_l W^{xl}_{pq} t_{lr}^{yz}.
+// The two permutations that put the same axis in z (first term) or in x
+// (second) share their output rows and columns and are two K segments of one
+// item; every block is an item of the launch for that axis, so the drivers are
+// six launches, each reading and writing R once (one launch per block and
+// permutation: count 24, o = 12, v = 96 288 launches, 5.6 -> 1.5 ms).
 int slab_drivers(cct_slab* sl, bool d1, bool d2) {
-  const int o = sl->o, v = sl->v;
-  const long long v2 = (long long)v * v, v3 = sl->v3, o2v2 = (long long)o * o * v2;
-  const long long ax_stride[3] = {v2, (long long)v, 1};
-  for (int t = 0; t < sl->count; ++t) {
-    const int4 tr = sl->tri_h[t];
-    const int occ[3] = {tr.x, tr.y, tr.z};
-    double* R = sl->r3 + (long long)t * v3;
-    for (int s = 0; s < 6; ++s) {
-      const int* pi = PERM3[s];
-      const int p = occ[pi[0]], q = occ[pi[1]], r = occ[pi[2]];
-      // output axes: x lives on R's axis pi[0], y on pi[1], z on pi[2]
-      const long long sx = ax_stride[pi[0]], sy = ax_stride[pi[1]], sz = ax_stride[pi[2]];
-      if (d1) {
-        // C[(x,y)][z] = sum_d Wt[q][x][y][d] t2[r][p][z][d]  (t_{pr}^{dz} = t_{rp}^{zd})
-        const double* Bm = sl->t2 + ((long long)r * o + p) * v2;
-        if (v % 2 == 0) {
-          NtArgs g{};
-          g.M = (int)v2; g.N = v; g.K = v; g.batch = 1;
-          g.A = sl->Wt + (long long)q * v3; g.lda = v;
-          g.B = Bm; g.ldb = v;
-          g.C = R; g.cm = idx2(v, sx, sy); g.cn = idx1(sz);
-          g.alpha = 1.0; g.beta = 1.0;
-          g.a_len = v3; g.b_len = v2; g.c_len = v3;
-          SHIP(gemm_nt(g, Prec::F64, sl->s));
-        } else {
-          GemmArgs g{};
-          g.M = (int)v2; g.N = v; g.K = v; g.batch = 1;
-          g.A = sl->Wt + (long long)q * v3; g.am = idx1(v); g.ak = idx1(1);
-          g.B = Bm; g.bk = idx1(1); g.bn = idx1(v);
-          g.C = R; g.cm = idx2(v, sx, sy); g.cn = idx1(sz);
-          g.alpha = 1.0; g.beta = 1.0;
-          g.a_len = v3; g.b_len = v2; g.c_len = v3;
-          SHIP(gemm(g, Prec::F64, sl->s));
-        }
-      }
-      if (d2) {
-        // C[x][(y,z)] = -sum_l Wvooo[x][l][p][q] t2[l][r][y][z]
-        GemmArgs g{};
-        g.M = v; g.N = (int)v2; g.K = o; g.batch = 1;
-        g.A = sl->Wvooo + ((long long)p * o + q); g.am = idx1((long long)o * o * o); g.ak = idx1((long long)o * o);
-        g.B = sl->t2 + (long long)r * v2; g.bk = idx1((long long)o * v2); g.bn = idx1(1);
-        g.C = R; g.cm = idx1(sx); g.cn = idx2(v, sy, sz);
-        g.alpha = -1.0; g.beta = 1.0;
-        g.a_len = (long long)v * o * o * o - ((long long)p * o + q); g.b_len = o2v2 - (long long)r * v2; g.c_len = v3;
-        SHIP(gemm(g, Prec::F64, sl->s));
-      }
+  const int v = sl->v;
+  const long long st[3] = {(long long)v * v, v, 1};
+  for (int which = 0; which < 2; ++which) {
+    if (!(which == 0 ? d1 : d2)) continue;
+    for (int ax = 0; ax < 3; ++ax) {
+      const int u = ax == 0 ? 1 : 0, w = ax == 2 ? 1 : 2;
+      const Idx4 pair{1, 1, v, st[u], 0, 0, st[w]}, one{1, 1, 1, st[ax], 0, 0, 0};
+      SegGemm g{};
+      g.M = which == 0 ? v * v : v;
+      g.N = which == 0 ? v : v * v;
+      g.K = which == 0 ? v : (int)sl->op;
+      g.kb = which == 0 ? v : sl->o;
+      g.n1 = 1; g.n2 = which == 0 ? v : 1;
+      g.nitems = sl->count;
+      g.vec = v % 2 == 0;
+      g.swap = which == 0 ? ax != 2 : ax == 2;
+      g.items = sl->drv + (size_t)(which * 3 + ax) * sl->count;
+      g.C = sl->r3;
+      g.cm = which == 0 ? pair : one;
+      g.cn = which == 0 ? one : pair;
+      g.accumulate = 1;
+      SHIP(seg_gemm(g, sl->s));
     }
   }
   return CCT_OK;
+}
+
+// The items of slab_drivers (every address is fixed once the buffers are).
+std::vector<SegItem> driver_items(const cct_slab* sl) {
+  const int o = sl->o, v = sl->v;
+  const long long v2 = (long long)v * v, v3 = sl->v3, op = sl->op;
+  std::vector<SegItem> items;
+  for (int which = 0; which < 2; ++which)
+    for (int ax = 0; ax < 3; ++ax) {
+      const int u = ax == 0 ? 1 : 0, w = ax == 2 ? 1 : 2;
+      for (int t = 0; t < sl->count; ++t) {
+        const int4 tr = sl->tri_h[t];
+        const long long oc[3] = {tr.x, tr.y, tr.z};
+        SegItem it{};
+        it.c = (long long)t * v3;
+        it.nseg = 2;
+        for (int k = 0; k < 2; ++k) {
+          SegOp& sg = it.seg[k];
+          const int f = k == 0 ? u : w, g = k == 0 ? w : u;  // the other two axes, in the order of this permutation
+          if (which == 0) {
+            // (x, y, z) = (f, g, ax): rows (x,y) of Wt[q][x][y][d], columns z of t2[p][r][d][z]
+            sg.a = sl->Wt + oc[g] * v3;
+            sg.rs0 = k == 0 ? (int)v2 : v;
+            sg.rs2 = k == 0 ? v : (int)v2;
+            sg.b = sl->t2 + (oc[f] * o + oc[ax]) * v2;
+            sg.ldb = v;
+            sg.coef = 1.0;
+          } else {
+            // (x, y, z) = (ax, f, g): rows x of Wvooo[p][q][x][l], columns (u,w) of
+            // t_{l r}^{y z} = t2[l][r][u][w], or with y = w of t2[r][l][u][w]
+            sg.a = sl->Wvooo + (oc[ax] * o + oc[f]) * v * op;
+            sg.rs0 = (int)op;
+            sg.b = k == 0 ? sl->t2 + oc[g] * v2 : sl->t2 + oc[g] * o * v2;
+            sg.ldb = k == 0 ? o * v2 : v2;
+            sg.coef = -1.0;
+          }
+        }
+        items.push_back(it);
+      }
+    }
+  return items;
 }
 
 }  // namespace
@@ -459,13 +485,15 @@ int cct_slab_create(int nocc, int nvir, int naux, int first, int count, cct_prec
     return CCT_EDEVICE;
   }
   sl->v3 = (long long)nvir * nvir * nvir;
-  sl->panel = std::max(1, std::min(nvir, 8));
+  sl->panel = 0;
   if (opts_json) {
     std::string js(opts_json), val;
-    if (opt_find(js, "panel", val)) sl->panel = std::atoi(val.c_str());
+    if (opt_find(js, "panel", val)) {
+      sl->panel = std::atoi(val.c_str());
+      if (sl->panel < 1 || sl->panel > nvir) { delete sl; return CCT_EINVAL; }
+    }
     if (opt_find(js, "timers", val)) sl->timers = (val == "true" || val == "1");
   }
-  if (sl->panel < 1 || sl->panel > nvir) { delete sl; return CCT_EINVAL; }
   const int o = nocc, v = nvir, n = sl->n;
   const long long v2 = (long long)v * v, v3 = sl->v3, o2 = (long long)o * o, nb = count;
   // packed triples of the slab, in the lexicographic i<=j<=k order
@@ -480,19 +508,21 @@ int cct_slab_create(int nocc, int nvir, int naux, int first, int count, cct_prec
           }
   }
   int rc = CCT_OK;
-  const bool lp = lp_ok(sl), nt = nt_ok(sl);
-  const size_t view_bytes = lp ? (size_t)3 * nb * v3 * 4 : (nt ? (size_t)2 * nb * v3 * 8 : 8);
+  const bool lp = lp_ok(sl);
+  sl->v2p = (v2 + 15) / 16 * 16;
+  sl->op = (o + 1) / 2 * 2;
+  const size_t view_bytes = lp ? (size_t)3 * nb * v3 * 4 : (size_t)(sl->v2p > v2 ? 3 : 2) * nb * v * sl->v2p * 8;
   if (rc == CCT_OK) rc = sallocd(sl, &sl->BvvT, v2 * naux);
   if (rc == CCT_OK) rc = sallocd(sl, &sl->t2T, v2 * o2);
   if (rc == CCT_OK) rc = sallocd(sl, &sl->VoT, v2 * o2);
   if (rc == CCT_OK) rc = sallocd(sl, &sl->t2, o2 * v2);
   if (rc == CCT_OK) rc = sallocd(sl, &sl->Fvv, v2);
   if (rc == CCT_OK) rc = sallocd(sl, &sl->Wt, (long long)o * v3);
-  if (rc == CCT_OK) rc = sallocd(sl, &sl->Wvooo, (long long)v * o * o2);
+  if (rc == CCT_OK) rc = sallocd(sl, &sl->Wvooo, (long long)v * o2 * sl->op);
+  if (rc == CCT_OK) rc = sallocd(sl, &sl->drv, 6 * nb);
   if (rc == CCT_OK) rc = sallocd(sl, &sl->t3, nb * v3);
   if (rc == CCT_OK) rc = sallocd(sl, &sl->r3, nb * v3);
   if (rc == CCT_OK) rc = salloc(sl, &sl->views, view_bytes);
-  if (rc == CCT_OK) rc = sallocd(sl, &sl->Wp, (long long)sl->panel * v3);
   if (lp) {
     const int w = sl->prec == Prec::F32 ? 4 : 8;
     sl->ka = ((long long)naux + w - 1) / w * w;
@@ -501,13 +531,39 @@ int cct_slab_create(int nocc, int nvir, int naux, int first, int count, cct_prec
     if (rc == CCT_OK) rc = salloc(sl, &sl->t2L, (size_t)(v2 * sl->ko) * 4);
     if (rc == CCT_OK) rc = salloc(sl, &sl->VoL, (size_t)(v2 * sl->ko) * 4);
   }
-  if (rc == CCT_OK && lp) rc = salloc(sl, &sl->Wl, (size_t)sl->panel * v3 * 4);
+  // W panel: the rows asked for; else 8, or as many more as 1 GiB holds (wide
+  // panels fill the chip and rebuild W in fewer launches: count 24, o = 12, v =
+  // 96 split-BF16 ladder and rebuild 8.7 -> 5.1 ms), 8 again when that is not to be had
+  const size_t row_bytes = (size_t)v * (lp ? v2 * 12 : sl->v2p * 8);
+  const bool given = sl->panel > 0;
+  if (!given) sl->panel = std::min<int>(v, std::max<long long>(8, (long long)(((size_t)1 << 30) / row_bytes)));
+  while (rc == CCT_OK) {
+    void *wp = nullptr, *wl = nullptr;
+    rc = sdev_alloc(sl, &wp, (size_t)sl->panel * v * (lp ? v2 : sl->v2p) * 8);
+    if (rc == CCT_OK && lp) rc = sdev_alloc(sl, &wl, (size_t)sl->panel * v3 * 4);
+    if (rc == CCT_OK) {
+      sl->owned.push_back(wp);
+      if (wl) sl->owned.push_back(wl);
+      sl->Wp = (double*)wp;
+      sl->Wl = wl;
+      break;
+    }
+    sdev_free(sl, wp);
+    if (given || sl->panel <= 8) break;
+    sl->panel = std::min(v, 8);
+    rc = CCT_OK;
+  }
   if (rc == CCT_OK) rc = sallocd(sl, &sl->eps0, n);
   if (rc == CCT_OK) rc = sallocd(sl, &sl->tri, nb);
   sl->red_n = 2048 + 64LL * nb;
   if (rc == CCT_OK) rc = sallocd(sl, &sl->red, sl->red_n);
   if (rc == CCT_OK && hipMemcpy(sl->tri, sl->tri_h.data(), sizeof(int4) * nb, hipMemcpyHostToDevice) != hipSuccess)
     rc = CCT_EDEVICE;
+  if (rc == CCT_OK) {
+    const std::vector<SegItem> items = driver_items(sl);
+    if (hipMemcpy(sl->drv, items.data(), sizeof(SegItem) * items.size(), hipMemcpyHostToDevice) != hipSuccess)
+      rc = CCT_EDEVICE;
+  }
   if (rc == CCT_OK && fill(sl->eps0, 0.0, n, sl->s) != hipSuccess) rc = CCT_EDEVICE;
   if (rc == CCT_OK && sl->timers)
     for (int i = 0; i < 7 && rc == CCT_OK; ++i)
@@ -542,7 +598,12 @@ int cct_slab_set_intermediates(cct_slab* sl, const double* Bt, const double* t2,
   SHIP(hipMemcpy(sl->t2, t2, (size_t)(o2 * v2) * 8, hipMemcpyHostToDevice));
   SHIP(hipMemcpy(sl->Fvv, Fvv, (size_t)v2 * 8, hipMemcpyHostToDevice));
   SHIP(hipMemcpy(sl->Wt, Wt, (size_t)o * v2 * v * 8, hipMemcpyHostToDevice));
-  SHIP(hipMemcpy(sl->Wvooo, Wvooo, (size_t)v * o * o2 * 8, hipMemcpyHostToDevice));
+  std::vector<double> wo((size_t)(o2 * v * sl->op), 0.0);
+  for (int a = 0; a < v; ++a)
+    for (int l = 0; l < o; ++l)
+      for (long long ij = 0; ij < o2; ++ij)
+        wo[(size_t)((ij * v + a) * sl->op + l)] = Wvooo[(size_t)(((long long)a * o + l) * o2 + ij)];
+  SHIP(hipMemcpy(sl->Wvooo, wo.data(), wo.size() * 8, hipMemcpyHostToDevice));
   // v~^{lm}_{de} = sum_P B~^P_{ld} B~^P_{me} as VoT[(d,e)][(l,m)]: host copy of the
   // occupied-virtual factors, one GEMM on the device
   std::vector<double> bov((size_t)naux * o * v);
@@ -602,8 +663,8 @@ int cct_slab_residual(cct_slab* sl, unsigned term_mask, double* r3slab, double* 
   }
   const long long v3 = sl->v3, nb = sl->count;
   for (double& m : sl->ms) m = 0.0;
-  SHIP(fill(sl->r3, 0.0, nb * v3, sl->s));
   if (term_mask & CCT_TERM_PP) RCK_(slab_pp(sl));
+  else SHIP(fill(sl->r3, 0.0, nb * v3, sl->s));
   mark(sl, 2);
   if (term_mask & CCT_TERM_F1) RCK_(slab_f1(sl));
   mark(sl, 3);
