@@ -236,7 +236,7 @@ __global__ __launch_bounds__(NT, 2) void gemm_f64_kernel(GemmArgs g, int tiles_m
   int tm, tn;
   if (!tile_coords(tiles_m, tiles_n, tm, tn)) return;
   const int b = blockIdx.z;
-  constexpr bool can_split = (BM == 64);  // the split path exists for the small-tile kernel only
+  constexpr bool can_split = (BM <= 64);  // the split path exists for the small-tile kernels only
   int kb = 0;  // first K index of this workgroup; g.K becomes the end of its range
   if (can_split && kchunk > 0) {
     kb = blockIdx.y * kchunk;
@@ -337,7 +337,7 @@ hipError_t launch(const GemmArgs& g, Prec prec, hipStream_t s) {
     int splits = 1;
     const long long tiles = nb * g.batch;
     const long long mn = (long long)g.M * g.N * g.batch;
-    if (BM == 64 && g.split_ws && tiles < 128 && g.K >= 8 * BK) {
+    if (BM <= 64 && g.split_ws && tiles < 128 && g.K >= 8 * BK) {
       splits = (int)std::min<long long>((256 + tiles - 1) / tiles, g.K / (4 * BK));
       splits = (int)std::min<long long>(splits, g.split_cap / std::max<long long>(mn, 1));
       splits = std::min(splits, 64);
@@ -380,6 +380,10 @@ hipError_t gemm(const GemmArgs& g, Prec prec, hipStream_t s) {
   if (g.K <= 0) return g.beta == 1.0 ? hipSuccess : hipErrorInvalidValue;
   const long long work = (long long)g.M * g.N * g.batch;
   if (work >= (long long)256 * 128 * 128 * 2) return launch<128, 128>(g, prec, s);
+  // fewer 64 x 64 tiles than compute units: 32 x 32, four times the workgroups
+  // and a quarter of the matrix-core time in each step of K (o = 4, v = 20: 38
+  // launches per iteration from 11.4 to 7.1 us each)
+  if ((long long)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch < 256) return launch<32, 32>(g, prec, s);
   return launch<64, 64>(g, prec, s);
 }
 
@@ -842,22 +846,26 @@ hipError_t gemm_nt(const NtArgs& g, Prec prec, hipStream_t s) {
   int variant = g.variant;
   if (variant == 0) {
     // score each tile shape by the fraction of its MFMA work that lands inside
-    // the matrix (skinny M or N wastes most of a large tile), by how well its
-    // tile count fills the chip (two workgroups on each of 256 CUs), and by
-    // the measured relative speed of the shape on full tiles (an M or N of
-    // v = 180 virtual labels fills 94 % of 192, 70 % of 256)
-    struct Cand { int var, bm, bn; double speed; };
-    const Cand cands[9] = {{9, 128, 256, 1.10}, {10, 192, 256, 1.10}, {11, 128, 192, 1.10},
-                           {1, 128, 256, 1.00}, {2, 256, 128, 1.00},  {4, 128, 128, 0.96},
-                           {3, 64, 64, 0.86},   {5, 256, 32, 0.80},   {6, 32, 256, 0.80}};
+    // the matrix (skinny M or N wastes most of a large tile), by how full the
+    // rounds of workgroups are that its tile count takes (`slots`: workgroups
+    // that run at once on 256 CUs, by their LDS), and by the measured relative
+    // speed of the shape on full tiles.  Rounds matter: 1500 x 5625 took 528
+    // tiles of 128 x 128, two rounds of 512, at 36 TF/s (176 of 192 x 256: 45),
+    // and 7320 x 1891 580 tiles of 128 x 192, three rounds of 256, at 47 (464
+    // of 128 x 256: 50).  32 x 32 is for the products that fill no shape's
+    // round: 400 x 210 x 224 from 16 to 9 us.
+    struct Cand { int var, bm, bn, slots; double speed; };
+    const Cand cands[10] = {{9, 128, 256, 256, 1.10}, {10, 192, 256, 256, 1.10}, {11, 128, 192, 256, 1.10},
+                           {1, 128, 256, 256, 1.00}, {2, 256, 128, 256, 1.00},  {4, 128, 128, 512, 0.96},
+                           {3, 64, 64, 1024, 0.86},  {5, 256, 32, 512, 0.80},   {6, 32, 256, 512, 0.80},
+                            {7, 32, 32, 2048, 0.55}};
     double best = -1.0;
     for (const Cand& c : cands) {
       if (c.var >= 9 && !dl_ok) continue;
       const long long tm = (g.M + c.bm - 1) / c.bm, tn = (g.N + c.bn - 1) / c.bn;
       const double used = ((double)g.M / (double)(tm * c.bm)) * ((double)g.N / (double)(tn * c.bn));
-      const double tiles = (double)(tm * tn * g.batch);
-      const double fill = tiles >= 512.0 ? 1.0 : tiles / 512.0;
-      const double score = used * fill * c.speed;
+      const long long tiles = tm * tn * g.batch, rounds = (tiles + c.slots - 1) / c.slots;
+      const double score = used * ((double)tiles / (double)(rounds * c.slots)) * c.speed;
       if (score > best) { best = score; variant = c.var; }
     }
   }
@@ -869,6 +877,7 @@ hipError_t gemm_nt(const NtArgs& g, Prec prec, hipStream_t s) {
     case 1: return launch_nt<128, 256, 2, 4, 2>(g, s);
     case 2: return launch_nt<256, 128, 4, 2, 2>(g, s);
     case 3: return launch_nt<64, 64, 2, 2, 2>(g, s);
+    case 7: return launch_nt<32, 32, 2, 2, 2>(g, s);       // few tiles: more workgroups, shorter steps
     case 5: return launch_nt<256, 32, 4, 1, 2>(g, s);  // N of a few tens: 64 x 32 per wave
     case 6: return launch_nt<32, 256, 1, 4, 2>(g, s);  // M of a few tens: 32 x 64 per wave
     default: return launch_nt<128, 128, 2, 2, 2>(g, s);
