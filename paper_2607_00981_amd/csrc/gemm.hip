@@ -59,17 +59,12 @@ __device__ __forceinline__ unsigned lds_addr(const __bf16* p) {
   return (unsigned)(size_t)(__attribute__((address_space(3))) const void*)p;
 }
 
-// Position of the tile handled by this workgroup.  Consecutive workgroup ids
-// land on different XCDs (round robin over 8); remap so that each XCD gets a
-// contiguous range of the tile order, and order tiles in groups of GM tile
-// rows so that concurrently running workgroups on one XCD share A and B
-// panels in that XCD's L2.
-__device__ __forceinline__ bool tile_coords(int tiles_m, int tiles_n, int& tm, int& tn) {
-  const int nb = tiles_m * tiles_n;
-  const int per = (nb + 7) / 8;
-  const int bid = blockIdx.x;
-  const int pid = (bid % 8) * per + bid / 8;
-  if (pid >= nb) return false;
+// Position of the tile handled by this workgroup, and the batch member it belongs
+// to: the member's tiles in groups of GM tile rows, so that concurrently running
+// workgroups on one XCD (xcd_place) share A and B panels in that XCD's L2.
+__device__ __forceinline__ bool tile_coords(int tiles_m, int tiles_n, int batch, int& tm, int& tn, int& b) {
+  int pid;
+  if (!xcd_place(tiles_m * tiles_n, batch, pid, b)) return false;
   constexpr int GM = 8;
   const int group = pid / (GM * tiles_n);
   const int first_m = group * GM;
@@ -78,6 +73,11 @@ __device__ __forceinline__ bool tile_coords(int tiles_m, int tiles_n, int& tm, i
   tm = first_m + r % gsize;
   tn = r / gsize;
   return true;
+}
+// Its grid: -1 if the ids do not fit.
+long long tile_grid(long long tiles_m, long long tiles_n, int batch) {
+  const long long n = xcd_grid(tiles_m * tiles_n, batch);
+  return n > INT_MAX ? -1 : n;
 }
 
 template <int BM, int BN>
@@ -233,9 +233,8 @@ __global__ __launch_bounds__(NT, 2) void gemm_f64_kernel(GemmArgs g, int tiles_m
   __shared__ double As[2][BK * T::LA];
   __shared__ double Bs[2][BK * T::LB];
   __shared__ long long rowA[BM], colB[BN];
-  int tm, tn;
-  if (!tile_coords(tiles_m, tiles_n, tm, tn)) return;
-  const int b = blockIdx.z;
+  int tm, tn, b;
+  if (!tile_coords(tiles_m, tiles_n, g.batch, tm, tn, b)) return;
   constexpr bool can_split = (BM <= 64);  // the split path exists for the small-tile kernels only
   int kb = 0;  // first K index of this workgroup; g.K becomes the end of its range
   if (can_split && kchunk > 0) {
@@ -328,14 +327,13 @@ __global__ void splitk_reduce_kernel(const double* __restrict__ part, int splits
 template <int BM, int BN>
 hipError_t launch(const GemmArgs& g, Prec prec, hipStream_t s) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  const long long nb = (long long)tiles_m * tiles_n;
-  const long long grid_x = ((nb + 7) / 8) * 8;
-  if (grid_x > INT_MAX || g.batch > 65535) return hipErrorInvalidValue;
-  dim3 grid((unsigned)grid_x, 1, (unsigned)g.batch);
+  const long long grid_x = tile_grid(tiles_m, tiles_n, g.batch);
+  if (grid_x < 0) return hipErrorInvalidValue;
+  dim3 grid((unsigned)grid_x);
   if (prec == Prec::F64) {
     // few output tiles and a long K: split K so that the chip fills
     int splits = 1;
-    const long long tiles = nb * g.batch;
+    const long long tiles = (long long)tiles_m * tiles_n * g.batch;
     const long long mn = (long long)g.M * g.N * g.batch;
     if (BM <= 64 && g.split_ws && tiles < 128 && g.K >= 8 * BK) {
       splits = (int)std::min<long long>((256 + tiles - 1) / tiles, g.K / (4 * BK));
@@ -415,10 +413,9 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_nt_f64_kernel(NtArgs g
   using C = NtCfg<BM, BN, WM, WN>;
   __shared__ double As[2][BK * C::LA];
   __shared__ double Bs[2][BK * C::LB];
-  int tm, tn;
-  if (!tile_coords(tiles_m, tiles_n, tm, tn)) return;
+  int tm, tn, b;
+  if (!tile_coords(tiles_m, tiles_n, g.batch, tm, tn, b)) return;
   const int tid = threadIdx.x;
-  const int b = blockIdx.z;
   const double* A = g.A + (long long)b * g.a_batch;
   const double* B = g.B + (long long)b * g.b_batch;
   // per-thread source rows (clamped) and validity
@@ -546,10 +543,9 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_nt_f64_kernel(NtArgs g
 template <int BM, int BN, int WM, int WN, int OCC>
 hipError_t launch_nt(const NtArgs& g, hipStream_t s) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  const long long nb = (long long)tiles_m * tiles_n;
-  const long long grid_x = ((nb + 7) / 8) * 8;
-  if (grid_x > INT_MAX || g.batch > 65535) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)grid_x, 1, (unsigned)g.batch);
+  const long long grid_x = tile_grid(tiles_m, tiles_n, g.batch);
+  if (grid_x < 0) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)grid_x);
   if (g.b_kn)
     hipLaunchKernelGGL((gemm_nt_f64_kernel<BM, BN, WM, WN, OCC, true>), grid, dim3(64 * WM * WN), 0, s, g, tiles_m,
                        tiles_n);
@@ -580,9 +576,9 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_nt_f64_dl_kernel(NtArgs 
   constexpr int ABUF = BM * BK, BBUF = BN * BK;  // doubles per buffer
   __shared__ __attribute__((aligned(1024))) double As[2 * ABUF];
   __shared__ __attribute__((aligned(1024))) double Bs[2 * BBUF];
-  int tm, tn;
-  if (!tile_coords(tiles_m, tiles_n, tm, tn)) return;
-  const int tid = threadIdx.x, b = blockIdx.z;
+  int tm, tn, b;
+  if (!tile_coords(tiles_m, tiles_n, g.batch, tm, tn, b)) return;
+  const int tid = threadIdx.x;
   const int wave = tid / 64, lane = tid & 63;
   const double* A = g.A + (long long)b * g.a_batch;
   const double* B = g.B + (long long)b * g.b_batch;
@@ -668,10 +664,9 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_nt_f64_dl_kernel(NtArgs 
 template <int BM, int BN, int WM, int WN>
 hipError_t launch_nt_dl(const NtArgs& g, hipStream_t s) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  const long long nb = (long long)tiles_m * tiles_n;
-  const long long grid_x = ((nb + 7) / 8) * 8;
-  if (grid_x > INT_MAX || g.batch > 65535) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)grid_x, 1, (unsigned)g.batch);
+  const long long grid_x = tile_grid(tiles_m, tiles_n, g.batch);
+  if (grid_x < 0) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)grid_x);
   hipLaunchKernelGGL((gemm_nt_f64_dl_kernel<BM, BN, WM, WN>), grid, dim3(64 * WM * WN), 0, s, g, tiles_m, tiles_n);
   return hipGetLastError();
 }
@@ -692,8 +687,8 @@ __global__ __launch_bounds__(512, 2) void gemm_tall_f64_kernel(TallArgs g, int t
   constexpr int ABUF = BM * BK, BBUF = BN * BK;
   __shared__ __attribute__((aligned(1024))) double As[2 * ABUF];
   __shared__ __attribute__((aligned(1024))) double Bs[2 * BBUF];
-  int tm, tn;
-  if (!tile_coords(tiles_m, tiles_n, tm, tn)) return;
+  int tm, tn, b;
+  if (!tile_coords(tiles_m, tiles_n, 1, tm, tn, b)) return;
   const int tid = threadIdx.x, wave = tid / 64, lane = tid & 63;
   const int nkt = g.K / BK, per = (nkt + g.splits - 1) / g.splits;
   const int k_first = blockIdx.y * per, k_last = min(nkt, k_first + per);
@@ -766,8 +761,8 @@ __global__ __launch_bounds__(512, 2) void gemm_tall_f64_kernel(TallArgs g, int t
 template <int TN>
 hipError_t launch_tall(const TallArgs& g, hipStream_t s) {
   const long long tiles_m = ((long long)g.M + 127) / 128, tiles_n = (g.N + 16 * TN - 1) / (16 * TN);
-  const long long gx = (tiles_m * tiles_n + 7) / 8 * 8;
-  if (gx > INT_MAX) return hipErrorInvalidValue;
+  const long long gx = tile_grid(tiles_m, tiles_n, 1);
+  if (gx < 0) return hipErrorInvalidValue;
   const dim3 grid((unsigned)gx, (unsigned)g.splits);
   if (g.trans) hipLaunchKernelGGL((gemm_tall_f64_kernel<TN, true>), grid, dim3(512), 0, s, g, (int)tiles_m, (int)tiles_n);
   else hipLaunchKernelGGL((gemm_tall_f64_kernel<TN, false>), grid, dim3(512), 0, s, g, (int)tiles_m, (int)tiles_n);
@@ -910,9 +905,9 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_lp_f32_kernel(NtLpArgs
   constexpr int SA = BM * (KB / 4) / NTH, SB = BN * (KB / 4) / NTH;  // 16-byte segments per thread
   __shared__ float As[2][KB * LA];
   __shared__ float Bs[2][KB * LB];
-  int tm, tn;
-  if (!tile_coords(tiles_m, tiles_n, tm, tn)) return;
-  const int tid = threadIdx.x, b = blockIdx.z;
+  int tm, tn, b;
+  if (!tile_coords(tiles_m, tiles_n, g.batch, tm, tn, b)) return;
+  const int tid = threadIdx.x;
   const float* A = (const float*)g.A + (long long)b * g.a_batch;
   const float* B = (const float*)g.B + (long long)b * g.b_batch;
   const float* pa[SA];
@@ -1062,9 +1057,9 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_lp_f32_dl_kernel(NtLpA
   constexpr int ABUF = BM * KB, BBUF = BN * KB;  // floats per buffer
   __shared__ __attribute__((aligned(1024))) float As[2 * ABUF];
   __shared__ __attribute__((aligned(1024))) float Bs[2 * BBUF];
-  int tm, tn;
-  if (!tile_coords(tiles_m, tiles_n, tm, tn)) return;
-  const int tid = threadIdx.x, b = blockIdx.z;
+  int tm, tn, b;
+  if (!tile_coords(tiles_m, tiles_n, g.batch, tm, tn, b)) return;
+  const int tid = threadIdx.x;
   const int wave = tid / 64, lane = tid & 63;
   const float* A = (const float*)g.A + (long long)b * g.a_batch;
   const float* B = (const float*)g.B + (long long)b * g.b_batch;
@@ -1165,10 +1160,9 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_lp_f32_dl_kernel(NtLpA
 template <int BM, int BN, int WM, int WN, int OCC>
 hipError_t launch_lp_f32_dl(const NtLpArgs& g, hipStream_t s) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  const long long nb = (long long)tiles_m * tiles_n;
-  const long long grid_x = ((nb + 7) / 8) * 8;
-  if (grid_x > INT_MAX || g.batch > 65535) return hipErrorInvalidValue;
-  dim3 grid((unsigned)grid_x, 1, (unsigned)g.batch);
+  const long long grid_x = tile_grid(tiles_m, tiles_n, g.batch);
+  if (grid_x < 0) return hipErrorInvalidValue;
+  dim3 grid((unsigned)grid_x);
   hipLaunchKernelGGL((gemm_lp_f32_dl_kernel<BM, BN, WM, WN, OCC>), grid, dim3(64 * WM * WN), 0, s, g, tiles_m, tiles_n);
   return hipGetLastError();
 }
@@ -1188,9 +1182,9 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_lp_bf16x3_kernel(NtLpA
   constexpr int SA = BM * (KB / 8) / NTH, SB = BN * (KB / 8) / NTH;  // 16-byte segments per plane per thread
   __shared__ __attribute__((aligned(16))) __bf16 As[2][2][BM * LK];
   __shared__ __attribute__((aligned(16))) __bf16 Bs[2][2][BN * LK];
-  int tm, tn;
-  if (!tile_coords(tiles_m, tiles_n, tm, tn)) return;
-  const int tid = threadIdx.x, b = blockIdx.z;
+  int tm, tn, b;
+  if (!tile_coords(tiles_m, tiles_n, g.batch, tm, tn, b)) return;
+  const int tid = threadIdx.x;
   const __bf16* A = (const __bf16*)g.A + (long long)b * g.a_batch;
   const __bf16* B = (const __bf16*)g.B + (long long)b * g.b_batch;
   const __bf16* pa[SA];
@@ -1425,9 +1419,9 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_lp_bf16x3_dl_kernel(NtLp
   constexpr int ABUF = 2 * BM * KB, BBUF = 2 * BN * KB;  // elements per buffer (planes hi, lo)
   __shared__ __attribute__((aligned(1024))) __bf16 As[2 * ABUF];
   __shared__ __attribute__((aligned(1024))) __bf16 Bs[2 * BBUF];
-  int tm, tn;
-  if (!tile_coords(tiles_m, tiles_n, tm, tn)) return;
-  const int tid = threadIdx.x, b = blockIdx.z;
+  int tm, tn, b;
+  if (!tile_coords(tiles_m, tiles_n, g.batch, tm, tn, b)) return;
+  const int tid = threadIdx.x;
   const int wave = tid / 64, lane = tid & 63;
   const __bf16* A = (const __bf16*)g.A + (long long)b * g.a_batch;
   const __bf16* B = (const __bf16*)g.B + (long long)b * g.b_batch;
@@ -1530,10 +1524,9 @@ __global__ __launch_bounds__(64 * WM * WN, 1) void gemm_lp_bf16x3_dl_kernel(NtLp
 template <int BM, int BN, int WM, int WN>
 hipError_t launch_lp_dl(const NtLpArgs& g, hipStream_t s) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  const long long nb = (long long)tiles_m * tiles_n;
-  const long long grid_x = ((nb + 7) / 8) * 8;
-  if (grid_x > INT_MAX || g.batch > 65535) return hipErrorInvalidValue;
-  dim3 grid((unsigned)grid_x, 1, (unsigned)g.batch);
+  const long long grid_x = tile_grid(tiles_m, tiles_n, g.batch);
+  if (grid_x < 0) return hipErrorInvalidValue;
+  dim3 grid((unsigned)grid_x);
   hipLaunchKernelGGL((gemm_lp_bf16x3_dl_kernel<BM, BN, WM, WN>), grid, dim3(64 * WM * WN), 0, s, g, tiles_m, tiles_n);
   return hipGetLastError();
 }
@@ -1541,10 +1534,9 @@ hipError_t launch_lp_dl(const NtLpArgs& g, hipStream_t s) {
 template <int BM, int BN, int WM, int WN, int OCC, bool VEC, bool ACC64 = true, int PF = 2>
 hipError_t launch_lp(const NtLpArgs& g, Prec prec, hipStream_t s) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  const long long nb = (long long)tiles_m * tiles_n;
-  const long long grid_x = ((nb + 7) / 8) * 8;
-  if (grid_x > INT_MAX || g.batch > 65535) return hipErrorInvalidValue;
-  dim3 grid((unsigned)grid_x, 1, (unsigned)g.batch);
+  const long long grid_x = tile_grid(tiles_m, tiles_n, g.batch);
+  if (grid_x < 0) return hipErrorInvalidValue;
+  dim3 grid((unsigned)grid_x);
   if (prec == Prec::F32)
     hipLaunchKernelGGL((gemm_lp_f32_kernel<BM, BN, WM, WN, OCC, VEC>), grid, dim3(64 * WM * WN), 0, s, g, tiles_m, tiles_n);
   else

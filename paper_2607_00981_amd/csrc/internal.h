@@ -20,6 +20,38 @@ struct StageUser {
 };
 hipError_t copy_to_host(void* dst, const void* src, size_t bytes, int dev, hipStream_t s);
 
+// Workgroup -> (batch member b, tile pid < nt of that member).  Consecutive
+// workgroup ids land on different XCDs (round robin over 8), each with an L2 of
+// its own, so ids are dealt such that an XCD takes a contiguous range.  Members
+// of at least XCD_MEMBER tiles are taken one after another, every XCD a range of
+// the member's tiles, so that what the members share passes through the caches
+// once ((Q) o = 6, v = 48: 51.4 ms against 55.7 with a range of members per XCD);
+// smaller ones form one (member, tile) order that is cut into eight ranges: one
+// after another they would all start on XCD 0 (virtual-tuple (Q) o = 8, v = 60,
+// products of one and two tiles per member: 78.2 -> 48.0 ms).
+constexpr int XCD_MEMBER = 256;
+__device__ __forceinline__ bool xcd_place(int nt, int batch, int& pid, int& b) {
+  int bid = blockIdx.x, n = nt * batch;
+  b = 0;
+  if (nt >= XCD_MEMBER) {
+    const int g = (nt + 7) / 8 * 8;
+    b = bid / g;
+    bid -= b * g;
+    n = nt;
+  }
+  pid = (bid % 8) * ((n + 7) / 8) + bid / 8;
+  if (pid >= n) return false;
+  if (nt < XCD_MEMBER) {
+    b = pid / nt;
+    pid -= b * nt;
+  }
+  return true;
+}
+// The number of workgroups it needs.
+static inline long long xcd_grid(long long nt, long long batch) {
+  return nt >= XCD_MEMBER ? (nt + 7) / 8 * 8 * batch : (nt * batch + 7) / 8 * 8;
+}
+
 // Two-level index map: i -> (i / inner) * s_hi + (i % inner) * s_lo.
 // inner == 0 means one level: i -> i * s_lo.
 struct Idx2 {

@@ -30,15 +30,11 @@ __device__ __forceinline__ long long map4(const Idx4& d, int i) {
   return (long long)d0 * d.s0 + (long long)d1 * d.s1 + (long long)d2 * d.s2 + (long long)d3 * d.s3;
 }
 
-// blockIdx.x -> output tile; consecutive workgroups go to different XCDs
-// (round-robin dispatch), so the tile order is strided by 8 and grouped by 8
-// rows of tiles so that the tiles resident on one XCD share operand panels.
-__device__ __forceinline__ bool q_tile(int tiles_m, int tiles_n, int& tm, int& tn) {
-  const int nb = tiles_m * tiles_n;
-  const int per = (nb + 7) / 8;
-  const int bid = blockIdx.x;
-  const int pid = (bid % 8) * per + bid / 8;
-  if (pid >= nb) return false;
+// blockIdx.x -> batch member and output tile (xcd_place), tiles grouped by 8 rows
+// of tiles so that those resident on one XCD share operand panels.
+__device__ __forceinline__ bool q_tile(int tiles_m, int tiles_n, int batch, int& tm, int& tn, int& z) {
+  int pid;
+  if (!xcd_place(tiles_m * tiles_n, batch, pid, z)) return false;
   constexpr int GM = 8;
   const int group = pid / (GM * tiles_n);
   const int first_m = group * GM;
@@ -64,11 +60,9 @@ __global__ __launch_bounds__(64 * WM * WN) void qgemm_kernel(QGemmArgs g, int ti
   constexpr int NA = (UA + NTH - 1) / NTH, NB = (UB + NTH - 1) / NTH;
   __shared__ double As[2][QBK * LA];
   __shared__ double Bs[2][QBK * LB];
-  int tm, tn;
-  if (!q_tile(tiles_m, tiles_n, tm, tn)) return;
+  int tm, tn, z;
+  if (!q_tile(tiles_m, tiles_n, batch, tm, tn, z)) return;
   const int tid = threadIdx.x;
-  int z = blockIdx.y * gridDim.z + blockIdx.z;
-  if (z >= batch) return;
   int dig[QG_MAXD] = {0, 0, 0, 0};
   for (int d = g.nd - 1; d >= 0; --d) {
     dig[d] = z % g.rad[d];
@@ -255,13 +249,10 @@ template <int TM, int TN, int WM, int WN, bool AKM, bool BKN, bool VEC>
 hipError_t qlaunch(const QGemmArgs& g, long long batch, hipStream_t s) {
   constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN;
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
-  const long long nb = (long long)tiles_m * tiles_n;
-  const long long gx = ((nb + 7) / 8) * 8;
+  const long long gx = xcd_grid((long long)tiles_m * tiles_n, batch);
   if (gx > INT_MAX) return hipErrorInvalidValue;
-  // the batch over grid z (at most 65535) and y
-  const long long gz = std::min<long long>(batch, 65535), gy = (batch + gz - 1) / gz;
-  hipLaunchKernelGGL((qgemm_kernel<TM, TN, WM, WN, AKM, BKN, VEC>), dim3((unsigned)gx, (unsigned)gy, (unsigned)gz),
-                     dim3(64 * WM * WN), 0, s, g, tiles_m, tiles_n, (int)batch);
+  hipLaunchKernelGGL((qgemm_kernel<TM, TN, WM, WN, AKM, BKN, VEC>), dim3((unsigned)gx), dim3(64 * WM * WN), 0, s, g,
+                     tiles_m, tiles_n, (int)batch);
   return hipGetLastError();
 }
 

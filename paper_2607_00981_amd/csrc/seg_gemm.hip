@@ -21,14 +21,10 @@ __device__ __forceinline__ long long map4(const Idx4& d, int i) {
   return (long long)d0 * d.s0 + (long long)d1 * d.s1 + (long long)d2 * d.s2 + (long long)d3 * d.s3;
 }
 
-// blockIdx.x -> output tile: each XCD takes a contiguous range of a tile order
-// grouped by 8 rows of tiles (see q_abc.hip).
-__device__ __forceinline__ bool seg_tile(int tiles_m, int tiles_n, int& tm, int& tn) {
-  const int nb = tiles_m * tiles_n;
-  const int per = (nb + 7) / 8;
-  const int bid = blockIdx.x;
-  const int pid = (bid % 8) * per + bid / 8;
-  if (pid >= nb) return false;
+// blockIdx.x -> item and output tile (xcd_place), tiles grouped by 8 rows of tiles.
+__device__ __forceinline__ bool seg_tile(int tiles_m, int tiles_n, int batch, int& tm, int& tn, int& z) {
+  int pid;
+  if (!xcd_place(tiles_m * tiles_n, batch, pid, z)) return false;
   constexpr int GM = 8;
   const int group = pid / (GM * tiles_n);
   const int first_m = group * GM;
@@ -61,10 +57,10 @@ __global__ __launch_bounds__(64 * WM * WN) void seg_gemm_kernel(SegGemm g, int t
   constexpr int NA = (UA + NTH - 1) / NTH, NB = (UB + NTH - 1) / NTH;
   __shared__ double As[2][SBK * LA];
   __shared__ double Bs[2][SBK * LB];
-  int tm, tn;
-  if (!seg_tile(tiles_m, tiles_n, tm, tn)) return;
+  int tm, tn, z;
+  if (!seg_tile(tiles_m, tiles_n, g.nitems, tm, tn, z)) return;
   const int tid = threadIdx.x;
-  const SegItem& it = g.items[blockIdx.z];
+  const SegItem& it = g.items[z];
   const int m0 = tm * BM, n0 = tn * BN, nseg = it.nseg, K = g.K, ktot = nseg * K;
   int ak[NA], as_[NA], ar[NA], ad0[NA], ad1[NA], ad2[NA], bk[NB], bs_[NB], br[NB];
   const double *pa[NA], *pb[NB];
@@ -263,9 +259,9 @@ template <int TM, int TN, int WM, int WN>
 hipError_t seg_launch(const SegGemm& g, bool vec, hipStream_t s) {
   constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN;
   const long long tiles_m = ((long long)g.M + BM - 1) / BM, tiles_n = ((long long)g.N + BN - 1) / BN;
-  const long long gx = ((tiles_m * tiles_n + 7) / 8) * 8;
+  const long long gx = xcd_grid(tiles_m * tiles_n, g.nitems);
   if (gx > INT_MAX) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)gx, 1, (unsigned)g.nitems), block(64 * WM * WN);
+  const dim3 grid((unsigned)gx), block(64 * WM * WN);
   if (g.swap) {
     if (vec) hipLaunchKernelGGL((seg_gemm_kernel<TM, TN, WM, WN, true, true>), grid, block, 0, s, g, (int)tiles_m, (int)tiles_n);
     else hipLaunchKernelGGL((seg_gemm_kernel<TM, TN, WM, WN, true, false>), grid, block, 0, s, g, (int)tiles_m, (int)tiles_n);
@@ -280,7 +276,7 @@ hipError_t seg_launch(const SegGemm& g, bool vec, hipStream_t s) {
 
 hipError_t seg_gemm(const SegGemm& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.nitems <= 0) return hipSuccess;
-  if (g.K <= 0 || g.kb > g.K || !g.items || g.n1 < 1 || g.n2 < 1 || g.nitems > 65535) return hipErrorInvalidValue;
+  if (g.K <= 0 || g.kb > g.K || !g.items || g.n1 < 1 || g.n2 < 1 ) return hipErrorInvalidValue;
   const bool vec = g.vec;
   // A skinny side (the v labels of one axis) takes the narrowest tile of 32,
   // 48 or 64 that wastes least, against 64 of the long side: the update of C

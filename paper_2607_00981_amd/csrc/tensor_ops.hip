@@ -77,7 +77,7 @@ __device__ __forceinline__ int xcd_tile(int ntiles) {
   const int per = (ntiles + 7) / 8;
   return (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
 }
-inline unsigned xcd_grid(int ntiles) { return (unsigned)(((ntiles + 7) / 8) * 8); }
+inline unsigned xcd_tiles_grid(int ntiles) { return (unsigned)(((ntiles + 7) / 8) * 8); }
 
 template <bool DUAL>
 __global__ __launch_bounds__(256) void unpack_tiled_kernel(const double* __restrict__ T,
@@ -529,7 +529,7 @@ hipError_t unpack_t3_fmt(const double* T, const BlockRef* tbl, const int2* slots
   if (ny > 65535) return hipErrorInvalidValue;
   if (a.nterms < 1 || a.nterms > 6) return hipErrorInvalidValue;
   const int nt = (a.v + UT - 1) / UT;
-  dim3 grid(xcd_grid(nt * nt * nt), (unsigned)ny);
+  dim3 grid(xcd_tiles_grid(nt * nt * nt), (unsigned)ny);
   hipLaunchKernelGGL(unpack_tiled_kernel<false>, grid, dim3(TPB), 0, s, T, tbl, slots, out, out, a, nt);
   return hipGetLastError();
 }
@@ -542,7 +542,7 @@ hipError_t unpack_t3_dual(const double* T, const BlockRef* tbl, const int2* slot
   if (ny > 65535) return hipErrorInvalidValue;
   if (a.nterms < 1 || a.nterms > 6) return hipErrorInvalidValue;
   const int nt = (a.v + UT - 1) / UT;
-  dim3 grid(xcd_grid(nt * nt * nt), (unsigned)ny);
+  dim3 grid(xcd_tiles_grid(nt * nt * nt), (unsigned)ny);
   hipLaunchKernelGGL(unpack_tiled_kernel<true>, grid, dim3(TPB), 0, s, T, tbl, slots, out, out2, a, nt);
   return hipGetLastError();
 }
@@ -557,7 +557,7 @@ hipError_t fold_r3(double* R, long long bs, int v, const double* Z, const FoldTa
   if (ntasks <= 0) return hipSuccess;
   if (ntasks > 65535) return hipErrorInvalidValue;
   const int nt = (v + UT - 1) / UT;
-  dim3 grid(xcd_grid(nt * nt * nt), (unsigned)ntasks);
+  dim3 grid(xcd_tiles_grid(nt * nt * nt), (unsigned)ntasks);
   hipLaunchKernelGGL(fold_tiled_kernel<double>, grid, dim3(TPB), 0, s, R, bs, v, Z, tasks, contribs, nt);
   return hipGetLastError();
 }
@@ -567,7 +567,7 @@ hipError_t fold_r3(double* R, long long bs, int v, const float* Z, const FoldTas
   if (ntasks <= 0) return hipSuccess;
   if (ntasks > 65535) return hipErrorInvalidValue;
   const int nt = (v + UT - 1) / UT;
-  dim3 grid(xcd_grid(nt * nt * nt), (unsigned)ntasks);
+  dim3 grid(xcd_tiles_grid(nt * nt * nt), (unsigned)ntasks);
   hipLaunchKernelGGL(fold_tiled_kernel<float>, grid, dim3(TPB), 0, s, R, bs, v, Z, tasks, contribs, nt);
   return hipGetLastError();
 }
