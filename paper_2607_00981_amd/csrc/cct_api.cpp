@@ -114,8 +114,8 @@ struct cct_ctx {
   Job ring[3], hh, d1, d2, feed1;
   // DIIS
   // history in device memory: M slots of diis_len doubles, overlap matrix,
-  // bookkeeping (see DiisArgs); diis_new: the Jacobi / extrapolated vector
-  double *dvecs = nullptr, *derrs = nullptr, *diis_new = nullptr, *diis_part = nullptr;
+  // bookkeeping (see DiisArgs); diis_sub: the T3 sub-cube, where DIIS takes only that
+  double *dvecs = nullptr, *derrs = nullptr, *diis_sub = nullptr, *diis_part = nullptr;
   double *diis_d = nullptr, *diis_B = nullptr, *diis_coef = nullptr;
   int* diis_st = nullptr;
   double* diis_old = nullptr;
@@ -2603,29 +2603,6 @@ long long diis_len(cct_ctx* ctx) {
   return n12 + ctx->ntri * diis_block(ctx);
 }
 
-int copy_amps_to(cct_ctx* ctx, double* dst) {
-  const long long n1 = (long long)ctx->o * ctx->v, n2 = n1 * n1;
-  HIPCK(axpby(1.0, ctx->t1, 0.0, dst, n1, ctx->s));
-  HIPCK(axpby(1.0, ctx->t2, 0.0, dst + n1, n2, ctx->s));
-  if (ctx->diis_t3 && ctx->diis_sv > 0)
-    HIPCK(t3_subcube(ctx->t3, dst + n1 + n2, ctx->ntri, ctx->v, ctx->diis_sv, true, ctx->s));
-  else if (ctx->diis_t3)
-    HIPCK(axpby(1.0, ctx->t3, 0.0, dst + n1 + n2, ctx->ntri * ctx->v3, ctx->s));
-  return CCT_OK;
-}
-
-// The DIIS part of a vector back into the amplitudes (inverse of copy_amps_to).
-int copy_amps_from(cct_ctx* ctx, const double* src) {
-  const long long n1 = (long long)ctx->o * ctx->v, n2 = n1 * n1;
-  HIPCK(axpby(1.0, src, 0.0, ctx->t1, n1, ctx->s));
-  HIPCK(axpby(1.0, src + n1, 0.0, ctx->t2, n2, ctx->s));
-  if (ctx->diis_t3 && ctx->diis_sv > 0)
-    HIPCK(t3_subcube(ctx->t3, const_cast<double*>(src + n1 + n2), ctx->ntri, ctx->v, ctx->diis_sv, false, ctx->s));
-  else if (ctx->diis_t3)
-    HIPCK(axpby(1.0, src + n1 + n2, 0.0, ctx->t3, ctx->ntri * ctx->v3, ctx->s));
-  return CCT_OK;
-}
-
 DiisArgs diis_args(const cct_ctx* ctx) {
   DiisArgs a{};
   a.L = ctx->diis_len;
@@ -2644,16 +2621,32 @@ int diis_reset(cct_ctx* ctx) {
   return CCT_OK;
 }
 
+// The amplitudes as the DIIS kernels see them: in place, except a T3 sub-cube,
+// which is gathered into a buffer of its own.
+DiisAmps diis_amps(const cct_ctx* ctx) {
+  return DiisAmps{ctx->t1, ctx->t2, ctx->diis_sub ? ctx->diis_sub : ctx->t3, (long long)ctx->o * ctx->v};
+}
+
+// The DIIS part of the amplitudes before the iteration into diis_old.
+int diis_keep(cct_ctx* ctx) {
+  DiisArgs a = diis_args(ctx);
+  if (ctx->diis_sub) {
+    HIPCK(t3_subcube(ctx->t3, ctx->diis_old + a.n12, ctx->ntri, ctx->v, ctx->diis_sv, true, ctx->s));
+    a.L = a.n12;
+    a.bs = 0;
+  }
+  HIPCK(diis_save(diis_amps(ctx), ctx->diis_old, a, ctx->s));
+  return CCT_OK;
+}
+
 // After the Jacobi step: T holds the Jacobi-updated amplitudes, diis_old the
-// amplitudes before it.  The Jacobi vector is gathered, the device step
-// (overlaps, bordered solve, history update, extrapolation) runs, and the
-// result is written back; no synchronisation.
+// amplitudes before it.  The device step (overlaps, history update, bordered
+// solve, extrapolation) works on T; no synchronisation.
 int diis_step(cct_ctx* ctx) {
-  RCK(copy_amps_to(ctx, ctx->diis_new));
-  const DiisArgs a = diis_args(ctx);
-  HIPCK(diis_device_step(ctx->diis_new, ctx->diis_old, ctx->dvecs, ctx->derrs, ctx->diis_part, ctx->diis_d,
-                         ctx->diis_B, ctx->diis_st, ctx->diis_coef, a, ctx->s));
-  RCK(copy_amps_from(ctx, ctx->diis_new));
+  if (ctx->diis_sub) HIPCK(t3_subcube(ctx->t3, ctx->diis_sub, ctx->ntri, ctx->v, ctx->diis_sv, true, ctx->s));
+  HIPCK(diis_device_step(diis_amps(ctx), ctx->diis_old, ctx->dvecs, ctx->derrs, ctx->diis_part, ctx->diis_d,
+                         ctx->diis_B, ctx->diis_st, ctx->diis_coef, diis_args(ctx), ctx->s));
+  if (ctx->diis_sub) HIPCK(t3_subcube(ctx->t3, ctx->diis_sub, ctx->ntri, ctx->v, ctx->diis_sv, false, ctx->s));
   return CCT_OK;
 }
 
@@ -2663,7 +2656,7 @@ int diis_step(cct_ctx* ctx) {
 // No host synchronisation and no allocation: safe to record into a graph.
 int enqueue_iteration(cct_ctx* ctx, double* out = nullptr) {
   const bool use_diis = ctx->diis_on && ctx->diis_space > 0;
-  if (use_diis) RCK(copy_amps_to(ctx, ctx->diis_old));
+  if (use_diis) RCK(diis_keep(ctx));
   RCK(enqueue_residual(ctx, CCT_TERM_ALL, true));
   HIPCK(jacobi_t1t2(ctx->t1, ctx->r1, ctx->t2, ctx->r2, ctx->eps, ctx->o, ctx->v, ctx->s));
   mark(ctx, PH_DIIS);
@@ -3030,7 +3023,7 @@ int cct_create(int nocc, int nvir, int naux, cct_precision prec, const char* opt
   fixed += (long long)v * v * v * v + o2v2 + ov;
   const int M = ctx->diis_on ? ctx->diis_space : 0;
   const long long dlen = ov + o2v2 + ctx->ntri * diis_block(ctx);
-  fixed += (long long)(2 * M + 2) * dlen;
+  fixed += (long long)(2 * M + 1) * dlen + (ctx->diis_sv > 0 && ctx->diis_t3 ? ctx->ntri * diis_block(ctx) : 0);
   // workspace: enough for every job in one batch (two unpacked/contracted
   // slabs per slot, o^2 slots for the rings), capped by the option
   // the split ladder needs W+- (about v^4/2) and, per packed block, its split
@@ -3089,7 +3082,7 @@ int cct_create(int nocc, int nvir, int naux, cct_precision prec, const char* opt
   if (M > 0) {
     const long long nchunk = diis_chunks(diis_args(ctx));
     AL(diis_old, ctx->diis_len);
-    AL(diis_new, ctx->diis_len);
+    if (ctx->diis_t3 && ctx->diis_sv > 0) { AL(diis_sub, ctx->ntri * diis_block(ctx)); }
     AL(dvecs, (long long)M * ctx->diis_len);
     AL(derrs, (long long)M * ctx->diis_len);
     AL(diis_part, (long long)(M + 1) * nchunk);

@@ -315,14 +315,22 @@ struct DiisArgs {
   const int4* tri;
   int ntri, M, start;
 };
+// Where such a vector lives: T1 (n1 elements), T2, and the packed T3 blocks one
+// after another.
+struct DiisAmps {
+  double *t1, *t2, *t3;
+  long long n1;
+};
 // Overlap chunks of one step (size of the partial-sum scratch: (M + 1) x chunks).
 long long diis_chunks(const DiisArgs& a);
-// One DIIS step on the Jacobi vector vnew (old: the amplitudes before the
-// step): overlaps of e = vnew - old with the history, the bordered solve
-// (a singular system drops the oldest vector for good), e and vnew enter the
-// history, and vnew becomes the extrapolated vector when the solve succeeded.
+// old = the vector at t.
+hipError_t diis_save(const DiisAmps& t, double* old, const DiisArgs& a, hipStream_t s);
+// One DIIS step on the Jacobi amplitudes t (old: the vector before the
+// step): overlaps of e = t - old with the history, e and t enter the history,
+// the bordered solve (a singular system drops the oldest vector for good), and
+// t becomes the extrapolated vector when the solve succeeded.
 // part: (M + 1) x diis_chunks doubles, d: M + 1, B: M x M, coef: M.
-hipError_t diis_device_step(double* vnew, const double* old, double* vecs, double* errs, double* part, double* d,
+hipError_t diis_device_step(const DiisAmps& t, const double* old, double* vecs, double* errs, double* part, double* d,
                             double* B, int* st, double* coef, const DiisArgs& a, hipStream_t s);
 // Empty history (a kernel, so that it may sit in a recorded graph).
 hipError_t diis_device_reset(int* st, hipStream_t s);

@@ -1061,7 +1061,9 @@ hipError_t add_pair_diag(double* W, const double* F, long long ldF, int nx, doub
 // ---------------------------------------------------------------------------
 namespace {
 
-constexpr int DIIS_CH = TPB * 16;  // elements per overlap chunk
+constexpr int DIIS_U = 16;            // elements per thread
+constexpr int DIIS_CH = TPB * DIIS_U;  // elements per chunk (one workgroup)
+static_assert(TPB == 256, "the sums of a chunk are folded over four waves");
 
 __device__ __forceinline__ void diis_chunk(const DiisArgs& a, long long c, long long& lo, long long& hi, double& w) {
   const long long nc12 = (a.n12 + DIIS_CH - 1) / DIIS_CH;
@@ -1079,30 +1081,124 @@ __device__ __forceinline__ void diis_chunk(const DiisArgs& a, long long c, long 
   w = (double)a.tri[t].w;
 }
 
-// part[j][c] = w_c sum over chunk c of e_new * errs[j] (j < M), or e_new^2 (j = M),
-// with e_new = vnew - old.
-__global__ void diis_overlap_kernel(const double* __restrict__ vnew, const double* __restrict__ old,
-                                    const double* __restrict__ errs, DiisArgs a, long long nchunk,
-                                    double* __restrict__ part) {
-  __shared__ double red[TPB];
+// Element r of chunk lo.. of the amplitudes: T1 then T2 (a chunk may hold the
+// seam), or part of one T3 block.
+struct DiisChunkAmps {
+  double *p, *q;
+  long long split;
+  __device__ __forceinline__ DiisChunkAmps(const DiisAmps& t, const DiisArgs& a, long long lo) {
+    const bool t3 = lo >= a.n12;
+    p = t3 ? t.t3 + (lo - a.n12) : t.t1 + lo;
+    split = t3 ? (long long)DIIS_CH : t.n1 - lo;
+    q = t.t2;
+  }
+  __device__ __forceinline__ double* at(long long r) const { return r < split ? p + r : q + (r - split); }
+};
+
+// The history entering a step: slot of its idx-th vector, oldest first; the
+// new vector takes slot k (idx = n_new - 1).
+__device__ __forceinline__ int diis_slot(int k, int n_new, int M, int idx) { return (k - n_new + 1 + idx + M) % M; }
+
+// old = the amplitudes.
+__global__ void diis_save_kernel(DiisAmps t, DiisArgs a, double* __restrict__ old) {
+  long long lo, hi;
+  double w;
+  diis_chunk(a, blockIdx.x, lo, hi, w);
+  const DiisChunkAmps x(t, a, lo);
+  const long long n = hi - lo;
+#pragma unroll
+  for (int u = 0; u < DIIS_U; ++u) {
+    const long long r = threadIdx.x + u * TPB;
+    if (r < n) old[lo + r] = *x.at(r);
+  }
+}
+
+// With e = T - old (T: the Jacobi amplitudes): T and e enter slot k of the
+// history, part[j][c] = w_c sum over chunk c of e * errs[j] for the slots j
+// held, and part[M][c] = w_c sum of e^2.
+// Bound by memory: a chunk of e stays in the registers of one workgroup while
+// the error vectors held go by, so T and old are read once and nothing is read
+// of empty slots.  Before, one workgroup per chunk and slot read T and old
+// M + 1 times and every slot, the history was written by a pass of its own, and
+// T was copied out of the amplitudes and back: with all of that gone the
+// iteration at o = 10, v = 90, M = 8 takes 5.5 ms less (three: 313 -> 296 ms),
+// a batch of 48 small systems 234 -> 223 ms.
+__global__ __launch_bounds__(TPB) void diis_overlap_kernel(DiisAmps t, const double* __restrict__ old,
+                                                           double* __restrict__ vecs, double* __restrict__ errs,
+                                                           DiisArgs a, long long nchunk, const int* __restrict__ st,
+                                                           double* __restrict__ part) {
+  constexpr int G = 8;  // sums reduced together
+  __shared__ double red[G][TPB];
   const long long c = blockIdx.x;
-  const int j = blockIdx.y;
   long long lo, hi;
   double w;
   diis_chunk(a, c, lo, hi, w);
-  const double* ej = errs + (long long)j * a.L;
-  double acc = 0.0;
-  for (long long i = lo + threadIdx.x; i < hi; i += TPB) {
-    const double e = vnew[i] - old[i];
-    acc += e * (j < a.M ? ej[i] : e);
+  const int k = st[0], n_new = st[1] + 1 < a.M ? st[1] + 1 : a.M;
+  const long long base = (long long)k * a.L + lo, n = hi - lo;
+  const DiisChunkAmps x(t, a, lo);
+  double e[DIIS_U];
+#pragma unroll
+  for (int u = 0; u < DIIS_U; ++u) {
+    const long long r = threadIdx.x + u * TPB;
+    e[u] = 0.0;
+    if (r < n) {
+      const double vn = *x.at(r);
+      e[u] = vn - old[lo + r];
+      vecs[base + r] = vn;
+    }
   }
-  const double s = block_sum(acc, red);
-  if (threadIdx.x == 0) part[(long long)j * nchunk + c] = w * s;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int g = 0; g < n_new; g += G) {
+    const int m = n_new - g < G ? n_new - g : G;
+    for (int jj = 0; jj < m; ++jj) {
+      double acc = 0.0;
+      if (g + jj + 1 < n_new) {
+        const double* ej = errs + (long long)diis_slot(k, n_new, a.M, g + jj) * a.L + lo;
+        double y[DIIS_U];
+#pragma unroll
+        for (int u = 0; u < DIIS_U; ++u) {
+          const long long r = threadIdx.x + u * TPB;
+          y[u] = r < n ? ej[r] : 0.0;
+        }
+#pragma unroll
+        for (int u = 0; u < DIIS_U; ++u) acc += e[u] * y[u];
+      } else {
+#pragma unroll
+        for (int u = 0; u < DIIS_U; ++u) acc += e[u] * e[u];
+      }
+      red[jj][threadIdx.x] = acc;
+    }
+    __syncthreads();
+    for (int jj = wave; jj < m; jj += TPB / 64) {
+      double sum = (red[jj][lane] + red[jj][lane + 128]) + (red[jj][lane + 64] + red[jj][lane + 192]);
+      for (int d = 32; d > 0; d >>= 1) sum += __shfl_down(sum, d);
+      const int row = g + jj + 1 < n_new ? diis_slot(k, n_new, a.M, g + jj) : a.M;
+      if (lane == 0) part[(long long)row * nchunk + c] = w * sum;
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int u = 0; u < DIIS_U; ++u) {
+    const long long r = threadIdx.x + u * TPB;
+    if (r < n) errs[base + r] = e[u];
+  }
 }
 
-__global__ void diis_finalize_kernel(const double* __restrict__ part, long long nchunk, double* __restrict__ d) {
+// d[j] = sum of part[j] for the slots held before this step and for j = M; the
+// other rows of part were not written and their d is not read.
+__global__ void diis_finalize_kernel(const double* __restrict__ part, long long nchunk, const int* __restrict__ st,
+                                     int M, double* __restrict__ d) {
   __shared__ double red[TPB];
   const int j = blockIdx.x;
+  const int k = st[0], n_new = st[1] + 1 < M ? st[1] + 1 : M;
+  if (j < M) {
+    bool held = false;
+    for (int idx = 0; idx + 1 < n_new; ++idx) held = held || diis_slot(k, n_new, M, idx) == j;
+    if (!held) {
+      if (threadIdx.x == 0) d[j] = 0.0;
+      return;
+    }
+  }
   double acc = 0.0;
   for (long long i = threadIdx.x; i < nchunk; i += TPB) acc += part[(long long)j * nchunk + i];
   const double s = block_sum(acc, red);
@@ -1196,28 +1292,34 @@ __global__ void diis_solve_kernel(const double* __restrict__ d, double* __restri
   }
 }
 
-// The new vector and its error enter the slot the solve assigned.
-__global__ void diis_push_kernel(const double* __restrict__ vnew, const double* __restrict__ old,
-                                 double* __restrict__ vecs, double* __restrict__ errs, long long L,
-                                 const int* __restrict__ st) {
-  const long long base = (long long)st[2] * L;
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < L; i += (long long)gridDim.x * blockDim.x) {
-    const double vn = vnew[i];
-    vecs[base + i] = vn;
-    errs[base + i] = vn - old[i];
-  }
-}
-
-// vnew = sum_idx coef[idx] vecs[slot idx] (oldest first) when the solve
-// succeeded; otherwise vnew keeps the Jacobi vector.
-__global__ void diis_extrapolate_kernel(double* __restrict__ vnew, const double* __restrict__ vecs, long long L,
-                                        const int* __restrict__ st, const double* __restrict__ coef) {
+// T = sum_idx coef[idx] vecs[slot idx] (oldest first) when the solve
+// succeeded; otherwise T keeps the Jacobi amplitudes.
+__global__ __launch_bounds__(TPB) void diis_extrapolate_kernel(DiisAmps t, const double* __restrict__ vecs, DiisArgs a,
+                                                               const int* __restrict__ st,
+                                                               const double* __restrict__ coef) {
   if (st[3] == 0) return;
   const int m = st[4];
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < L; i += (long long)gridDim.x * blockDim.x) {
-    double acc = 0.0;
-    for (int idx = 0; idx < m; ++idx) acc = fma(coef[idx], vecs[(long long)st[5 + idx] * L + i], acc);
-    vnew[i] = acc;
+  long long lo, hi;
+  double w;
+  diis_chunk(a, blockIdx.x, lo, hi, w);
+  const long long n = hi - lo;
+  const DiisChunkAmps x(t, a, lo);
+  double acc[DIIS_U];
+#pragma unroll
+  for (int u = 0; u < DIIS_U; ++u) acc[u] = 0.0;
+  for (int idx = 0; idx < m; ++idx) {
+    const double cf = coef[idx];
+    const double* y = vecs + (long long)st[5 + idx] * a.L + lo;
+#pragma unroll
+    for (int u = 0; u < DIIS_U; ++u) {
+      const long long r = threadIdx.x + u * TPB;
+      acc[u] = fma(cf, r < n ? y[r] : 0.0, acc[u]);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < DIIS_U; ++u) {
+    const long long r = threadIdx.x + u * TPB;
+    if (r < n) *x.at(r) = acc[u];
   }
 }
 
@@ -1246,19 +1348,25 @@ long long diis_chunks(const DiisArgs& a) {
   return nc12 + (long long)a.ntri * ((a.bs + DIIS_CH - 1) / DIIS_CH);
 }
 
-hipError_t diis_device_step(double* vnew, const double* old, double* vecs, double* errs, double* part, double* d,
+hipError_t diis_save(const DiisAmps& t, double* old, const DiisArgs& a, hipStream_t s) {
+  const long long nc = diis_chunks(a);
+  if (nc < 1 || nc > INT_MAX) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(diis_save_kernel, dim3((unsigned)nc), dim3(TPB), 0, s, t, a, old);
+  return hipGetLastError();
+}
+
+hipError_t diis_device_step(const DiisAmps& t, const double* old, double* vecs, double* errs, double* part, double* d,
                             double* B, int* st, double* coef, const DiisArgs& a, hipStream_t s) {
   if (a.M < 1 || a.M > DIIS_MAX || a.L <= 0) return hipErrorInvalidValue;
   const long long nc = diis_chunks(a);
   if (nc > INT_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(diis_overlap_kernel, dim3((unsigned)nc, (unsigned)(a.M + 1)), dim3(TPB), 0, s,
-                     (const double*)vnew, old, (const double*)errs, a, nc, part);
-  hipLaunchKernelGGL(diis_finalize_kernel, dim3((unsigned)(a.M + 1)), dim3(TPB), 0, s, (const double*)part, nc, d);
+  hipLaunchKernelGGL(diis_overlap_kernel, dim3((unsigned)nc), dim3(TPB), 0, s, t, old, vecs, errs, a, nc,
+                     (const int*)st, part);
+  hipLaunchKernelGGL(diis_finalize_kernel, dim3((unsigned)(a.M + 1)), dim3(TPB), 0, s, (const double*)part, nc,
+                     (const int*)st, a.M, d);
   hipLaunchKernelGGL(diis_solve_kernel, dim3(1), dim3(64), 0, s, (const double*)d, B, st, coef, a.M, a.start);
-  hipLaunchKernelGGL(diis_push_kernel, dim3(blocks_for(a.L, TPB * 4)), dim3(TPB), 0, s, (const double*)vnew, old,
-                     vecs, errs, a.L, (const int*)st);
-  hipLaunchKernelGGL(diis_extrapolate_kernel, dim3(blocks_for(a.L, TPB * 4)), dim3(TPB), 0, s, vnew,
-                     (const double*)vecs, a.L, (const int*)st, (const double*)coef);
+  hipLaunchKernelGGL(diis_extrapolate_kernel, dim3((unsigned)nc), dim3(TPB), 0, s, t, (const double*)vecs, a,
+                     (const int*)st, (const double*)coef);
   return hipGetLastError();
 }
 
