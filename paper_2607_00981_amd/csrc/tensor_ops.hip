@@ -38,13 +38,17 @@ __device__ __forceinline__ void put_out(const OutSpec& o, long long i, double x)
 // ---------------------------------------------------------------------------
 // permute / accumulate
 // ---------------------------------------------------------------------------
-__global__ void permute_add_kernel(const double* __restrict__ X, double* __restrict__ Y, PermArgs p, long long total) {
-  for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
-       idx += (long long)gridDim.x * blockDim.x) {
-    long long r = idx, ox = 0, oy = 0;
+// IT: 32 bits where the element count allows them; a 64-bit division by each
+// dimension took several times as long as the access (o = 4, v = 20: 5.8 -> 4.6 us each).
+template <typename IT>
+__global__ void permute_add_kernel(const double* __restrict__ X, double* __restrict__ Y, PermArgs p, IT total) {
+  for (IT idx = (IT)blockIdx.x * blockDim.x + threadIdx.x; idx < total; idx += (IT)gridDim.x * blockDim.x) {
+    IT r = idx;
+    long long ox = 0, oy = 0;
     for (int d = p.nd - 1; d >= 0; --d) {
-      const long long c = r % p.dim[d];
-      r /= p.dim[d];
+      const IT q = r / (IT)p.dim[d];
+      const long long c = (long long)(r - q * (IT)p.dim[d]);
+      r = q;
       ox += c * p.sx[d];
       oy += c * p.sy[d];
     }
@@ -56,55 +60,102 @@ __global__ void permute_add_kernel(const double* __restrict__ X, double* __restr
 // ---------------------------------------------------------------------------
 // T3 unpacking
 // ---------------------------------------------------------------------------
-// grid.y enumerates (slot, free indices); grid.x enumerates tiles of the v^3 virtual block.
 // LDS-staged unpack.  One workgroup builds one UT x UT x UT tile of one
-// output block.  Each term is gathered with the threads running along the
-// axis that is unit-stride in that term's stored block (coalesced 128-byte
-// row segments whatever the virtual permutation) and accumulated into the
-// LDS tile; the tile is then written with the threads running along the
-// output's unit-stride axis.
+// output block (a slot with its free indices).  Each term is gathered with the
+// threads running along the axis that is unit-stride in that term's stored
+// block (coalesced 128-byte row segments whatever the virtual permutation) and
+// accumulated into the LDS tile; the tile is then written with the threads
+// running along the output's unit-stride axis.
+// Sixteen lanes run along the unit-stride axis u, sixteen rows along the next,
+// and a thread's elements along the third, so that one offset per thread and
+// one uniform stride per step address all of them: with the three coordinates
+// and three 64-bit products of each element worked out anew the vector units,
+// not the memory, set the time (the hole ladder's at
+// o = 8, v = 61: 452 -> 373 us; at o = 4, v = 20 16.0 -> 8.4 us).
 constexpr int UT = 16;
 constexpr int UP_Z = UT + 1;            // pitch of y rows in the LDS tile
 constexpr int UP_X = UT * UP_Z + 1;     // pitch of x planes
 
-// Tile of this workgroup.  Workgroups go to the eight XCDs in turn, so tile
-// k * per + i runs on XCD k: each XCD takes a contiguous range of tiles, and
-// neighbouring tiles, which share the 128-byte lines that a row of v values
-// leaves partly used when v is not a multiple of 16, meet in one L2 instead
-// of fetching (and writing) the same lines from two.  The grid's x extent is
-// 8 per; workgroups past the last tile return at once.
-__device__ __forceinline__ int xcd_tile(int ntiles) {
-  const int per = (ntiles + 7) / 8;
-  return (int)(blockIdx.x % 8) * per + (int)(blockIdx.x / 8);
+// Tile of block blockIdx.y / (member, tile) of a workgroup, see xcd_place:
+// blocks of XCD_MEMBER tiles and more lie along the grid's y axis, each XCD
+// taking a contiguous range of a block's tiles, so that neighbouring tiles,
+// which share the 128-byte lines that a row of v values leaves partly used when
+// v is not a multiple of 16, meet in one L2 instead of fetching (and writing)
+// the same lines from two; the tiles of smaller blocks form one order, without
+// which blocks of 27 tiles leave one XCD idle and blocks of one tile seven.
+__device__ __forceinline__ bool ut_place(int nt, int nblk, int& tile, int& blk) {
+  const int n = nt * nt * nt;
+  if (n < XCD_MEMBER) return xcd_place(n, nblk, tile, blk);
+  tile = (int)(blockIdx.x % 8) * ((n + 7) / 8) + (int)(blockIdx.x / 8);
+  blk = blockIdx.y;
+  return tile < n;
 }
-inline unsigned xcd_tiles_grid(int ntiles) { return (unsigned)(((ntiles + 7) / 8) * 8); }
+inline dim3 ut_grid(int nt, long long nblk) {
+  const long long n = (long long)nt * nt * nt;
+  if (n < XCD_MEMBER) return dim3((unsigned)xcd_grid(n, nblk));
+  return dim3((unsigned)((n + 7) / 8 * 8), (unsigned)nblk);
+}
+
+__device__ __forceinline__ int ut_pick(int m, int x, int y, int z) { return m == 0 ? x : (m == 1 ? y : z); }
+__device__ __forceinline__ long long ut_pick(int m, long long x, long long y, long long z) {
+  return m == 0 ? x : (m == 1 ? y : z);
+}
+
+// This thread's column of a tile: lane i along axis u, row j along the next
+// axis, element it = 0..15 along the third, for a tensor of strides s0, s1, s2.
+struct UtColumn {
+  int i, j;            // clamped to the tile's extent
+  int nb;              // extent along the third axis
+  bool ok;             // i, j inside
+  long long thr, col;  // offset of the thread, and of one step along the third axis
+  int lds, lds_col;
+  __device__ __forceinline__ UtColumn(int u, const int* ext, long long s0, long long s1, long long s2) {
+    const int ua = (u + 1) % 3, ub = (u + 2) % 3;
+    const int i0 = threadIdx.x % UT, j0 = threadIdx.x / UT;
+    const int eu = ut_pick(u, ext[0], ext[1], ext[2]), ea = ut_pick(ua, ext[0], ext[1], ext[2]);
+    nb = ut_pick(ub, ext[0], ext[1], ext[2]);
+    ok = i0 < eu && j0 < ea;
+    i = i0 < eu ? i0 : eu - 1;
+    j = j0 < ea ? j0 : ea - 1;
+    thr = i * ut_pick(u, s0, s1, s2) + j * ut_pick(ua, s0, s1, s2);
+    col = ut_pick(ub, s0, s1, s2);
+    lds = i0 * ut_pick(u, UP_X, UP_Z, 1) + j0 * ut_pick(ua, UP_X, UP_Z, 1);
+    lds_col = ut_pick(ub, UP_X, UP_Z, 1);
+  }
+};
+
+__device__ __forceinline__ void ut_store(const OutSpec& out, long long off, const double* L, const UtColumn& c) {
+  if (!c.ok) return;
+#pragma unroll
+  for (int it = 0; it < UT; ++it) {
+    if (it >= c.nb) break;
+    put_out(out, off + c.thr + it * c.col, L[c.lds + it * c.lds_col]);
+  }
+}
 
 template <bool DUAL>
 __global__ __launch_bounds__(256) void unpack_tiled_kernel(const double* __restrict__ T,
                                                            const BlockRef* __restrict__ tbl,
                                                            const int2* __restrict__ slots, OutSpec out,
-                                                           OutSpec out2, UnpackArgs a, int nt) {
+                                                           OutSpec out2, UnpackArgs a, int nt, int nblk) {
   __shared__ double L[UT * UP_X];
   const int o = a.o, v = a.v;
   const int nfc = (a.nfree == 2) ? o * o : o;
-  const int sy_ = blockIdx.y;
+  int tile, sy_;
+  if (!ut_place(nt, nblk, tile, sy_)) return;
   const int slot = sy_ / nfc;
   const int fc = sy_ - slot * nfc;
   const int f0 = (a.nfree == 2) ? fc / o : fc;
   const int f1 = (a.nfree == 2) ? fc - f0 * o : 0;
   const int2 fx = slots[slot];
   const int ids[4] = {fx.x, fx.y, f0, f1};
-  const int tile = xcd_tile(nt * nt * nt);
-  if (tile >= nt * nt * nt) return;
   const int t2 = tile % nt, t1 = (tile / nt) % nt, t0 = tile / (nt * nt);
   // the fastest tile digit runs along the output's unit-stride axis
   const int wf = a.fast == 0 ? 2 : (a.fast == 1 ? 1 : 0);
-  int tb[3];
-  tb[wf] = t2;
-  tb[(wf + 1) % 3] = t1;
-  tb[(wf + 2) % 3] = t0;
-  const int base[3] = {tb[0] * UT, tb[1] * UT, tb[2] * UT};  // x, y, z origins
-  const long long obase = (long long)slot * a.s_slot + (long long)f0 * a.s_free[0] + (long long)f1 * a.s_free[1];
+  const int b0 = (wf == 0 ? t2 : (wf == 2 ? t1 : t0)) * UT;  // x, y, z origins
+  const int b1 = (wf == 1 ? t2 : (wf == 0 ? t1 : t0)) * UT;
+  const int b2 = (wf == 2 ? t2 : (wf == 1 ? t1 : t0)) * UT;
+  const int ext[3] = {v - b0 < UT ? v - b0 : UT, v - b1 < UT ? v - b1 : UT, v - b2 < UT ? v - b2 : UT};
   for (int t = 0; t < a.nterms; ++t) {
     const UnpackTerm& tm = a.terms[t];
     const int p = ids[tm.occ[0]], q = ids[tm.occ[1]], r = ids[tm.occ[2]];
@@ -114,65 +165,41 @@ __global__ __launch_bounds__(256) void unpack_tiled_kernel(const double* __restr
 #pragma unroll
     for (int m = 0; m < 3; ++m)
       if (br.s[m] == 1) u = tm.virt[m];
-    const int ua = (u + 1) % 3, ub = (u + 2) % 3;
     // stride of each output axis in the stored block
-    long long st[3];
+    long long s0 = 0, s1 = 0, s2 = 0;
 #pragma unroll
-    for (int m = 0; m < 3; ++m) st[tm.virt[m]] = br.s[m];
-    // all loads of this thread first (independent, in flight together), then the LDS updates
-    constexpr int PER = UT * UT * UT / 256;
-    double vals[PER];
-    int lds[PER];
-#pragma unroll
-    for (int it = 0; it < PER; ++it) {
-      const int e = threadIdx.x + it * 256;
-      int c[3];
-      c[u] = e % UT;
-      c[ua] = (e / UT) % UT;
-      c[ub] = e / (UT * UT);
-      const int x = base[0] + c[0], y = base[1] + c[1], z = base[2] + c[2];
-      const bool ok = x < v && y < v && z < v;
-      lds[it] = ok ? c[0] * UP_X + c[1] * UP_Z + c[2] : -1;
-      vals[it] = ok ? T[br.off + x * st[0] + y * st[1] + z * st[2]] : 0.0;
+    for (int m = 0; m < 3; ++m) {
+      if (tm.virt[m] == 0) s0 = br.s[m];
+      if (tm.virt[m] == 1) s1 = br.s[m];
+      if (tm.virt[m] == 2) s2 = br.s[m];
     }
+    const UtColumn c(u, ext, s0, s1, s2);
+    const double* Tt = T + br.off + b0 * s0 + b1 * s1 + b2 * s2;
+    // all loads of this thread first (independent, in flight together), then the
+    // LDS updates; past the edge the last element is read again and its place
+    // in LDS not written out
+    double vals[UT];
 #pragma unroll
-    for (int it = 0; it < PER; ++it) {
-      if (lds[it] < 0) continue;
+    for (int it = 0; it < UT; ++it) vals[it] = Tt[(it < c.nb ? it : c.nb - 1) * c.col + c.thr];
+#pragma unroll
+    for (int it = 0; it < UT; ++it) {
       const double val = tm.coef * vals[it];
-      L[lds[it]] = (t == 0) ? val : L[lds[it]] + val;
+      const int e = c.lds + it * c.lds_col;
+      L[e] = (t == 0) ? val : L[e] + val;
     }
     __syncthreads();
   }
   // write the tile along the output's unit-stride axis (fast: 0 = z, 1 = y, 2 = x)
   {
-    const int w = a.fast == 0 ? 2 : (a.fast == 1 ? 1 : 0);
-    const int wa = (w + 1) % 3, wb = (w + 2) % 3;
-    const long long so[3] = {a.s_x, a.s_y, a.s_z};
-    for (int e = threadIdx.x; e < UT * UT * UT; e += blockDim.x) {
-      int c[3];
-      c[w] = e % UT;
-      c[wa] = (e / UT) % UT;
-      c[wb] = e / (UT * UT);
-      const int x = base[0] + c[0], y = base[1] + c[1], z = base[2] + c[2];
-      if (x >= v || y >= v || z >= v) continue;
-      put_out(out, obase + x * so[0] + y * so[1] + z * so[2], L[c[0] * UP_X + c[1] * UP_Z + c[2]]);
-    }
+    const long long off = (long long)slot * a.s_slot + (long long)f0 * a.s_free[0] + (long long)f1 * a.s_free[1] +
+                          b0 * a.s_x + b1 * a.s_y + b2 * a.s_z;
+    ut_store(out, off, L, UtColumn(wf, ext, a.s_x, a.s_y, a.s_z));
   }
   if constexpr (DUAL) {
-    const long long obase2 =
-        (long long)slot * a.s2_slot + (long long)f0 * a.s2_free[0] + (long long)f1 * a.s2_free[1];
     const int w = a.fast2 == 0 ? 2 : (a.fast2 == 1 ? 1 : 0);
-    const int wa = (w + 1) % 3, wb = (w + 2) % 3;
-    const long long so[3] = {a.s2_x, a.s2_y, a.s2_z};
-    for (int e = threadIdx.x; e < UT * UT * UT; e += blockDim.x) {
-      int c[3];
-      c[w] = e % UT;
-      c[wa] = (e / UT) % UT;
-      c[wb] = e / (UT * UT);
-      const int x = base[0] + c[0], y = base[1] + c[1], z = base[2] + c[2];
-      if (x >= v || y >= v || z >= v) continue;
-      put_out(out2, obase2 + x * so[0] + y * so[1] + z * so[2], L[c[0] * UP_X + c[1] * UP_Z + c[2]]);
-    }
+    const long long off = (long long)slot * a.s2_slot + (long long)f0 * a.s2_free[0] +
+                          (long long)f1 * a.s2_free[1] + b0 * a.s2_x + b1 * a.s2_y + b2 * a.s2_z;
+    ut_store(out2, off, L, UtColumn(w, ext, a.s2_x, a.s2_y, a.s2_z));
   }
 }
 
@@ -182,59 +209,45 @@ __global__ __launch_bounds__(256) void unpack_tiled_kernel(const double* __restr
 // One workgroup per UT^3 tile of one output block: the R tile is staged in
 // LDS, each contribution is added with the threads running along the axis
 // that is unit-stride in Z for that contribution (coalesced reads for any
-// virtual permutation), and the tile is written back along c.
+// virtual permutation), and the tile is written back along c.  Addressed like
+// the unpack (o = 10, v = 90: FP32 blocks of the
+// rings 2.1 and 3.4 -> 0.9 and 1.4 ms, FP64 2.4 -> 2.1 ms).
 template <typename ZT>
 __global__ __launch_bounds__(256) void fold_tiled_kernel(double* __restrict__ R, long long bs, int v,
                                                          const ZT* __restrict__ Z,
                                                          const FoldTask* __restrict__ tasks,
-                                                         const FoldContrib* __restrict__ contribs, int nt) {
+                                                         const FoldContrib* __restrict__ contribs, int nt,
+                                                         int nblk) {
   __shared__ double L[UT * UP_X];
-  constexpr int PER = UT * UT * UT / 256;
-  const FoldTask tk = tasks[blockIdx.y];
+  int tile, blk;
+  if (!ut_place(nt, nblk, tile, blk)) return;
+  const FoldTask tk = tasks[blk];
   const long long v2 = (long long)v * v;
-  double* Rt = R + (long long)tk.t * bs;
-  const int tile = xcd_tile(nt * nt * nt);
-  if (tile >= nt * nt * nt) return;
   const int t2 = tile % nt, t1 = (tile / nt) % nt, t0 = tile / (nt * nt);
-  const int base[3] = {t0 * UT, t1 * UT, t2 * UT};  // a, b, c origins
+  const int b0 = t0 * UT, b1 = t1 * UT, b2 = t2 * UT;  // a, b, c origins
+  const int ext[3] = {v - b0 < UT ? v - b0 : UT, v - b1 < UT ? v - b1 : UT, v - b2 < UT ? v - b2 : UT};
+  double* Rt = R + (long long)tk.t * bs + b0 * v2 + (long long)b1 * v + b2;
+  const UtColumn cr(2, ext, v2, v, 1);
 #pragma unroll
-  for (int it = 0; it < PER; ++it) {
-    const int e = threadIdx.x + it * 256;
-    const int c2 = e % UT, c1 = (e / UT) % UT, c0 = e / (UT * UT);
-    const int a = base[0] + c0, b = base[1] + c1, c = base[2] + c2;
-    if (a < v && b < v && c < v) L[c0 * UP_X + c1 * UP_Z + c2] = Rt[a * v2 + (long long)b * v + c];
-  }
+  for (int it = 0; it < UT; ++it)
+    L[cr.lds + it * cr.lds_col] = Rt[(it < cr.nb ? it : cr.nb - 1) * cr.col + cr.thr];
   __syncthreads();
   for (int i = 0; i < tk.nc; ++i) {
     const FoldContrib fc = contribs[tk.c0 + i];
-    const long long st[3] = {fc.sa, fc.sb, fc.sc};
-    const int u = fc.sa == 1 ? 0 : (fc.sb == 1 ? 1 : 2);
-    const int ua = (u + 1) % 3, ub = (u + 2) % 3;
-    double vals[PER];
-    int lds[PER];
+    const UtColumn c(fc.sa == 1 ? 0 : (fc.sb == 1 ? 1 : 2), ext, fc.sa, fc.sb, fc.sc);
+    const ZT* Zt = Z + fc.base + b0 * fc.sa + b1 * fc.sb + b2 * fc.sc;
+    double vals[UT];
 #pragma unroll
-    for (int it = 0; it < PER; ++it) {
-      const int e = threadIdx.x + it * 256;
-      int cc[3];
-      cc[u] = e % UT;
-      cc[ua] = (e / UT) % UT;
-      cc[ub] = e / (UT * UT);
-      const int a = base[0] + cc[0], b = base[1] + cc[1], c = base[2] + cc[2];
-      const bool ok = a < v && b < v && c < v;
-      lds[it] = ok ? cc[0] * UP_X + cc[1] * UP_Z + cc[2] : -1;
-      vals[it] = ok ? (double)Z[fc.base + a * st[0] + b * st[1] + c * st[2]] : 0.0;
-    }
+    for (int it = 0; it < UT; ++it) vals[it] = (double)Zt[(it < c.nb ? it : c.nb - 1) * c.col + c.thr];
 #pragma unroll
-    for (int it = 0; it < PER; ++it)
-      if (lds[it] >= 0) L[lds[it]] += fc.coef * vals[it];
+    for (int it = 0; it < UT; ++it) L[c.lds + it * c.lds_col] += fc.coef * vals[it];
     __syncthreads();
   }
+  if (!cr.ok) return;
 #pragma unroll
-  for (int it = 0; it < PER; ++it) {
-    const int e = threadIdx.x + it * 256;
-    const int c2 = e % UT, c1 = (e / UT) % UT, c0 = e / (UT * UT);
-    const int a = base[0] + c0, b = base[1] + c1, c = base[2] + c2;
-    if (a < v && b < v && c < v) Rt[a * v2 + (long long)b * v + c] = L[c0 * UP_X + c1 * UP_Z + c2];
+  for (int it = 0; it < UT; ++it) {
+    if (it >= cr.nb) break;
+    Rt[it * cr.col + cr.thr] = L[cr.lds + it * cr.lds_col];
   }
 }
 
@@ -517,7 +530,13 @@ hipError_t permute_add(const double* X, double* Y, const PermArgs& p, hipStream_
   long long total = 1;
   for (int d = 0; d < p.nd; ++d) total *= p.dim[d];
   if (total <= 0) return hipSuccess;
-  hipLaunchKernelGGL(permute_add_kernel, dim3(blocks_for(total, TPB * 4)), dim3(TPB), 0, s, X, Y, p, total);
+  const dim3 grid(blocks_for(total, TPB * 4));
+  // (half the range, so that the last stride of the loop does not wrap)
+  if (total <= INT_MAX)
+    hipLaunchKernelGGL(permute_add_kernel<unsigned>, grid, dim3(TPB), 0, s, X, Y, p, (unsigned)total);
+  else
+    hipLaunchKernelGGL(permute_add_kernel<unsigned long long>, grid, dim3(TPB), 0, s, X, Y, p,
+                       (unsigned long long)total);
   return hipGetLastError();
 }
 
@@ -529,8 +548,8 @@ hipError_t unpack_t3_fmt(const double* T, const BlockRef* tbl, const int2* slots
   if (ny > 65535) return hipErrorInvalidValue;
   if (a.nterms < 1 || a.nterms > 6) return hipErrorInvalidValue;
   const int nt = (a.v + UT - 1) / UT;
-  dim3 grid(xcd_tiles_grid(nt * nt * nt), (unsigned)ny);
-  hipLaunchKernelGGL(unpack_tiled_kernel<false>, grid, dim3(TPB), 0, s, T, tbl, slots, out, out, a, nt);
+  hipLaunchKernelGGL(unpack_tiled_kernel<false>, ut_grid(nt, ny), dim3(TPB), 0, s, T, tbl, slots, out, out, a, nt,
+                     (int)ny);
   return hipGetLastError();
 }
 
@@ -542,8 +561,8 @@ hipError_t unpack_t3_dual(const double* T, const BlockRef* tbl, const int2* slot
   if (ny > 65535) return hipErrorInvalidValue;
   if (a.nterms < 1 || a.nterms > 6) return hipErrorInvalidValue;
   const int nt = (a.v + UT - 1) / UT;
-  dim3 grid(xcd_tiles_grid(nt * nt * nt), (unsigned)ny);
-  hipLaunchKernelGGL(unpack_tiled_kernel<true>, grid, dim3(TPB), 0, s, T, tbl, slots, out, out2, a, nt);
+  hipLaunchKernelGGL(unpack_tiled_kernel<true>, ut_grid(nt, ny), dim3(TPB), 0, s, T, tbl, slots, out, out2, a, nt,
+                     (int)ny);
   return hipGetLastError();
 }
 
@@ -557,8 +576,8 @@ hipError_t fold_r3(double* R, long long bs, int v, const double* Z, const FoldTa
   if (ntasks <= 0) return hipSuccess;
   if (ntasks > 65535) return hipErrorInvalidValue;
   const int nt = (v + UT - 1) / UT;
-  dim3 grid(xcd_tiles_grid(nt * nt * nt), (unsigned)ntasks);
-  hipLaunchKernelGGL(fold_tiled_kernel<double>, grid, dim3(TPB), 0, s, R, bs, v, Z, tasks, contribs, nt);
+  hipLaunchKernelGGL(fold_tiled_kernel<double>, ut_grid(nt, ntasks), dim3(TPB), 0, s, R, bs, v, Z, tasks, contribs, nt,
+                     ntasks);
   return hipGetLastError();
 }
 
@@ -567,8 +586,8 @@ hipError_t fold_r3(double* R, long long bs, int v, const float* Z, const FoldTas
   if (ntasks <= 0) return hipSuccess;
   if (ntasks > 65535) return hipErrorInvalidValue;
   const int nt = (v + UT - 1) / UT;
-  dim3 grid(xcd_tiles_grid(nt * nt * nt), (unsigned)ntasks);
-  hipLaunchKernelGGL(fold_tiled_kernel<float>, grid, dim3(TPB), 0, s, R, bs, v, Z, tasks, contribs, nt);
+  hipLaunchKernelGGL(fold_tiled_kernel<float>, ut_grid(nt, ntasks), dim3(TPB), 0, s, R, bs, v, Z, tasks, contribs, nt,
+                     ntasks);
   return hipGetLastError();
 }
 
