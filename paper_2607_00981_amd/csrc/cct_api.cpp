@@ -2281,12 +2281,15 @@ int energy_q_abc(cct_ctx* ctx, int nb, const int64_t* tasks, long long ntasks, d
   HIPCK(hipStreamWaitEvent(sy, side.ready, 0));
 
   double macs_mfma = 0.0, macs_valu = 0.0;
-  auto run = [&](QGemmArgs& g, hipStream_t st) -> int {
+  auto count = [&](const QGemmArgs& g) {
     long long batch = 1;
     for (int d = 0; d < g.nd; ++d) batch *= g.rad[d];
     long long K = 0;
     for (int k = 0; k < g.nseg; ++k) K += g.K[k];
     macs_mfma += (double)g.M * g.N * K * batch;
+  };
+  auto run = [&](QGemmArgs& g, hipStream_t st) -> int {
+    count(g);
     HIPCK(qgemm(g, st));
     return CCT_OK;
   };
@@ -2309,6 +2312,8 @@ int energy_q_abc(cct_ctx* ctx, int nb, const int64_t* tasks, long long ntasks, d
     }
     const long long ntau = (long long)sl.n[0] * sl.n[1] * sl.n[2] * sl.n[3];
     const long long tlen = ntau * o4;
+    T3GatherJob tg[T3_GATHERS];
+    int ntg = 0;
     // T3 slices: X1 fragments [lx][ly][e][i_u][i_v][i_w] (u < v < w the slots
     // other than r; column pairs (i_s0, e), (i_x, tau_x), (i_y, tau_y))
     for (int r = 0; r < 4; ++r) {
@@ -2325,7 +2330,7 @@ int energy_q_abc(cct_ctx* ctx, int nb, const int64_t* tasks, long long ntasks, d
         g.lab[0] = 3; g.ax[0] = pos(s0);
         g.lab[1] = 0; g.ax[1] = pos(x);
         g.lab[2] = 1; g.ax[2] = pos(y);
-        HIPCK(t3v_gather(T3v, frag[r][s0], g, s));
+        tg[ntg++] = T3GatherJob{g, frag[r][s0]};
       }
     }
     // X2 blocks [l_s1][l_c0][l_c1][m][i_c0][i_c1], column pairs (m, tau_s1),
@@ -2345,9 +2350,12 @@ int energy_q_abc(cct_ctx* ctx, int nb, const int64_t* tasks, long long ntasks, d
             g.lab[c] = c;
             g.ax[c] = c;
           }
-          HIPCK(t3v_gather(T3v, x2b[s1][s0], g, s));
+          tg[ntg++] = T3GatherJob{g, x2b[s1][s0]};
         }
       }
+    HIPCK(t3v_gather(T3v, tg, ntg, s));
+    QGemmArgs zg[Q_JOBS];
+    int nzg = 0;
     // Z_abc[la][lb][lc][j][k][e] = 1/2 sum_f v^{xy}_{ef} t_jk^{fz}
     for (int a = 0; a < 4; ++a)
       for (int b = 0; b < 4; ++b)
@@ -2365,17 +2373,24 @@ int energy_q_abc(cct_ctx* ctx, int nb, const int64_t* tasks, long long ntasks, d
           g.sc[0] = (long long)sl.n[b] * sl.n[c] * o2v; g.sc[1] = (long long)sl.n[c] * o2v;
           g.c_len = b3 * o2v;
           g.alpha = 0.5; g.accumulate = 0;
-          RCK(run(g, sy));
+          count(g);
+          zg[nzg++] = g;
         }
+    HIPCK(qgemm_jobs(zg, nzg, sy));
+    QWvJob wv[QW_JOBS];
+    int nwv = 0;
     // Wbar^{vvv}_{voo} for x in slot s0, (y, z) in the row slots (r0, r1)
     for (int s0 = 0; s0 < 4; ++s0)
       for (int r0 = 0; r0 < 4; ++r0)
         for (int r1 = r0 + 1; r1 < 4; ++r1) {
           if (s0 == r0 || s0 == r1) continue;
-          HIPCK(q_wv_build(WvS[s0][pid(r0, r1)], Z[s0][r0][r1], Z[s0][r1][r0], Vmyje, Vmxje, ctx->t2, o, v, sl.st[s0],
-                           sl.n[s0], sl.st[r0], sl.n[r0], sl.st[r1], sl.n[r1], sy));
+          wv[nwv++] = QWvJob{WvS[s0][pid(r0, r1)], Z[s0][r0][r1], Z[s0][r1][r0], sl.st[s0], sl.n[s0],
+                             sl.st[r0], sl.n[r0], sl.st[r1], sl.n[r1]};
           macs_valu += 4.0 * o * sl.n[s0] * sl.n[r0] * sl.n[r1] * o2v;
         }
+    HIPCK(q_wv_build(wv, nwv, Vmyje, Vmxje, ctx->t2, o, v, sy));
+    QWoJob wo[QW_JOBS];
+    int nwo = 0;
     // Wbar^{vvo}_{ooo} for (x, y) in slots (s0 < s1), rows = the slots other than s3
     for (int s3 = 0; s3 < 4; ++s3)
       for (int s2 = 0; s2 < 4; ++s2) {
@@ -2386,11 +2401,11 @@ int energy_q_abc(cct_ctx* ctx, int nb, const int64_t* tasks, long long ntasks, d
         for (int t = 0; t < 4; ++t)
           if (t != s3 && t != s2) p01[kk++] = t;
         auto pos = [&](int sl_) { return sl_ == rs[0] ? 0 : (sl_ == rs[1] ? 1 : 2); };
-        const int rowpos[3] = {pos(p01[0]), pos(p01[1]), pos(s2)};
-        HIPCK(q_wo_build(Wo[s3][s2], Voooo, ctx->t2, o, v, sl.st[p01[0]], sl.n[p01[0]], sl.st[p01[1]], sl.n[p01[1]],
-                         rowpos, sy));
+        wo[nwo++] = QWoJob{Wo[s3][s2], sl.st[p01[0]], sl.n[p01[0]], sl.st[p01[1]], sl.n[p01[1]],
+                           {pos(p01[0]), pos(p01[1]), pos(s2)}};
         macs_valu += 2.0 * o * sl.n[p01[0]] * sl.n[p01[1]] * o4;
       }
+    HIPCK(q_wo_build(wo, nwo, Voooo, ctx->t2, o, v, sy));
     // X1: per row slot r, K segments over s0 (the slot whose label is summed)
     for (int r = 0; r < 4; ++r) {
       int oth[3], k = 0;

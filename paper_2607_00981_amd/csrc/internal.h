@@ -423,6 +423,11 @@ struct QGemmArgs {
   int accumulate;  // 1: C += alpha A B, 0: C = alpha A B
 };
 hipError_t qgemm(const QGemmArgs& g, hipStream_t s);
+// n <= Q_JOBS products that differ in M, the radices, where their operands and
+// C begin and C's digit strides only (one segment, two digits): one launch
+// where they are short, one each otherwise.
+constexpr int Q_JOBS = 24;
+hipError_t qgemm_jobs(const QGemmArgs* g, int n, hipStream_t s);
 
 // T3 in the virtual-triangular layout: block vb(a <= b <= c) (lexicographic)
 // holds t_{ijk}^{abc} for all i, j, k at vb * o^3 + (i o + j) o + k.  Filled
@@ -440,7 +445,12 @@ struct T3Gather {
   int rad[3], st[3];
   int lab[3], ax[3];
 };
-hipError_t t3v_gather(const double* T3v, double* out, const T3Gather& g, hipStream_t s);
+struct T3GatherJob {
+  T3Gather g;
+  double* out;
+};
+constexpr int T3_GATHERS = 24;
+hipError_t t3v_gather(const double* T3v, const T3GatherJob* jobs, int n, hipStream_t s);
 
 // Slots of one virtual tile task: first label and size of each of the four
 // index ranges.
@@ -451,15 +461,25 @@ struct QSlots {
 // (s0, s1) with the occupied indices of slots (s0, s1, s2) in slot order:
 // out[lx][ly][rows][m], rows = the three indices ordered by slot, from
 // Voooo[n][k][i][m] = v^{mn}_{ki} and t2[i][j][a][b].
-hipError_t q_wo_build(double* out, const double* Voooo, const double* t2, int o, int v, int x0, int nx, int y0, int ny,
-                      const int rowpos[3], hipStream_t s);
+// rowpos[c]: position in the row index of i (c = 0), j (1), k (2).
+struct QWoJob {
+  double* out;
+  int x0, nx, y0, ny, rowpos[3];
+};
+constexpr int QW_JOBS = 12;  // one per ordered pair of slots, or per slot and pair of the others
+hipError_t q_wo_build(const QWoJob* jobs, int n, const double* Voooo, const double* t2, int o, int v, hipStream_t s);
 // Wbar^{vvv}_{voo} of Eq. q_w_alter for x in slot s0 and (y, z) in slots
 // (r0, r1): out[lx][ly][lz][j][k][e] = Z_xy[z](j, k, e) + Z_xz[y](k, j, e)
 // + the four K = o terms, with Z_ab[c] = 1/2 sum_f v^{ab}_{ef} t_{jk}^{fc}
 // laid out [la][lb][lc][j][k][e] (Zxy: slots (s0, r0, r1), Zxz: (s0, r1, r0)),
 // Vmyje[m][y][j][e] = v^{my}_{ej}, Vmxje[m][x][j][e] = v^{mx}_{je}.
-hipError_t q_wv_build(double* out, const double* Zxy, const double* Zxz, const double* Vmyje, const double* Vmxje,
-                      const double* t2, int o, int v, int x0, int nx, int y0, int ny, int z0, int nz, hipStream_t s);
+struct QWvJob {
+  double* out;
+  const double *Zxy, *Zxz;
+  int x0, nx, y0, ny, z0, nz;
+};
+hipError_t q_wv_build(const QWvJob* jobs, int n, const double* Vmyje, const double* Vmxje, const double* t2, int o,
+                      int v, hipStream_t s);
 // out[i] = src[idx[i]], i < n.
 hipError_t gather_idx(const double* src, const long long* idx, long long n, double* out, hipStream_t s);
 // Energy of the tuples of one task (t2R[b][a][i][j] = t_ij^ab): for every

@@ -10,6 +10,7 @@
 #include <climits>
 #include <cmath>
 #include <cstdint>
+#include <type_traits>
 #include <vector>
 
 #include "internal.h"
@@ -45,14 +46,27 @@ __device__ __forceinline__ bool q_tile(int tiles_m, int tiles_n, int batch, int&
   return true;
 }
 
+// What differs between the products of one launch (grid y), see qgemm_jobs.
+struct QgNone {};
+struct QgJobs {
+  struct Job {
+    const double *a, *b;
+    double* C;
+    long long sc[2];
+    int M, rad[2];
+  } j[Q_JOBS];
+};
+
 // Tile BM x BN = (16 TM WM) x (16 TN WN), WM x WN waves; K tiles of 16 over
 // the concatenated segments; LDS double-buffered as [k][m] and [k][n].
 // Each thread's load units keep their offsets inside the operand (set when a
 // segment starts, advanced by one K tile per step), so the main loop does no
 // index arithmetic beyond an add; the epilogue maps its rows and columns
 // once.
-template <int TM, int TN, int WM, int WN, bool AKM, bool BKN, bool VEC>
-__global__ __launch_bounds__(64 * WM * WN) void qgemm_kernel(QGemmArgs g, int tiles_m, int tiles_n, int batch) {
+template <int TM, int TN, int WM, int WN, bool AKM, bool BKN, bool VEC, class JOBS>
+__global__ __launch_bounds__(64 * WM * WN) void qgemm_kernel(QGemmArgs g, JOBS jobs, int tiles_m, int tiles_n,
+                                                             int batch) {
+  constexpr bool MANY = std::is_same<JOBS, QgJobs>::value;
   constexpr int NTH = 64 * WM * WN, BM = 16 * TM * WM, BN = 16 * TN * WN;
   constexpr int LA = BM + 2, LB = BN + 2;
   constexpr int W = VEC ? 2 : 1;
@@ -64,11 +78,20 @@ __global__ __launch_bounds__(64 * WM * WN) void qgemm_kernel(QGemmArgs g, int ti
   if (!q_tile(tiles_m, tiles_n, batch, tm, tn, z)) return;
   const int tid = threadIdx.x;
   int dig[QG_MAXD] = {0, 0, 0, 0};
-  for (int d = g.nd - 1; d >= 0; --d) {
-    dig[d] = z % g.rad[d];
-    z /= g.rad[d];
-  }
   const int m0 = tm * BM, n0 = tn * BN;
+  int M = g.M;
+  if constexpr (MANY) {
+    const auto& jb = jobs.j[blockIdx.y];
+    M = jb.M;
+    dig[1] = z % jb.rad[1];
+    dig[0] = z / jb.rad[1];
+    if (m0 >= M || dig[0] >= jb.rad[0]) return;
+  } else {
+    for (int d = g.nd - 1; d >= 0; --d) {
+      dig[d] = z % g.rad[d];
+      z /= g.rad[d];
+    }
+  }
   // this thread's load units: position in the tile (row or column, k)
   int ar[NA], ak[NA], br[NB], bk[NB];
 #pragma unroll
@@ -108,8 +131,13 @@ __global__ __launch_bounds__(64 * WM * WN) void qgemm_kernel(QGemmArgs g, int ti
       ao += dig[d] * g.a[s].sd[d];
       bo += dig[d] * g.b[s].sd[d];
     }
-    Ab = g.a[s].p + ao;
-    Bb = g.b[s].p + bo;
+    if constexpr (MANY) {
+      Ab = jobs.j[blockIdx.y].a + ao;
+      Bb = jobs.j[blockIdx.y].b + bo;
+    } else {
+      Ab = g.a[s].p + ao;
+      Bb = g.b[s].p + bo;
+    }
     const long long lda = g.a[s].ld, ldb = g.b[s].ld;
     astep = AKM ? QBK * lda : QBK;
     bstep = BKN ? QBK * ldb : QBK;
@@ -136,7 +164,7 @@ __global__ __launch_bounds__(64 * WM * WN) void qgemm_kernel(QGemmArgs g, int ti
     const long long ash = kt_in_seg * astep, bsh = kt_in_seg * bstep;
 #pragma unroll
     for (int i = 0; i < NA; ++i) {
-      oa[i] = (tid + i * NTH) < UA && m0 + ar[i] < g.M && k0 + ak[i] < seg_k;
+      oa[i] = (tid + i * NTH) < UA && m0 + ar[i] < M && k0 + ak[i] < seg_k;
       const double* p = Ab + (oa[i] ? aoff[i] + ash : 0);
       if constexpr (VEC) ra[i] = *(const dbl2*)p;
       else ra[i].x = *p;
@@ -187,7 +215,14 @@ __global__ __launch_bounds__(64 * WM * WN) void qgemm_kernel(QGemmArgs g, int ti
   }
   // output rows and columns of this lane
   long long coff = 0;
-  for (int d = 0; d < g.nd; ++d) coff += dig[d] * g.sc[d];
+  double* C = g.C;
+  if constexpr (MANY) {
+    const auto& jb = jobs.j[blockIdx.y];
+    C = jb.C;
+    coff = dig[0] * jb.sc[0] + dig[1] * jb.sc[1];
+  } else {
+    for (int d = 0; d < g.nd; ++d) coff += dig[d] * g.sc[d];
+  }
   long long cof[TN];
   bool cin[TN];
 #pragma unroll
@@ -203,8 +238,8 @@ __global__ __launch_bounds__(64 * WM * WN) void qgemm_kernel(QGemmArgs g, int ti
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int m = m0 + wm0 + i * 16 + 4 * r + lane / 16;
-      rin[i][r] = m < g.M;
-      rowp[i][r] = g.C + coff + (rin[i][r] ? map4(g.cm, m) : 0);
+      rin[i][r] = m < M;
+      rowp[i][r] = C + coff + (rin[i][r] ? map4(g.cm, m) : 0);
     }
   __syncthreads();
   for (int t = 0; t < total; ++t) {
@@ -251,8 +286,8 @@ hipError_t qlaunch(const QGemmArgs& g, long long batch, hipStream_t s) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
   const long long gx = xcd_grid((long long)tiles_m * tiles_n, batch);
   if (gx > INT_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((qgemm_kernel<TM, TN, WM, WN, AKM, BKN, VEC>), dim3((unsigned)gx), dim3(64 * WM * WN), 0, s, g,
-                     tiles_m, tiles_n, (int)batch);
+  hipLaunchKernelGGL((qgemm_kernel<TM, TN, WM, WN, AKM, BKN, VEC, QgNone>), dim3((unsigned)gx), dim3(64 * WM * WN), 0, s,
+                     g, QgNone{}, tiles_m, tiles_n, (int)batch);
   return hipGetLastError();
 }
 
@@ -361,8 +396,12 @@ __global__ __launch_bounds__(256) void t3v_transpose_kernel(const double* __rest
 // ordered by virtual label once, which fixes the source block and the
 // stride of each output axis inside it; the threads then copy the o^3
 // block (reads stay inside one 8 o^3-byte block of T3v).
-__global__ __launch_bounds__(256) void t3v_gather_kernel(const double* __restrict__ T3v, double* __restrict__ out,
-                                                         T3Gather g) {
+struct T3GatherJobs {
+  T3GatherJob j[T3_GATHERS];
+};
+__global__ __launch_bounds__(256) void t3v_gather_kernel(const double* __restrict__ T3v, T3GatherJobs jobs) {
+  const T3Gather& g = jobs.j[blockIdx.y].g;
+  double* __restrict__ out = jobs.j[blockIdx.y].out;
   const long long o3 = (long long)g.o * g.o * g.o;
   const int e = (int)(blockIdx.x % g.ne);
   long long r = blockIdx.x / g.ne;
@@ -371,6 +410,7 @@ __global__ __launch_bounds__(256) void t3v_gather_kernel(const double* __restric
     dig[d] = (int)(r % g.rad[d]);
     r /= g.rad[d];
   }
+  if (r > 0) return;  // past this job's blocks
   int lab[3], ax[3];
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
@@ -405,10 +445,15 @@ __global__ __launch_bounds__(256) void t3v_gather_kernel(const double* __restric
 // for x = x0 + lx, y = y0 + ly; element [lx][ly][rows][m] with the row index
 // holding i, j, k at the positions rowpos[0..2].  VT[n][k][i][m] = v^{mn}_{ki}
 // (m fastest, as the output).
-__global__ __launch_bounds__(256) void q_wo_kernel(double* __restrict__ out, const double* __restrict__ VT,
-                                                   const double* __restrict__ t2, int o, int v, int x0, int nx,
-                                                   int y0, int ny, int p0, int p1, int p2, long long total) {
-  const long long vv = (long long)v * v;
+struct QWoJobs {
+  QWoJob j[QW_JOBS];
+};
+__global__ __launch_bounds__(256) void q_wo_kernel(QWoJobs jobs, const double* __restrict__ VT,
+                                                   const double* __restrict__ t2, int o, int v) {
+  const QWoJob& jb = jobs.j[blockIdx.y];
+  double* __restrict__ out = jb.out;
+  const int x0 = jb.x0, y0 = jb.y0, ny = jb.ny, p0 = jb.rowpos[0], p1 = jb.rowpos[1], p2 = jb.rowpos[2];
+  const long long vv = (long long)v * v, total = (long long)jb.nx * ny * o * o * o * o;
   for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
        idx += (long long)gridDim.x * blockDim.x) {
     const int m = (int)(idx % o);
@@ -433,7 +478,7 @@ __global__ __launch_bounds__(256) void q_wo_kernel(double* __restrict__ out, con
   }
 }
 
-// Wbar_{ejk}^{xyz} in two passes for o <= QW_OMAX: pass A writes the two
+// Wbar_{ejk}^{xyz} in two passes for o <= QW_OMAX (OM: o rounded up): pass A writes the two
 // Z terms and the two K = o terms that do not involve k (v^{my}_{ej},
 // v^{mx}_{je} held in registers across the k loop); pass B adds the two that
 // do not involve j (v^{mz}_{ek}, v^{mx}_{ke} held across the j loop).  One
@@ -441,11 +486,19 @@ __global__ __launch_bounds__(256) void q_wo_kernel(double* __restrict__ out, con
 // threads over e; the T2 factors of the workgroup's labels are staged in LDS
 // and read as broadcasts.
 constexpr int QW_OMAX = 32;
-__global__ __launch_bounds__(256) void q_wv_a_kernel(double* __restrict__ out, const double* __restrict__ Zxy,
-                                                     const double* __restrict__ Zxz, const double* __restrict__ Vmyje,
+struct QWvJobs {
+  QWvJob j[QW_JOBS];
+};
+template <int OM>
+__global__ __launch_bounds__(256) void q_wv_a_kernel(QWvJobs jobs, const double* __restrict__ Vmyje,
                                                      const double* __restrict__ Vmxje, const double* __restrict__ t2,
-                                                     int o, int v, int x0, int ny, int y0, int nz, int z0) {
-  __shared__ double ta[QW_OMAX * QW_OMAX], tb[QW_OMAX * QW_OMAX];
+                                                     int o, int v) {
+  const QWvJob& jb = jobs.j[blockIdx.y];
+  double* __restrict__ out = jb.out;
+  const double* __restrict__ Zxy = jb.Zxy;
+  const double* __restrict__ Zxz = jb.Zxz;
+  const int x0 = jb.x0, y0 = jb.y0, ny = jb.ny, z0 = jb.z0, nz = jb.nz;
+  __shared__ double ta[OM * OM], tb[OM * OM];
   const long long ov = (long long)o * v, vv = (long long)v * v, o2v = (long long)o * ov;
   int r = blockIdx.x;
   const int j = r % o;
@@ -453,6 +506,7 @@ __global__ __launch_bounds__(256) void q_wv_a_kernel(double* __restrict__ out, c
   const int lz = r % nz;
   r /= nz;
   const int ly = r % ny, lx = r / ny;
+  if (lx >= jb.nx) return;  // past this job's labels
   const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
   for (int q = threadIdx.x; q < o * o; q += blockDim.x) {  // [m][k]
     const long long row = (long long)q * vv;               // (m o + k) vv
@@ -462,26 +516,30 @@ __global__ __launch_bounds__(256) void q_wv_a_kernel(double* __restrict__ out, c
   __syncthreads();
   const long long bxy = (((long long)lx * ny + ly) * nz + lz) * o2v, bxz = (((long long)lx * nz + lz) * ny + ly) * o2v;
   for (int e = threadIdx.x; e < v; e += blockDim.x) {
-    double u1[QW_OMAX], u2[QW_OMAX];
+    double u1[OM], u2[OM];
 #pragma unroll
-    for (int m = 0; m < QW_OMAX; ++m) {
+    for (int m = 0; m < OM; ++m) {
       u1[m] = m < o ? Vmyje[((long long)m * v + y) * ov + (long long)j * v + e] : 0.0;
       u2[m] = m < o ? Vmxje[((long long)m * v + x) * ov + (long long)j * v + e] : 0.0;
     }
     for (int k = 0; k < o; ++k) {
       double s = Zxy[bxy + ((long long)j * o + k) * v + e] + Zxz[bxz + ((long long)k * o + j) * v + e];
 #pragma unroll
-      for (int m = 0; m < QW_OMAX; ++m)
+      for (int m = 0; m < OM; ++m)
         if (m < o) s -= u1[m] * ta[m * o + k] + u2[m] * tb[m * o + k];
       out[bxy + ((long long)j * o + k) * v + e] = s;
     }
   }
 }
 
-__global__ __launch_bounds__(256) void q_wv_b_kernel(double* __restrict__ out, const double* __restrict__ Vmyje,
+template <int OM>
+__global__ __launch_bounds__(256) void q_wv_b_kernel(QWvJobs jobs, const double* __restrict__ Vmyje,
                                                      const double* __restrict__ Vmxje, const double* __restrict__ t2,
-                                                     int o, int v, int x0, int ny, int y0, int nz, int z0) {
-  __shared__ double ta[QW_OMAX * QW_OMAX], tb[QW_OMAX * QW_OMAX];
+                                                     int o, int v) {
+  const QWvJob& jb = jobs.j[blockIdx.y];
+  double* __restrict__ out = jb.out;
+  const int x0 = jb.x0, y0 = jb.y0, ny = jb.ny, z0 = jb.z0, nz = jb.nz;
+  __shared__ double ta[OM * OM], tb[OM * OM];
   const long long ov = (long long)o * v, vv = (long long)v * v, o2v = (long long)o * ov;
   int r = blockIdx.x;
   const int k = r % o;
@@ -489,6 +547,7 @@ __global__ __launch_bounds__(256) void q_wv_b_kernel(double* __restrict__ out, c
   const int lz = r % nz;
   r /= nz;
   const int ly = r % ny, lx = r / ny;
+  if (lx >= jb.nx) return;  // past this job's labels
   const int x = x0 + lx, y = y0 + ly, z = z0 + lz;
   for (int q = threadIdx.x; q < o * o; q += blockDim.x) {  // [m][j]
     const long long row = (long long)q * vv;
@@ -498,16 +557,16 @@ __global__ __launch_bounds__(256) void q_wv_b_kernel(double* __restrict__ out, c
   __syncthreads();
   const long long b = (((long long)lx * ny + ly) * nz + lz) * o2v;
   for (int e = threadIdx.x; e < v; e += blockDim.x) {
-    double w1[QW_OMAX], w2[QW_OMAX];
+    double w1[OM], w2[OM];
 #pragma unroll
-    for (int m = 0; m < QW_OMAX; ++m) {
+    for (int m = 0; m < OM; ++m) {
       w1[m] = m < o ? Vmyje[((long long)m * v + z) * ov + (long long)k * v + e] : 0.0;
       w2[m] = m < o ? Vmxje[((long long)m * v + x) * ov + (long long)k * v + e] : 0.0;
     }
     for (int j = 0; j < o; ++j) {
       double s = 0.0;
 #pragma unroll
-      for (int m = 0; m < QW_OMAX; ++m)
+      for (int m = 0; m < OM; ++m)
         if (m < o) s += w1[m] * ta[m * o + j] + w2[m] * tb[m * o + j];
       out[b + ((long long)j * o + k) * v + e] -= s;
     }
@@ -515,11 +574,15 @@ __global__ __launch_bounds__(256) void q_wv_b_kernel(double* __restrict__ out, c
 }
 
 // Wbar_{ejk}^{xyz} (alternative form) as [lx][ly][lz][j][k][e].
-__global__ __launch_bounds__(256) void q_wv_kernel(double* __restrict__ out, const double* __restrict__ Zxy,
-                                                   const double* __restrict__ Zxz, const double* __restrict__ Vmyje,
+__global__ __launch_bounds__(256) void q_wv_kernel(QWvJobs jobs, const double* __restrict__ Vmyje,
                                                    const double* __restrict__ Vmxje, const double* __restrict__ t2,
-                                                   int o, int v, int x0, int nx, int y0, int ny, int z0, int nz,
-                                                   long long total) {
+                                                   int o, int v) {
+  const QWvJob& jb = jobs.j[blockIdx.y];
+  double* __restrict__ out = jb.out;
+  const double* __restrict__ Zxy = jb.Zxy;
+  const double* __restrict__ Zxz = jb.Zxz;
+  const int x0 = jb.x0, y0 = jb.y0, ny = jb.ny, z0 = jb.z0, nz = jb.nz;
+  const long long total = (long long)jb.nx * ny * nz * o * o * v;
   const long long ov = (long long)o * v, vv = (long long)v * v, o2v = (long long)o * ov;
   for (long long idx = (long long)blockIdx.x * blockDim.x + threadIdx.x; idx < total;
        idx += (long long)gridDim.x * blockDim.x) {
@@ -706,17 +769,19 @@ unsigned grid_for(long long n) { return (unsigned)std::min<long long>((n + 255) 
 
 }  // namespace
 
-hipError_t qgemm(const QGemmArgs& g, hipStream_t s) {
-  if (g.M <= 0 || g.N <= 0) return hipSuccess;
+namespace {
+// Host checks of a product with M, N > 0: batch members and whether its loads
+// may be two elements wide.
+hipError_t qcheck(const QGemmArgs& g, long long& batch, bool& vec) {
   if (g.nseg < 1 || g.nseg > QG_MAXSEG || g.nd < 0 || g.nd > QG_MAXD) return hipErrorInvalidValue;
-  long long batch = 1;
+  batch = 1;
   for (int d = 0; d < g.nd; ++d) {
     if (g.rad[d] < 1) return hipErrorInvalidValue;
     batch *= g.rad[d];
   }
   if (batch > INT_MAX / 2) return hipErrorInvalidValue;
   // host bounds check: the largest offset each operand and C reach
-  bool vec = true;
+  vec = true;
   for (int sg = 0; sg < g.nseg; ++sg) {
     if (g.K[sg] < 0) return hipErrorInvalidValue;
     const QgOperand* ops[2] = {&g.a[sg], &g.b[sg]};
@@ -767,14 +832,76 @@ hipError_t qgemm(const QGemmArgs& g, hipStream_t s) {
     for (int d = 0; d < g.nd; ++d) hi += (long long)(g.rad[d] - 1) * g.sc[d];
     if (g.c_len > 0 && hi >= g.c_len) return hipErrorInvalidValue;
   }
+  return hipSuccess;
+}
+constexpr long long QSHORT = 64;  // the longest of the short contractions
+}  // namespace
+
+hipError_t qgemm(const QGemmArgs& g, hipStream_t s) {
+  if (g.M <= 0 || g.N <= 0) return hipSuccess;
+  long long batch;
+  bool vec;
+  const hipError_t e = qcheck(g, batch, vec);
+  if (e != hipSuccess) return e;
   // short contractions are bound by the update of C: small tiles, several
   // workgroups per compute unit
   long long ktot = 0;
   for (int sg = 0; sg < g.nseg; ++sg) ktot += g.K[sg];
-  const int cfg = ktot <= 64 ? QCFG_N - 1 : qpick(g.M, g.N);
+  const int cfg = ktot <= QSHORT ? QCFG_N - 1 : qpick(g.M, g.N);
   if (g.akm && !g.bkn) return vec ? qdispatch<true, false, true>(cfg, g, batch, s) : qdispatch<true, false, false>(cfg, g, batch, s);
   if (!g.akm && g.bkn) return vec ? qdispatch<false, true, true>(cfg, g, batch, s) : qdispatch<false, true, false>(cfg, g, batch, s);
   return hipErrorInvalidValue;  // the two mirrored layouts are the ones used
+}
+
+// Short products (64 x 64 tiles) leave the chip part idle and last little
+// longer than a launch: the 24 Z products of a task of six labels per slot at
+// o = 8, v = 60 have 216 workgroups each, 12 us one after
+// another; together they take 147 us.
+// Longer contractions choose a tile by their own sizes and fill the chip.
+hipError_t qgemm_jobs(const QGemmArgs* g, int n, hipStream_t s) {
+  if (n < 1) return hipSuccess;
+  bool one = n <= Q_JOBS && g[0].nseg == 1 && g[0].K[0] <= QSHORT && g[0].nd == 2 && g[0].akm && !g[0].bkn;
+  bool vec = true;
+  int m_max = 0;
+  long long b_max = 0;
+  QgJobs jb{};
+  auto same = [](const Idx4& x, const Idx4& y) {
+    return x.n1 == y.n1 && x.n2 == y.n2 && x.n3 == y.n3 && x.s0 == y.s0 && x.s1 == y.s1 && x.s2 == y.s2 && x.s3 == y.s3;
+  };
+  for (int i = 0; one && i < n; ++i) {
+    const QGemmArgs& q = g[i];
+    one = q.M > 0 && q.N > 0 && q.N == g[0].N && q.nseg == 1 && q.nd == 2 && q.K[0] == g[0].K[0] && q.akm && !q.bkn &&
+          q.a[0].ld == g[0].a[0].ld && q.b[0].ld == g[0].b[0].ld && same(q.cm, g[0].cm) && same(q.cn, g[0].cn) &&
+          q.alpha == g[0].alpha && q.accumulate == g[0].accumulate;
+    for (int d = 0; d < 2; ++d)
+      one = one && q.a[0].sd[d] == g[0].a[0].sd[d] && q.b[0].sd[d] == g[0].b[0].sd[d];
+    if (!one) break;
+    long long batch;
+    bool v2;
+    const hipError_t e = qcheck(q, batch, v2);
+    if (e != hipSuccess) return e;
+    vec = vec && v2;
+    m_max = std::max(m_max, q.M);
+    b_max = std::max(b_max, batch);
+    jb.j[i] = QgJobs::Job{q.a[0].p, q.b[0].p, q.C, {q.sc[0], q.sc[1]}, q.M, {q.rad[0], q.rad[1]}};
+  }
+  const int tiles_m = (m_max + 63) / 64, tiles_n = (g[0].N + 63) / 64;
+  const long long gx = one ? xcd_grid((long long)tiles_m * tiles_n, b_max) : 0;
+  if (!one || gx * 256 > INT_MAX) {
+    for (int i = 0; i < n; ++i) {
+      const hipError_t e = qgemm(g[i], s);
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  const dim3 grid((unsigned)gx, (unsigned)n);
+  if (vec)
+    hipLaunchKernelGGL((qgemm_kernel<2, 2, 2, 2, true, false, true, QgJobs>), grid, dim3(256), 0, s, g[0], jb, tiles_m,
+                       tiles_n, (int)b_max);
+  else
+    hipLaunchKernelGGL((qgemm_kernel<2, 2, 2, 2, true, false, false, QgJobs>), grid, dim3(256), 0, s, g[0], jb, tiles_m,
+                       tiles_n, (int)b_max);
+  return hipGetLastError();
 }
 
 hipError_t t3v_transpose(const double* T, const BlockRef* tbl, double* T3v, const int4* cubes, long long ncubes,
@@ -790,42 +917,79 @@ hipError_t t3v_transpose(const double* T, const BlockRef* tbl, double* T3v, cons
   return hipGetLastError();
 }
 
-hipError_t t3v_gather(const double* T3v, double* out, const T3Gather& g, hipStream_t s) {
-  long long nblk = g.ne;
-  for (int d = 0; d < g.nd; ++d) nblk *= g.rad[d];
-  if (nblk <= 0 || g.o <= 0) return hipSuccess;
-  if (nblk > INT_MAX) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(t3v_gather_kernel, dim3((unsigned)nblk), dim3(256), 0, s, T3v, out, g);
-  return hipGetLastError();
-}
-
-hipError_t q_wo_build(double* out, const double* Voooo, const double* t2, int o, int v, int x0, int nx, int y0, int ny,
-                      const int rowpos[3], hipStream_t s) {
-  const long long total = (long long)nx * ny * o * o * o * o;
-  if (total <= 0) return hipSuccess;
-  // rowpos[c]: position in the row index of i (c = 0), j (1), k (2); the
-  // kernel reads i = w[p0] etc. with w the row digits
-  hipLaunchKernelGGL(q_wo_kernel, dim3(grid_for(total)), dim3(256), 0, s, out, Voooo, t2, o, v, x0, nx, y0, ny,
-                     rowpos[0], rowpos[1], rowpos[2], total);
-  return hipGetLastError();
-}
-
-hipError_t q_wv_build(double* out, const double* Zxy, const double* Zxz, const double* Vmyje, const double* Vmxje,
-                      const double* t2, int o, int v, int x0, int nx, int y0, int ny, int z0, int nz, hipStream_t s) {
-  const long long total = (long long)nx * ny * nz * o * o * v;
-  if (total <= 0) return hipSuccess;
-  if (o <= QW_OMAX) {
-    const unsigned nblk = (unsigned)((long long)nx * ny * nz * o);  // (lx, ly, lz, j) and (lx, ly, lz, k)
-    const unsigned nth = (unsigned)std::min(256, ((v + 63) / 64) * 64);
-    hipLaunchKernelGGL(q_wv_a_kernel, dim3(nblk), dim3(nth), 0, s, out, Zxy, Zxz, Vmyje, Vmxje, t2, o, v, x0, ny, y0,
-                       nz, z0);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(q_wv_b_kernel, dim3(nblk), dim3(nth), 0, s, out, Vmyje, Vmxje, t2, o, v, x0, ny, y0, nz, z0);
-    return hipGetLastError();
+hipError_t t3v_gather(const double* T3v, const T3GatherJob* jobs, int n, hipStream_t s) {
+  if (n > T3_GATHERS) return hipErrorInvalidValue;
+  T3GatherJobs jb{};
+  long long most = 0;
+  int m = 0;
+  for (int i = 0; i < n; ++i) {
+    long long nblk = jobs[i].g.ne;
+    for (int d = 0; d < jobs[i].g.nd; ++d) nblk *= jobs[i].g.rad[d];
+    if (nblk <= 0 || jobs[i].g.o <= 0) continue;
+    most = std::max(most, nblk);
+    jb.j[m++] = jobs[i];
   }
-  hipLaunchKernelGGL(q_wv_kernel, dim3(grid_for(total)), dim3(256), 0, s, out, Zxy, Zxz, Vmyje, Vmxje, t2, o, v, x0,
-                     nx, y0, ny, z0, nz, total);
+  if (m == 0) return hipSuccess;
+  if (most > INT_MAX) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(t3v_gather_kernel, dim3((unsigned)most, (unsigned)m), dim3(256), 0, s, T3v, jb);
+  return hipGetLastError();
+}
+
+// The Wbar builds of a task in one launch each (grid y): a build of 216 label
+// triples has 1728 workgroups of one wave, less than two per SIMD, and is all
+// latency on its own: twelve of them 390 us in 24 launches, 140 in two.  With the
+// gathers and the Z products in one launch each as well the tasks of o = 8, v = 60,
+// six labels per slot take 33.9 ms in place of 48.0.
+hipError_t q_wo_build(const QWoJob* jobs, int n, const double* Voooo, const double* t2, int o, int v, hipStream_t s) {
+  if (n > QW_JOBS) return hipErrorInvalidValue;
+  QWoJobs jb{};
+  long long most = 0;
+  int m = 0;
+  for (int i = 0; i < n; ++i) {
+    const long long total = (long long)jobs[i].nx * jobs[i].ny * o * o * o * o;
+    if (total <= 0) continue;
+    most = std::max(most, total);
+    jb.j[m++] = jobs[i];
+  }
+  if (m == 0) return hipSuccess;
+  hipLaunchKernelGGL(q_wo_kernel, dim3(grid_for(most), (unsigned)m), dim3(256), 0, s, jb, Voooo, t2, o, v);
+  return hipGetLastError();
+}
+
+template <int OM>
+static hipError_t wv_passes(dim3 grid, unsigned nth, const QWvJobs& jb, const double* Vmyje, const double* Vmxje,
+                            const double* t2, int o, int v, hipStream_t s) {
+  hipLaunchKernelGGL(q_wv_a_kernel<OM>, grid, dim3(nth), 0, s, jb, Vmyje, Vmxje, t2, o, v);
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(q_wv_b_kernel<OM>, grid, dim3(nth), 0, s, jb, Vmyje, Vmxje, t2, o, v);
+  return hipGetLastError();
+}
+
+hipError_t q_wv_build(const QWvJob* jobs, int n, const double* Vmyje, const double* Vmxje, const double* t2, int o,
+                      int v, hipStream_t s) {
+  if (n > QW_JOBS) return hipErrorInvalidValue;
+  QWvJobs jb{};
+  long long most = 0;
+  int m = 0;
+  for (int i = 0; i < n; ++i) {
+    const long long c = (long long)jobs[i].nx * jobs[i].ny * jobs[i].nz;
+    if (c * o * o * v <= 0) continue;
+    most = std::max(most, c);
+    jb.j[m++] = jobs[i];
+  }
+  if (m == 0) return hipSuccess;
+  if (o <= QW_OMAX) {
+    const dim3 grid((unsigned)(most * o), (unsigned)m);  // (lx, ly, lz, j) and (lx, ly, lz, k)
+    const unsigned nth = (unsigned)std::min(256, ((v + 63) / 64) * 64);
+    // the V columns held per thread (2 o doubles) decide the waves per SIMD (o = 8:
+    // 163 and 155 us with room for 32, 76 and 64 with room for 8)
+    return o <= 8 ? wv_passes<8>(grid, nth, jb, Vmyje, Vmxje, t2, o, v, s)
+                  : (o <= 16 ? wv_passes<16>(grid, nth, jb, Vmyje, Vmxje, t2, o, v, s)
+                             : wv_passes<QW_OMAX>(grid, nth, jb, Vmyje, Vmxje, t2, o, v, s));
+  }
+  hipLaunchKernelGGL(q_wv_kernel, dim3(grid_for(most * o * o * v), (unsigned)m), dim3(256), 0, s, jb, Vmyje, Vmxje, t2,
+                     o, v);
   return hipGetLastError();
 }
 
