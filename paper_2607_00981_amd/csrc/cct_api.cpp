@@ -843,7 +843,7 @@ int feedback(cct_ctx* ctx) {
     }
     HIPCK(zero_cols(OutSpec{UA, OUT_F64, 0}, rows_a * S, v2p, v2, s));
     HIPCK(zero_cols(OutSpec{UB, OUT_F64, 0}, rows_b * S, ovp, ov, s));
-    HIPCK(feedback_r1(UA, v2p, vvT, ctx->r1, o, v, S, f0, s));
+    HIPCK(feedback_r1(UA, v2p, vvT, ctx->r1, o, v, S, f0, ctx->red, ctx->red_n, s));
     // partial sums in what is left of the workspace, else in R3, which is
     // filled after this
     auto product = [&](const double* A, long long M, long long K, const double* B, long long ldb, long long b_len,

@@ -264,8 +264,9 @@ hipError_t axpby(double a, const double* x, double b, double* y, long long n, hi
 hipError_t fill(double* y, double val, long long n, hipStream_t s);
 // R1[i][a] += 1/2 sum_{j in [f0, f0+S), k, b, c} vvT[j][k][c][b] (2 U[(k,i,c)][j-f0][a][b] - U[(k,i,a)][j-f0][c][b])
 // with U[(k,i,x)][j'][p][q] the single-check spin-summed slab t~_{j k i}^{q x p} (slots of ldu >= v^2
-// doubles; one block per (i,a)).
+// doubles).  part: part_n >= o v doubles of scratch.
 hipError_t feedback_r1(const double* U, long long ldu, const double* vvT, double* r1, int o, int v, int S, int f0,
+                       double* part, long long part_n,
                        hipStream_t s);
 // Partial sums of the two feedback products added up (in order) and into place:
 //   part[z][(i,j,a)][n]: X2[(i,j,a)][n] += for n < v, W[a][n - v][(i,j)] += for the o after them;

@@ -936,31 +936,49 @@ hipError_t pair_combine_cols(const float* CpT, const float* CmT, long long ncol,
 // ---------------------------------------------------------------------------
 namespace {
 
-__global__ void r1_feedback_kernel(const double* __restrict__ U, long long ldu, const double* __restrict__ vvT,
-                                   double* __restrict__ r1, int o, int v, int S, int f0) {
+// One workgroup per (i, a) and share y of the (slot, k) planes: part[y][ia].
+// Reads both terms' rows of U, of which one hits the caches, near the rate of
+// a copy at o = 10, v = 90; with one workgroup per (i, a) the small systems
+// left the chip idle and a 64-bit division per element cost more than its
+// loads (o = 8, v = 61: 316 -> 173 us; o = 10, v = 90: 2.05 -> 1.85 ms; a batch of
+// 48 small systems 206 -> 204 ms).
+__global__ __launch_bounds__(TPB) void r1_feedback_kernel(const double* __restrict__ U, long long ldu,
+                                                          const double* __restrict__ vvT, double* __restrict__ part,
+                                                          int o, int v, int S, int f0) {
   __shared__ double red[TPB];
   const int ia = blockIdx.x;
   const int i = ia / v, a = ia - (ia / v) * v;
-  const long long v2 = (long long)v * v, rowS = (long long)S * ldu;
+  const int v2 = v * v;
+  const long long rowS = (long long)S * ldu;
+  const int dc = TPB / v, db = TPB % v;
   double acc = 0.0;
-  for (int jj = 0; jj < S; ++jj) {
-    for (int k = 0; k < o; ++k) {
-      const double* M = vvT + ((long long)(f0 + jj) * o + k) * v2;            // [c][b]
-      const double* U1 = U + ((long long)(k * o + i) * v) * rowS + jj * ldu + (long long)a * v;  // + c rowS + b
-      const double* U2 = U + ((long long)(k * o + i) * v + a) * rowS + jj * ldu;             // + c v + b
-      for (long long e = threadIdx.x; e < v2; e += TPB) {
-        const int c = (int)(e / v), b = (int)(e - (long long)c * v);
-        acc += M[e] * (2.0 * U1[(long long)c * rowS + b] - U2[e]);
+  for (int q = blockIdx.y; q < S * o; q += gridDim.y) {
+    const int jj = q / o, k = q - jj * o;
+    const double* M = vvT + ((long long)(f0 + jj) * o + k) * v2;            // [c][b]
+    const double* U1 = U + ((long long)(k * o + i) * v) * rowS + jj * ldu + (long long)a * v;  // + c rowS + b
+    const double* U2 = U + ((long long)(k * o + i) * v + a) * rowS + jj * ldu;             // + c v + b
+    int c = threadIdx.x / v, b = threadIdx.x % v;
+#pragma unroll 4
+    for (int e = threadIdx.x; e < v2; e += TPB) {
+      acc += M[e] * (2.0 * U1[c * rowS + b] - U2[e]);
+      c += dc;
+      b += db;
+      if (b >= v) {
+        b -= v;
+        ++c;
       }
     }
   }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int w = TPB / 2; w > 0; w >>= 1) {
-    if ((int)threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) r1[ia] += 0.5 * red[0];
+  const double s = block_sum(acc, red);
+  if (threadIdx.x == 0) part[(long long)blockIdx.y * gridDim.x + ia] = s;
+}
+
+__global__ void r1_feedback_sum_kernel(const double* __restrict__ part, int splits, double* __restrict__ r1, int n) {
+  const int ia = blockIdx.x * TPB + threadIdx.x;
+  if (ia >= n) return;
+  double s = 0.0;
+  for (int y = 0; y < splits; ++y) s += part[(long long)y * n + ia];
+  r1[ia] += 0.5 * s;
 }
 
 __global__ void feedback_add_a_kernel(const double* __restrict__ part, int splits, double* __restrict__ X2,
@@ -1026,9 +1044,17 @@ __global__ void add_diag_rows_kernel(double* __restrict__ Y, const double* __res
 }  // namespace
 
 hipError_t feedback_r1(const double* U, long long ldu, const double* vvT, double* r1, int o, int v, int S, int f0,
-                       hipStream_t s) {
+                       double* part, long long part_n, hipStream_t s) {
   if (S <= 0) return hipSuccess;
-  hipLaunchKernelGGL(r1_feedback_kernel, dim3((unsigned)(o * v)), dim3(TPB), 0, s, U, ldu, vvT, r1, o, v, S, f0);
+  const long long n = (long long)o * v;
+  if (v > 46340 || part_n < n) return hipErrorInvalidValue;
+  // eight workgroups for each of the 256 compute units, as far as the planes and part go
+  long long y = (2048 + n - 1) / n;
+  y = std::min(std::min(y, (long long)S * o), std::min<long long>(part_n / n, 65535));
+  hipLaunchKernelGGL(r1_feedback_kernel, dim3((unsigned)n, (unsigned)y), dim3(TPB), 0, s, U, ldu, vvT, part, o, v, S,
+                     f0);
+  hipLaunchKernelGGL(r1_feedback_sum_kernel, dim3((unsigned)((n + TPB - 1) / TPB)), dim3(TPB), 0, s,
+                     (const double*)part, (int)y, r1, (int)n);
   return hipGetLastError();
 }
 
