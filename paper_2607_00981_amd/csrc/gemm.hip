@@ -377,11 +377,17 @@ hipError_t gemm(const GemmArgs& g, Prec prec, hipStream_t s) {
   if (g.c_len > 0 && nb * g.c_batch + idx_max(g.cm, g.M) + idx_max(g.cn, g.N) >= g.c_len) return hipErrorInvalidValue;
   if (g.K <= 0) return g.beta == 1.0 ? hipSuccess : hipErrorInvalidValue;
   const long long work = (long long)g.M * g.N * g.batch;
-  if (work >= (long long)256 * 128 * 128 * 2) return launch<128, 128>(g, prec, s);
+  // large products: 128 x 128 tiles, or 64 x 64 where those leave much less
+  // padding (o = 8, v = 61, hole ladder of 36 rows and F terms of 61: the residual
+  // from 28.4 to 27.5 ms)
+  auto used = [&](int t) { return (double)g.M * g.N / ((double)((g.M + t - 1) / t * t) * (double)((g.N + t - 1) / t * t)); };
+  const long long tiles64 = (long long)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch;
+  if (work >= (long long)256 * 128 * 128 * 2 && (used(64) <= 1.15 * used(128) || tiles64 > (1 << 23)))
+    return launch<128, 128>(g, prec, s);
   // fewer 64 x 64 tiles than compute units: 32 x 32, four times the workgroups
   // and a quarter of the matrix-core time in each step of K (o = 4, v = 20: 38
   // launches per iteration from 11.4 to 7.1 us each)
-  if ((long long)((g.M + 63) / 64) * ((g.N + 63) / 64) * g.batch < 256) return launch<32, 32>(g, prec, s);
+  if (tiles64 < 256) return launch<32, 32>(g, prec, s);
   return launch<64, 64>(g, prec, s);
 }
 
