@@ -775,12 +775,15 @@ hipError_t launch_tall(const TallArgs& g, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Columns of 16 per tile: the fewest padded columns, then the widest tile.
+// Columns of 16 per tile: the fewest padded columns, a tile of t counted 0.3/t
+// dearer for reading and waiting on A once per tile (at N = 200 the 13 tiles of
+// 16 without padding took the T3 feedback of o = 20, v = 180 to 1.82 s, two of
+// 112 take 1.20 s, the four products before it 1.31).
 int tall_tn(int N) {
   int best = 8;
-  auto padded = [&](int t) { return (N + 16 * t - 1) / (16 * t) * t; };
+  auto cost = [&](int t) { return (double)((N + 16 * t - 1) / (16 * t) * t) * (1.0 + 0.3 / t); };
   for (int t = 7; t >= 1; --t)
-    if (padded(t) < padded(best)) best = t;
+    if (cost(t) < cost(best)) best = t;
   return best;
 }
 
