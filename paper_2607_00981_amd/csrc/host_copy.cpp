@@ -6,7 +6,7 @@
 // the first time on that thread), against 57 GB/s into pinned memory.  The
 // staged copy keeps the link busy: a few threads each own two pinned buffers,
 // let the copy engine fill one while they move the other to its place, and
-// take the next chunk from a shared counter.  Fresh destination, MI355X machine,
+// take the next chunk from a shared counter.  Fresh destination, on MI355X,
 // plain -> staged: 3 MB 0.71 -> 0.46 ms, 8 MB 0.80 -> 0.61 ms, 32 MB 3.16 ->
 // 1.16 ms, 93 MB 9.4 -> 2.6 ms, 1 GB 101 -> 26 ms (41 GB/s; the first touch of
 // the destination's pages is what is left).

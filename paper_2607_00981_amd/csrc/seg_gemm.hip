@@ -35,7 +35,7 @@ __device__ __forceinline__ bool seg_tile(int tiles_m, int tiles_n, int batch, in
   return true;
 }
 
-// C_z(m, n) (+)= sum_s coef_s sum_k A_s(m, k) B_s(k, n), one item z per grid z.
+// C_z(m, n) (+)= sum_s coef_s sum_k A_s(m, k) B_s(k, n), one item z and tile per workgroup (xcd_place).
 //
 // Bound: at v = 48 the products of one task are 24 v^5 multiply-adds against
 // 14 updates of a v^4 array, about 13 FLOP per byte of accumulator traffic, so
