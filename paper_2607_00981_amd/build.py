@@ -15,7 +15,7 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libcct.so")
 
 SOURCES = ["gemm.hip", "tensor_ops.hip", "seg_gemm.hip", "q_ops.hip", "q_abc.hip", "contract.cpp", "cct_api.cpp",
-           "slab.cpp", "quad.cpp", "host_copy.cpp"]
+           "slab.cpp", "quad.cpp", "host_copy.cpp", "device_memory.cpp"]
 
 FLAGS = [
     "--offload-arch=gfx950",

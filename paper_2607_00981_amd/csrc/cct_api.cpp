@@ -164,25 +164,12 @@ long long tri_count(int o) { return (long long)o * (o + 1) * (o + 2) / 6; }
 
 // Device memory from the caller's allocator when one was given, else hipMalloc.
 int dev_alloc(cct_ctx* ctx, void** p, size_t bytes) {
-  void* q = nullptr;
+  const char* why = "";
   bytes = std::max<size_t>(bytes, 8);
-  if (ctx->alloc_fn) {
-    q = ctx->alloc_fn(bytes, ctx->alloc_user);
-    if (!q || ((uintptr_t)q & 255)) {
-      if (q) ctx->free_fn(q, ctx->alloc_user);
-      ctx->err = "caller allocator: " + std::string(q ? "pointer not 256-byte aligned" : "NULL") + " for " +
-                 std::to_string(bytes) + " bytes";
-      return CCT_ENOMEM;
-    }
-  } else {
-    const hipError_t e = hipMalloc(&q, bytes);
-    if (e != hipSuccess) {
-      ctx->err = std::string("hipMalloc of ") + std::to_string(bytes) + " bytes: " + hipGetErrorString(e);
-      return CCT_ENOMEM;
-    }
-  }
-  *p = q;
-  return CCT_OK;
+  *p = device_alloc(bytes, ctx->alloc_fn, ctx->free_fn, ctx->alloc_user, &why);
+  if (*p) return CCT_OK;
+  ctx->err = std::string(why) + " for " + std::to_string(bytes) + " bytes";
+  return CCT_ENOMEM;
 }
 void dev_free(cct_ctx* ctx, void* p) {
   if (!p) return;
@@ -3485,11 +3472,8 @@ int cct_batch_create(int nsys, const int* nocc, const int* nvir, const int* naux
   int rc = CCT_OK;
   {
     const size_t bytes = sizeof(double) * 4 * (size_t)nsys;
-    void* p = nullptr;
-    if (alloc) p = alloc(bytes, alloc_user);
-    else if (hipMalloc(&p, bytes) != hipSuccess) p = nullptr;
-    if (!p) rc = CCT_ENOMEM;
-    b->dout = (double*)p;
+    b->dout = (double*)device_alloc(bytes, alloc, free_fn, alloc_user);
+    if (!b->dout) rc = CCT_ENOMEM;
   }
   for (int i = 0; i < nstreams && rc == CCT_OK; ++i) {
     hipStream_t s = nullptr;

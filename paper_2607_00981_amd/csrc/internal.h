@@ -7,7 +7,14 @@
 #include <string>
 #include <vector>
 
+#include "cct.h"
+
 namespace cct {
+
+// Device memory from the caller's allocator where one is given, else from
+// hipMalloc on the current device.  nullptr: refused (or, from the caller's,
+// not aligned to 256 bytes: *why says which); no error is left pending.
+void* device_alloc(size_t bytes, cct_alloc_fn alloc, cct_free_fn free_fn, void* user, const char** why = nullptr);
 
 // Synchronous device-to-host copy on stream s (of device dev), through a pool
 // of pinned buffers and a few threads where dst is pageable and large.  Every

@@ -64,17 +64,11 @@ namespace {
   } while (0)
 
 int qalloc(cct_quad* q, void** p, size_t bytes) {
-  void* x = nullptr;
+  const char* why = "";
   bytes = std::max<size_t>(bytes, 8);
-  if (q->alloc_fn) {
-    x = q->alloc_fn(bytes, q->alloc_user);
-    if (!x || ((uintptr_t)x & 255)) {
-      if (x) q->free_fn(x, q->alloc_user);
-      q->err = "caller allocator: " + std::string(x ? "pointer not 256-byte aligned" : "NULL");
-      return CCT_ENOMEM;
-    }
-  } else if (hipMalloc(&x, bytes) != hipSuccess) {
-    q->err = "hipMalloc of " + std::to_string(bytes) + " bytes failed";
+  void* x = device_alloc(bytes, q->alloc_fn, q->free_fn, q->alloc_user, &why);
+  if (!x) {
+    q->err = std::string(why) + " for " + std::to_string(bytes) + " bytes";
     return CCT_ENOMEM;
   }
   q->owned.push_back(x);

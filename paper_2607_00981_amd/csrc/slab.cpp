@@ -87,22 +87,12 @@ namespace {
 
 // Device memory from the caller's allocator when one was given, else hipMalloc.
 int sdev_alloc(cct_slab* sl, void** p, size_t bytes) {
-  void* q = nullptr;
+  const char* why = "";
   bytes = std::max<size_t>(bytes, 8);
-  if (sl->alloc_fn) {
-    q = sl->alloc_fn(bytes, sl->alloc_user);
-    if (!q || ((uintptr_t)q & 255)) {
-      if (q) sl->free_fn(q, sl->alloc_user);
-      sl->err = "caller allocator: " + std::string(q ? "pointer not 256-byte aligned" : "NULL") + " for " +
-                std::to_string(bytes) + " bytes";
-      return CCT_ENOMEM;
-    }
-  } else if (hipMalloc(&q, bytes) != hipSuccess) {
-    sl->err = "hipMalloc of " + std::to_string(bytes) + " bytes failed";
-    return CCT_ENOMEM;
-  }
-  *p = q;
-  return CCT_OK;
+  *p = device_alloc(bytes, sl->alloc_fn, sl->free_fn, sl->alloc_user, &why);
+  if (*p) return CCT_OK;
+  sl->err = std::string(why) + " for " + std::to_string(bytes) + " bytes";
+  return CCT_ENOMEM;
 }
 void sdev_free(cct_slab* sl, void* p) {
   if (!p) return;

@@ -1,0 +1,108 @@
+"""GPU: objects and calls where device memory is short.  The card is filled but
+for a stated rest (hipMalloc, freed at the end), or the caller's allocator
+refuses above a limit; what ran before on that rest has to run, and a refusal
+has to be CCT_ENOMEM with nothing left behind.  Results are compared with those
+of the same object where memory is plentiful (equal bits where the same launches
+run, else the tolerance of the object's own tests)."""
+
+import contextlib
+import ctypes as C
+import sys
+import time
+
+import numpy as np
+import pytest
+
+import cct_inputs as ci
+from paper_2607_00981_amd import binding
+
+pytestmark = pytest.mark.gpu
+
+
+def say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+def _hip():
+    """The libamdhip64 already mapped into this process by libcct."""
+    binding.load()
+    with open("/proc/self/maps") as f:
+        paths = {line.split()[-1] for line in f if "libamdhip64" in line}
+    assert paths, "libamdhip64 is not loaded"
+    hip = C.CDLL(sorted(paths)[0])
+    hip.hipMemGetInfo.argtypes = [C.POINTER(C.c_size_t), C.POINTER(C.c_size_t)]
+    hip.hipMalloc.argtypes = [C.POINTER(C.c_void_p), C.c_size_t]
+    hip.hipFree.argtypes = [C.c_void_p]
+    return hip
+
+
+def free_bytes():
+    fr, tot = C.c_size_t(), C.c_size_t()
+    assert _hip().hipMemGetInfo(C.byref(fr), C.byref(tot)) == 0
+    return fr.value
+
+
+@contextlib.contextmanager
+def rest_of_card(rest):
+    """All but `rest` bytes of the free device memory taken."""
+    hip = _hip()
+    held = []
+    try:
+        for _ in range(50):  # memory freed shortly before turns up a little later
+            more = free_bytes() - rest
+            if more > 8 << 20:
+                p = C.c_void_p()
+                assert hip.hipMalloc(C.byref(p), more) == 0
+                held.append(p)
+            time.sleep(0.01)
+        say(f"  {free_bytes() / 1e6:.0f} MB left of {rest / 1e6:.0f} asked for")
+        yield
+    finally:
+        for p in held:
+            assert hip.hipFree(p) == 0
+
+
+def _engine(o, v, seed, **kw):
+    s = ci.make_system(o, v, 2 * (o + v), seed, sigma=0.1)
+    t2 = ci.random_amplitudes(o, v, seed, 0.0, 0.05, 0.0, triples=False)[1]
+    eng = binding.Engine(o, v, s["naux"], **kw)
+    eng.set_fock(s["f"])
+    eng.set_eri_df(s["B"])
+    eng.set_amplitudes(np.zeros((o, v)), t2, ci.random_t3_packed(o, v, seed + 1, 0.03))
+    return eng
+
+
+def test_a_refused_object_leaves_no_error_pending():
+    say("[memory limits] slab of 8 TB refused, then an iteration")
+    with _engine(3, 8, 1) as eng:
+        with pytest.raises(binding.CCTError) as err:
+            binding.Slab(1, 1000, 1_000_000, 0, 1)
+        assert err.value.code == binding.CCT_ENOMEM
+        eng.update()
+
+
+def _slab_inputs(o, v, naux, count, seed):
+    rng = np.random.default_rng(seed)
+    s = ci.make_system(o, v, naux, seed, sigma=0.1)
+    t2 = ci.random_amplitudes(o, v, seed, 0.03, 0.03, 0.0, triples=False)[1]
+    return (s["B"], t2, rng.normal(0, 0.1, (v, v)), rng.normal(0, 0.1, (o, v, v, v)),
+            rng.normal(0, 0.1, (v, o, o, o)), ci.random_t3_packed(o, v, seed + 1, 0.02)[:count])
+
+
+def _slab_residual(inputs, o, v, naux, count, **kw):
+    with binding.Slab(o, v, naux, 0, count, **kw) as sl:
+        sl.set_intermediates(*inputs[:-1])
+        sl.set_t3(inputs[-1])
+        return sl.residual()[0]
+
+
+def test_slab_panel_narrows_when_memory_is_short():
+    """The whole of W is 680 MB here, eight rows of it 57 MB."""
+    o, v, naux, count = 2, 96, 20, 1
+    say(f"[memory limits] slab panel o={o} v={v}")
+    inputs = _slab_inputs(o, v, naux, count, 5)
+    want = _slab_residual(inputs, o, v, naux, count, opts={"panel": 8})
+    with rest_of_card(400 << 20):
+        got = _slab_residual(inputs, o, v, naux, count)
+    assert np.array_equal(got, want)
