@@ -169,9 +169,10 @@ int cct_solve(cct_ctx* ctx, int max_iter, double tol, double* e_corr, int* iters
  * 8 * (n^4 + o^2 v^4 + o^3 v^3 + 2 o^4 v^2 + 28 v^4 + 48 * 4096 ceil(v/8)^4)
  * bytes of device memory for even v and nocc <= 16 (room for the accumulators
  * of more tasks at a time), else 8 * (n^4 + o^2 v^4 + o^3 v^3 + 2 o^4 v^2 + 52 v^4)
- * (about 110 GB at o=10, v=90): CCT_ENOMEM if that is not free (checked
- * before allocating when the library allocates; a caller's allocator is
- * asked block by block).  Where the library allocates, up to 4 GiB of it stay
+ * (about 110 GB at o=10, v=90); 128 MiB where that is more: CCT_ENOMEM if that
+ * is not free (checked before allocating when the library allocates; a caller's
+ * allocator is asked block by block, for fewer tasks at a time where it
+ * refuses).  Where the library allocates, up to 4 GiB of it stay
  * with the context for its next call and go with the context.  CCT_EINVAL for
  * nocc > 40; CCT_ESTATE before cct_set_fock / cct_set_eri_df.  Synchronous
  * (returns after the stream has drained). */

@@ -1582,8 +1582,10 @@ long long q_task_count(int o) { return (long long)o * (o + 1) * (o + 2) * (o + 3
 // against 24 + 24 blocks written, updated and read 24 times by one product per
 // ordered tuple (o = 6, v = 48: 196 -> 51.6 ms per evaluation).
 constexpr int kQoLaunches = 14;
-// (Q) memory that may stay with a context between calls.
+// (Q) memory that may stay with a context between calls, and what a call may
+// take for more tasks at a time where the documented need is less.
 constexpr size_t kQKeep = (size_t)4 << 30;
+constexpr size_t kQSmall = (size_t)128 << 20;
 // Position of (q <= r) among the o(o+1)/2 such pairs; qo_pair(o, o, o) is their number.
 long long qo_pair(long long o, long long q, long long r) { return q * o - q * (q - 1) / 2 + (r - q); }
 struct QoOperands {
@@ -1805,11 +1807,11 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
       return CCT_ENOMEM;
     }
   }
+  // what a call may take, without the planner's scratch
+  const long long full_n = n4 + v4 + (long long)o * v3 + o2 * o * v + o2 * v2 + o2 * v4 + 2 * o2 * o2 * v2 + o2 * o * v3 +
+                           (even ? 27 * v4 + 48 * v4p : 50 * v4) + 24 * v2 + ntask + 1 + o2;
   if (region) {
-    // what a call needs with every buffer at its full size
-    const size_t all = (size_t)(n4 + v4 + (long long)o * v3 + o2 * o * v + o2 * v2 + o2 * v4 + 2 * o2 * o2 * v2 +
-                                o2 * o * v3 + (even ? 27 * v4 + 48 * v4p : 50 * v4) + 24 * v2 + ntask + 1 + arena_n +
-                                o2) * 8;
+    const size_t all = (size_t)(full_n + arena_n) * 8;
     if (all > region_bytes) {  // nothing has been launched yet
       ctx->err = "energy_q: this system needs " + std::to_string(all >> 20) + " MiB of device scratch, the " +
                  "fixed scratch region holds " + std::to_string(region_bytes >> 20) + " MiB";
@@ -1829,38 +1831,41 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
   const bool use_ws = ctx->ws.available() / 8 >= (size_t)(std::max(v4, o2 * o2 * v2) + 65536);
   const long long other_n = (use_ws ? 0 : up(arena_n)) + up(n4) + up(v4) + up(o * v3) + up(o2 * o * v) + up(o2 * v2) + up(npair * v4) +
                             2 * up(o2 * o2 * v2) + up(o2 * o * v3) + up(ntask + 1) + up(o2);
+  // Tasks whose accumulators are held at once: as many as the documented need
+  // has room for (the smallest systems may take kQSmall), and half of them again
+  // for as long as the memory is refused.
+  const long long room_n = std::max(full_n + (use_ws ? 0 : arena_n), (long long)(kQSmall / 8));
   long long ntb = std::min<long long>(ntask, 4096);
-  if (region) {
-    ntb = std::min(ntb, ((long long)(region_bytes / 8) - other_n - fixed_n) / per_task);
-  } else {
+  ntb = std::min(ntb, ((region ? (long long)(region_bytes / 8) : room_n) - other_n - fixed_n) / per_task);
+  ntb = std::max<long long>(ntb, 1);
+  if (!region && !ctx->alloc_fn) {
     // Memory that stays with the context from call to call when it is at most
     // kQKeep (allocated and freed per call it costs more than the products of a
     // small system once the device has no cleared memory at hand: o = 4, v = 20
-    // 1.5 ms per call at first, 6 to 12 ms after some thousand calls); a larger
-    // system takes room for at most the tasks of the documented need.
-    const long long keep_n = (long long)(kQKeep / 8);
-    const long long fit = (keep_n - other_n - fixed_n) / per_task;
-    if (!ctx->alloc_fn && fit >= std::min<long long>(ntb, 16)) {
+    // 1.5 ms per call at first, 6 to 12 ms after some thousand calls).
+    const long long fit = ((long long)(kQKeep / 8) - other_n - fixed_n) / per_task;
+    if (fit >= std::min<long long>(ntb, 16)) {
       ntb = std::min(ntb, fit);
-      const size_t bytes = (size_t)(other_n + fixed_n + ntb * per_task) * 8;
-      if (ctx->q_keep_bytes < bytes) {
+      for (;; ntb = (ntb + 1) / 2) {
+        const size_t bytes = (size_t)(other_n + fixed_n + ntb * per_task) * 8;
+        if (bytes <= ctx->q_keep_bytes) break;
         if (ctx->q_keep) {
           HIPCK(hipStreamSynchronize(s));
           dev_free(ctx, ctx->q_keep);
           ctx->q_keep = nullptr;
           ctx->q_keep_bytes = 0;
         }
-        RCK(dev_alloc(ctx, &ctx->q_keep, bytes));
-        ctx->q_keep_bytes = bytes;
+        const int rc = dev_alloc(ctx, &ctx->q_keep, bytes);
+        if (rc == CCT_OK) {
+          ctx->q_keep_bytes = bytes;
+          break;
+        }
+        if (ntb == 1) return rc;
       }
       region = (char*)ctx->q_keep;
       region_bytes = ctx->q_keep_bytes;
-    } else {
-      ntb = std::min(ntb, ((even ? 27 * v4 + 48 * v4p : 50 * v4) - fixed_n) / per_task);
     }
   }
-  ntb = std::max<long long>(ntb, 1);
-  const long long scratch_n = fixed_n - 32 + ntb * per_task;  // the last 32: its end rounded up
   QMem mem(ctx, region, region_bytes);
   double *Vb, *VVVV, *VVVO, *VOOO, *VVOO, *Wv, *g, *Wo, *T3u, *et, *scratch;
   int2* slots;
@@ -1873,7 +1878,6 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
   RCK(mem.get(&g, o2 * o2 * v2));
   RCK(mem.get(&Wo, o2 * o2 * v2));
   RCK(mem.get(&T3u, o2 * o * v3));
-  RCK(mem.get(&scratch, scratch_n));
   RCK(mem.get(&et, ntask + 1));
   RCK(mem.get(&slots, o2));
   Arena own;
@@ -1884,6 +1888,12 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
     own.init((char*)ar, (size_t)arena_n * 8);
     qa = &own;
   }
+  for (;; ntb = (ntb + 1) / 2) {
+    const int rc = mem.get(&scratch, fixed_n - 32 + ntb * per_task);  // the last 32: its end rounded up
+    if (rc == CCT_OK) break;
+    if (ntb == 1) return rc;
+  }
+  const long long scratch_n = fixed_n - 32 + ntb * per_task;
   if (!mem.fits()) { ctx->err = "energy_q: scratch plan"; return CCT_EDEVICE; }
   const Prec F = Prec::F64;
 

@@ -106,3 +106,82 @@ def test_slab_panel_narrows_when_memory_is_short():
     with rest_of_card(400 << 20):
         got = _slab_residual(inputs, o, v, naux, count)
     assert np.array_equal(got, want)
+
+
+def _q_bound(o, v):
+    """Bytes that cct_energy_q may take, as include/cct.h has it."""
+    per = 28 * v ** 4 + 48 * 4096 * ((v + 7) // 8) ** 4 if v % 2 == 0 and o <= 16 else 52 * v ** 4
+    return max(8 * ((o + v) ** 4 + o ** 2 * v ** 4 + o ** 3 * v ** 3 + 2 * o ** 4 * v ** 2 + per), 128 << 20)
+
+
+@pytest.mark.parametrize("o,v", [(10, 24), (8, 32), (5, 33), (17, 6)])
+def test_q_takes_no_more_than_documented(o, v):
+    say(f"[memory limits] (Q) o={o} v={v}, bound {_q_bound(o, v) / 1e6:.0f} MB")
+    with _engine(o, v, 7) as eng:
+        before = free_bytes()
+        e = eng.energy_q()
+        kept = before - free_bytes()
+        say(f"  {kept / 1e6:.0f} MB kept")
+        assert kept <= _q_bound(o, v) + (16 << 20)
+        assert eng.energy_q() == e
+
+
+def test_q_runs_where_little_more_than_its_need_is_free():
+    o, v = 10, 24
+    say(f"[memory limits] (Q) o={o} v={v} on a nearly full card")
+    with _engine(o, v, 7) as eng:
+        with rest_of_card(_q_bound(o, v) + (600 << 20)):
+            e, tasks = eng.energy_q(tasks=True)
+    with _engine(o, v, 7) as eng:
+        e2, tasks2 = eng.energy_q(tasks=True)
+    assert e == e2 and np.array_equal(tasks, tasks2)
+
+
+class LimitedAllocator:
+    """The caller's allocator over hipMalloc: refuses above `limit` bytes in all."""
+
+    def __init__(self):
+        self.hip, self.live, self.limit, self.most = _hip(), {}, None, 0
+
+    def alloc(self, nbytes):
+        if self.limit is not None and sum(self.live.values()) + nbytes > self.limit:
+            return None
+        p = C.c_void_p()
+        if self.hip.hipMalloc(C.byref(p), nbytes) != 0:
+            return None
+        self.live[p.value] = nbytes
+        self.most = max(self.most, sum(self.live.values()))
+        return p.value
+
+    def free(self, ptr):
+        del self.live[ptr]
+        self.hip.hipFree(C.c_void_p(ptr))
+
+    def pair(self):
+        return self.alloc, self.free
+
+
+@pytest.mark.parametrize("o,v", [(6, 20), (5, 13)])
+def test_q_takes_fewer_tasks_at_a_time_where_memory_is_refused(o, v):
+    say(f"[memory limits] (Q) o={o} v={v} under an allocator's limit")
+    al = LimitedAllocator()
+    with _engine(o, v, 9, allocator=al.pair()) as eng:
+        own = sum(al.live.values())
+        want = eng.energy_q(tasks=True)
+        full = al.most - own
+        least = None
+        for part in (0.9, 0.7, 0.5, 0.3, 0.1, 0.02):
+            al.limit = own + int(part * full)
+            try:
+                e, tasks = eng.energy_q(tasks=True)
+            except binding.CCTError as err:
+                assert err.code == binding.CCT_ENOMEM
+                assert sum(al.live.values()) == own
+                continue
+            assert e == want[0] and np.array_equal(tasks, want[1])
+            least = part
+        say(f"  {full / 1e6:.1f} MB by itself, down to {least} of it")
+        assert least is not None and least <= 0.7
+        al.limit = None
+        assert eng.energy_q(tasks=True)[0] == want[0]
+    assert not al.live
