@@ -172,9 +172,10 @@ int cct_solve(cct_ctx* ctx, int max_iter, double tol, double* e_corr, int* iters
  * (about 110 GB at o=10, v=90); 128 MiB where that is more: CCT_ENOMEM if that
  * is not free (checked before allocating when the library allocates; a caller's
  * allocator is asked block by block, for fewer tasks at a time where it
- * refuses).  Where the library allocates, up to 4 GiB of it stay
- * with the context for its next call and go with the context.  CCT_EINVAL for
- * nocc > 40; CCT_ESTATE before cct_set_fock / cct_set_eri_df.  Synchronous
+ * refuses).  Where the library allocates, it keeps a block of up to 4 GiB
+ * per GPU for the next call of any context; it goes with the context that used
+ * it last, or to an allocation of the library that would be refused without it.
+ * CCT_EINVAL for nocc > 40; CCT_ESTATE before cct_set_fock / cct_set_eri_df.  Synchronous
  * (returns after the stream has drained). */
 int cct_energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, int64_t cap);
 /* cct_energy_q without any device allocation, for callers that cannot

@@ -80,8 +80,6 @@ struct cct_ctx {
   bool have_f = false, have_B = false, have_res = false;
 
   std::vector<void*> owned;
-  void* q_keep = nullptr;  // memory of cct_energy_q kept between calls
-  size_t q_keep_bytes = 0;
   // inputs
   double *f = nullptr, *B = nullptr, *eps = nullptr, *fov = nullptr;
   double *vbare_c = nullptr;  // 2 v^{ij}_{ab} - v^{ij}_{ba} (bare), [i][j][a][b]
@@ -1582,8 +1580,8 @@ long long q_task_count(int o) { return (long long)o * (o + 1) * (o + 2) * (o + 3
 // against 24 + 24 blocks written, updated and read 24 times by one product per
 // ordered tuple (o = 6, v = 48: 196 -> 51.6 ms per evaluation).
 constexpr int kQoLaunches = 14;
-// (Q) memory that may stay with a context between calls, and what a call may
-// take for more tasks at a time where the documented need is less.
+// (Q) memory that may be kept between calls, and what a call may take for more
+// tasks at a time where the documented need is less.
 constexpr size_t kQKeep = (size_t)4 << 30;
 constexpr size_t kQSmall = (size_t)128 << 20;
 // Position of (q <= r) among the o(o+1)/2 such pairs; qo_pair(o, o, o) is their number.
@@ -1799,8 +1797,7 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
                          o2 * o * v3 + 50 * v4 + (even ? 48 * v4p : 0) + ntask + 1 + arena_n;
   if (!ctx->alloc_fn && !region) {
     size_t fr = 0, tot = 0;
-    HIPCK(hipMemGetInfo(&fr, &tot));
-    fr += ctx->q_keep_bytes;
+    HIPCK(device_mem_info(&fr, &tot));
     if ((double)need * 8.0 + 256e6 > (double)fr) {
       ctx->err = "energy_q: needs " + std::to_string(need * 8.0 / 1e9) + " GB of device memory, " +
                  std::to_string(fr / 1e9) + " GB free";
@@ -1838,32 +1835,36 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
   long long ntb = std::min<long long>(ntask, 4096);
   ntb = std::min(ntb, ((region ? (long long)(region_bytes / 8) : room_n) - other_n - fixed_n) / per_task);
   ntb = std::max<long long>(ntb, 1);
+  struct KeptUse {
+    cct_ctx* c;
+    bool on = false;
+    ~KeptUse() {
+      if (!on) return;
+      (void)hipStreamSynchronize(c->s);  // the next call may come from another stream
+      kept_give(c->dev);
+    }
+  } kept{ctx};
   if (!region && !ctx->alloc_fn) {
-    // Memory that stays with the context from call to call when it is at most
-    // kQKeep (allocated and freed per call it costs more than the products of a
-    // small system once the device has no cleared memory at hand: o = 4, v = 20
-    // 1.5 ms per call at first, 6 to 12 ms after some thousand calls).
+    // The kept block where at most kQKeep is wanted (allocated and freed per call
+    // it costs more than the products of a small system once the device has no
+    // cleared memory at hand: o = 4, v = 20 1.5 ms per call at first, 6 to 12 ms
+    // after some thousand calls), unless another call has it.
     const long long fit = ((long long)(kQKeep / 8) - other_n - fixed_n) / per_task;
     if (fit >= std::min<long long>(ntb, 16)) {
-      ntb = std::min(ntb, fit);
-      for (;; ntb = (ntb + 1) / 2) {
-        const size_t bytes = (size_t)(other_n + fixed_n + ntb * per_task) * 8;
-        if (bytes <= ctx->q_keep_bytes) break;
-        if (ctx->q_keep) {
-          HIPCK(hipStreamSynchronize(s));
-          dev_free(ctx, ctx->q_keep);
-          ctx->q_keep = nullptr;
-          ctx->q_keep_bytes = 0;
+      for (long long nt = std::min(ntb, fit);; nt = (nt + 1) / 2) {
+        void* p = nullptr;
+        size_t got = 0;
+        const size_t bytes = (size_t)(other_n + fixed_n + nt * per_task) * 8;
+        const hipError_t e = kept_take(ctx->dev, ctx, bytes, &p, &got);
+        if (e == hipSuccess) {
+          kept.on = true;
+          ntb = nt;
+          region = (char*)p;
+          region_bytes = got;
         }
-        const int rc = dev_alloc(ctx, &ctx->q_keep, bytes);
-        if (rc == CCT_OK) {
-          ctx->q_keep_bytes = bytes;
-          break;
-        }
-        if (ntb == 1) return rc;
+        if (e != hipErrorOutOfMemory) break;
+        if (nt == 1) { ctx->err = "energy_q: " + std::to_string(bytes) + " bytes refused"; return CCT_ENOMEM; }
       }
-      region = (char*)ctx->q_keep;
-      region_bytes = ctx->q_keep_bytes;
     }
   }
   QMem mem(ctx, region, region_bytes);
@@ -2139,7 +2140,7 @@ int energy_q_abc(cct_ctx* ctx, int nb, const int64_t* tasks, long long ntasks, d
   if ((double)ctx->ws.available() < (double)bytes) {
     if (!ctx->alloc_fn) {
       size_t fr = 0, tot = 0;
-      HIPCK(hipMemGetInfo(&fr, &tot));
+      HIPCK(device_mem_info(&fr, &tot));
       if ((double)bytes + 256e6 > (double)fr) {
         ctx->err = "energy_q_abc: needs " + std::to_string(peak_gb) + " GB; the context workspace holds " +
                    std::to_string(ctx->ws.available() / 1e9) + " GB and the device has " + std::to_string(fr / 1e9) +
@@ -2963,7 +2964,7 @@ void cct_destroy(cct_ctx* ctx) {
   (void)hipStreamSynchronize(ctx->s);  // nothing in flight may touch what is freed below
   for (void* p : ctx->owned) dev_free(ctx, p);
   dev_free(ctx, ctx->wsbuf);
-  dev_free(ctx, ctx->q_keep);
+  kept_drop(ctx);
   for (int i = 0; i <= PH_N; ++i)
     if (ctx->ev[i]) (void)hipEventDestroy(ctx->ev[i]);
   for (hipEvent_t e : ctx->lad_ev) (void)hipEventDestroy(e);
@@ -3047,7 +3048,7 @@ int cct_create(int nocc, int nvir, int naux, cct_precision prec, const char* opt
   const long long need_ws =
       std::max(6 * (long long)o * v3 + 2 * o2v3 * o, lad_w + ntri_l * lad_blk) + (1 << 22);
   size_t free_b = 0, total_b = 0;
-  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+  if (device_mem_info(&free_b, &total_b) != hipSuccess) {
     ctx->err = "hipMemGetInfo failed (no HIP device?)";
     *out = nullptr;
     delete ctx;

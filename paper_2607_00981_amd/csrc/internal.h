@@ -15,6 +15,16 @@ namespace cct {
 // hipMalloc on the current device.  nullptr: refused (or, from the caller's,
 // not aligned to 256 bytes: *why says which); no error is left pending.
 void* device_alloc(size_t bytes, cct_alloc_fn alloc, cct_free_fn free_fn, void* user, const char** why = nullptr);
+// hipMemGetInfo of the current device, its idle kept block counted as free
+// (device_alloc gives it back before it refuses).
+hipError_t device_mem_info(size_t* free_b, size_t* total_b);
+// The block of `dev` (the current device) that is kept between calls, *got >=
+// bytes: hipErrorNotReady while another call has it, hipErrorOutOfMemory if it
+// does not fit.  kept_give: no work on it is in flight any more.  kept_drop: the
+// user is destroyed; blocks that it used last are freed.
+hipError_t kept_take(int dev, const void* user, size_t bytes, void** p, size_t* got);
+void kept_give(int dev);
+void kept_drop(const void* user);
 
 // Synchronous device-to-host copy on stream s (of device dev), through a pool
 // of pinned buffers and a few threads where dst is pageable and large.  Every

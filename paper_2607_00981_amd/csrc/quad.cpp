@@ -244,7 +244,7 @@ int cct_quad_create(int nocc, int nvir, cct_precision prec, const char* opts_jso
   }
   const long long n4 = nq * q->v4;
   size_t free_b = 0, total_b = 0;
-  if (hipMemGetInfo(&free_b, &total_b) != hipSuccess) {
+  if (device_mem_info(&free_b, &total_b) != hipSuccess) {
     delete q;
     return CCT_EDEVICE;
   }

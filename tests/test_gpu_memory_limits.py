@@ -8,6 +8,7 @@ run, else the tolerance of the object's own tests)."""
 import contextlib
 import ctypes as C
 import sys
+import threading
 import time
 
 import numpy as np
@@ -185,3 +186,102 @@ def test_q_takes_fewer_tasks_at_a_time_where_memory_is_refused(o, v):
         al.limit = None
         assert eng.energy_q(tasks=True)[0] == want[0]
     assert not al.live
+
+
+def _alone(o, v, seed, f):
+    with _engine(o, v, seed) as eng:
+        return f(eng)
+
+
+def test_q_memory_is_one_block_and_goes_with_its_last_user():
+    o, v = 8, 32
+    say(f"[memory limits] (Q) o={o} v={v} on three contexts")
+    engines = [_engine(o, v, 20 + k) for k in range(3)]
+    try:
+        before = free_bytes()
+        energies = [e.energy_q() for e in engines]
+        assert before - free_bytes() <= _q_bound(o, v) + (16 << 20)
+        engines.pop(0).close()
+        assert [e.energy_q() for e in engines] == energies[1:]
+    finally:
+        for e in engines:
+            e.close()
+    for k in range(3):
+        assert _alone(o, v, 20 + k, lambda e: e.energy_q()) == energies[k]
+
+
+def test_q_memory_is_given_back_on_destroy():
+    say("[memory limits] (Q) memory after destroy")
+    _engine(8, 32, 20).close()
+    time.sleep(0.5)
+    before = free_bytes()
+    with _engine(8, 32, 20) as eng:
+        eng.energy_q()
+    for _ in range(100):
+        if before - free_bytes() <= 16 << 20:
+            break
+        time.sleep(0.05)
+    assert before - free_bytes() <= 16 << 20
+
+
+def test_virtual_tuple_order_takes_the_kept_memory():
+    """o = 10, v = 24, block 8: 1.5 GB with its margin; (Q) keeps 0.68 of what is free."""
+    o, v, block = 10, 24, 8
+    say(f"[memory limits] both orders o={o} v={v} on a nearly full card")
+    tasks = [0, 3, 14]
+    want = _alone(o, v, 7, lambda e: e.energy_q_abc(block, tasks)["e_tasks"])
+    with _engine(o, v, 7) as eng:
+        eng.energy_q()
+        with rest_of_card(1100 << 20):
+            got = eng.energy_q_abc(block, tasks)["e_tasks"]
+    assert np.array_equal(got, want)
+
+
+def test_new_objects_take_the_kept_memory():
+    say("[memory limits] a quadruples object beside kept (Q) memory")
+    with _engine(8, 32, 20) as eng:
+        eng.energy_q()
+        with rest_of_card(300 << 20):
+            with binding.Quad(4, 30):  # 35 blocks of 6.5 MB, three times: 0.7 GB
+                pass
+
+
+def test_q_after_new_amplitudes_equals_a_fresh_context():
+    o, v = 4, 20
+    say("[memory limits] (Q) twice on a context, other amplitudes")
+    rng = np.random.default_rng(3)
+    t2 = rng.normal(0, 0.05, (o, o, v, v))
+    t2 = 0.5 * (t2 + t2.transpose(1, 0, 3, 2))
+    t3p = ci.random_t3_packed(o, v, 77, 0.03)
+
+    def second(eng, first):
+        if first:
+            eng.energy_q()
+        eng.set_amplitudes(np.zeros((o, v)), t2, t3p)
+        return eng.energy_q(tasks=True)
+
+    e1, x1 = _alone(o, v, 30, lambda e: second(e, True))
+    e2, x2 = _alone(o, v, 30, lambda e: second(e, False))
+    assert e1 == e2 and np.array_equal(x1, x2)
+
+
+def test_q_on_two_threads():
+    say("[memory limits] (Q) on two contexts, a thread each")
+    sizes = [(5, 20, 40), (4, 25, 41)]
+    want = [_alone(*s, lambda e: e.energy_q(tasks=True)[1]) for s in sizes]
+    got = [[], []]
+
+    def work(k):
+        with _engine(*sizes[k]) as eng:
+            for _ in range(20):
+                got[k].append(eng.energy_q(tasks=True)[1])
+
+    ts = [threading.Thread(target=work, args=(k,)) for k in range(2)]
+    for t in ts:
+        t.start()
+    for t in ts:
+        t.join()
+    for k in range(2):
+        assert len(got[k]) == 20
+        for x in got[k]:
+            assert np.array_equal(x, want[k])
