@@ -350,7 +350,7 @@ int cct_slab_copy_r3(cct_slab* sl, int64_t first, int64_t count, double* out);
 /* Multiply-adds of the last residual: [0] ladder 3 count v^5, [1] W rebuild
  * (naux + o^2) v^4, [2] F_vv 3 count v^4, [3] W^{ab}_{dj} driver 6 count v^4,
  * [4] W^{al}_{ij} driver 6 count o v^3, [5] 0; milliseconds (with "timers"):
- * [0] T3 relabelling, [1] W rebuild, [2] ladder GEMMs, [3] F_vv, [4] drivers,
+ * [0] T3 relabelling (within [2] where T3 is relabelled in parts), [1] W rebuild, [2] ladder GEMMs, [3] F_vv, [4] drivers,
  * [5] post-processing.  Writes min(cap, 6) of each. */
 int cct_slab_get_counters(cct_slab* sl, double* macs, double* ms, int cap);
 const char* cct_slab_last_error(const cct_slab* sl);

@@ -16,6 +16,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <string>
 #include <vector>
@@ -34,6 +35,7 @@ struct cct_slab {
   hipStream_t s = nullptr;
   int dev = 0;    // the stream's device
   int panel = 0;  // rows a per W panel
+  int vblk = 0;   // FP64: blocks whose relabelled copies are held at once (0: none, see slab_pp)
   bool have_ims = false, have_t3 = false, timers = false;
   long long v3 = 0;
   // device buffers
@@ -159,37 +161,39 @@ int ladder_fmt(const cct_slab* sl) {
   return sl->prec == Prec::F32 ? OUT_F32 : (v2 % 32 == 0 ? OUT_BF16X2I : OUT_BF16X2);
 }
 
-// Relabelled copies of the slab's T3: views[term] = [t][x][(d,e)] with x the
-// free axis of that term, in the working precision.  FP64 rows are padded with
-// zeros to v2p, whole K tiles of the direct-copy kernel for every v (R3, not
-// yet in use, takes the unpadded copies); a v^2 that needs no padding keeps
-// term 2 in T3 itself.
-int build_views(cct_slab* sl) {
+// FP64 rows of v^2 are padded with zeros to v2p, whole K tiles of the
+// direct-copy kernel for every v; a v^2 that needs no padding keeps term 2 in T3
+// itself.
+int view_areas(const cct_slab* sl) { return sl->v2p > (long long)sl->v * sl->v ? 3 : 2; }
+
+// Relabelled copies of blocks [t0, t0 + nb) of the slab's T3: views[term] =
+// [t][x][(d,e)] with x the free axis of that term, in the working precision.
+int build_views(cct_slab* sl, long long t0, long long nb) {
   const int v = sl->v;
-  const long long v2 = (long long)v * v, v3 = sl->v3, nb = sl->count;
+  const long long v2 = (long long)v * v, v3 = sl->v3;
+  const double* t3 = sl->t3 + t0 * v3;
   if (lp_ok(sl)) {
     const int fmt = ladder_fmt(sl);
     char* base = (char*)sl->views;
     for (int term = 0; term < 3; ++term) {
       void* dst = base + (size_t)term * nb * v3 * 4;
       const OutSpec os{dst, fmt, nb * v3};
-      if (term == 2) SHIP(convert(sl->t3, os, nb * v3, sl->s));
-      else if (term == 1) SHIP(swap01_batched(sl->t3, os, nb, v, v, v, sl->s));
-      else SHIP(transpose_batched(sl->t3, os, nb, (int)v2, v, sl->s));
+      if (term == 2) SHIP(convert(t3, os, nb * v3, sl->s));
+      else if (term == 1) SHIP(swap01_batched(t3, os, nb, v, v, v, sl->s));
+      else SHIP(transpose_batched(t3, os, nb, (int)v2, v, sl->s));
     }
     return CCT_OK;
   }
   double* base = (double*)sl->views;
-  const long long len = nb * v * sl->v2p;
+  const long long len = (long long)sl->vblk * v * sl->v2p;
   const bool pad = sl->v2p > v2;
-  double* tmp = pad ? sl->r3 : base;
-  SHIP(transpose_batched(sl->t3, OutSpec{tmp, OUT_F64, 0}, nb, (int)v2, v, sl->s));
+  double* tmp = base + 2 * len;  // unpadded, before term 2 takes the place
+  SHIP(transpose_batched(t3, OutSpec{pad ? tmp : base, OUT_F64, 0}, nb, (int)v2, v, sl->s));
   if (pad) SHIP(copy_pad_rows(tmp, nb * v, v2, OutSpec{base, OUT_F64, 0}, sl->v2p, sl->s));
-  tmp = pad ? sl->r3 : base + len;
-  SHIP(swap01_batched(sl->t3, OutSpec{tmp, OUT_F64, 0}, nb, v, v, v, sl->s));
+  SHIP(swap01_batched(t3, OutSpec{pad ? tmp : base + len, OUT_F64, 0}, nb, v, v, v, sl->s));
   if (pad) {
     SHIP(copy_pad_rows(tmp, nb * v, v2, OutSpec{base + len, OUT_F64, 0}, sl->v2p, sl->s));
-    SHIP(copy_pad_rows(sl->t3, nb * v, v2, OutSpec{base + 2 * len, OUT_F64, 0}, sl->v2p, sl->s));
+    SHIP(copy_pad_rows(t3, nb * v, v2, OutSpec{base + 2 * len, OUT_F64, 0}, sl->v2p, sl->s));
   }
   return CCT_OK;
 }
@@ -269,7 +273,10 @@ int build_panel(cct_slab* sl, int a0, int na) {
   return CCT_OK;
 }
 
-// Ladder over all panels: R[t] += sum_de W^{..}_{de} t^{..} (three relabelled terms).
+// Ladder over all panels: R[t] += sum_de W^{..}_{de} t^{..} (three relabelled
+// terms).  FP64: from the relabelled copies of vblk blocks at a time, built once
+// where all blocks fit and for each panel anew where not; with room for none
+// the generally strided kernel reads the stored blocks in place.
 int slab_pp(cct_slab* sl) {
   const int v = sl->v;
   const long long v2 = (long long)v * v, v3 = sl->v3, nb = sl->count;
@@ -277,8 +284,9 @@ int slab_pp(cct_slab* sl) {
   ladder_maps(v, cm, cn);
   const bool lp = lp_ok(sl);
   mark(sl, 0);
-  RCK_(build_views(sl));
-  SHIP(fill(sl->r3, 0.0, nb * v3, sl->s));  // after build_views, which stages in it
+  const long long vb = lp || sl->vblk == 0 ? nb : sl->vblk;
+  const bool views = lp || sl->vblk > 0, once = vb >= nb;
+  if (views && once) RCK_(build_views(sl, 0, nb));
   mark(sl, 1);
   float t_rebuild = 0.f, t_ladder = 0.f;
   hipEvent_t e0 = nullptr, e1 = nullptr, e2 = nullptr;
@@ -294,29 +302,45 @@ int slab_pp(cct_slab* sl) {
     RCK_(build_panel(sl, a0, na));
     if (lp) SHIP(convert(sl->Wp, OutSpec{sl->Wl, ladder_fmt(sl), prow * v2}, prow * v2, sl->s));
     if (sl->timers) (void)hipEventRecord(e1, sl->s);
-    for (int term = 0; term < 3; ++term) {
-      // panel rows (y,z) = (a0 + r / v, r % v): offset of the output by a0 along y
-      const long long coff = (cn[term].inner == 0 ? (long long)a0 * v * cn[term].s_lo : (long long)a0 * cn[term].s_hi);
-      if (lp) {
-        NtLpArgs g{};
-        g.M = (int)(nb * v); g.N = (int)prow; g.K = (int)v2; g.batch = 1;
-        g.A = (const char*)sl->views + (size_t)term * nb * v3 * 4; g.lda = v2; g.a_plane = nb * v3;
-        g.B = sl->Wl; g.ldb = v2; g.b_plane = prow * v2;
-        g.C = sl->r3 + coff; g.cm = cm[term]; g.cn = cn[term];
-        g.alpha = 1.0; g.beta = 1.0;
-        g.a_len = nb * v3; g.b_len = prow * v2; g.c_len = nb * v3 - coff;
-        g.il = ladder_fmt(sl) == OUT_BF16X2I;
-        SHIP(gemm_nt_lp(g, sl->prec, sl->s));
-      } else {
-        const long long kp = sl->v2p, len = nb * v * kp;
-        NtArgs g{};
-        g.M = (int)(nb * v); g.N = (int)prow; g.K = (int)kp; g.batch = 1;
-        g.A = term == 2 && kp == v2 ? sl->t3 : (const double*)sl->views + term * len; g.lda = kp;
-        g.B = sl->Wp; g.ldb = kp;
-        g.C = sl->r3 + coff; g.cm = cm[term]; g.cn = cn[term];
-        g.alpha = 1.0; g.beta = 1.0;
-        g.a_len = len; g.b_len = prow * kp; g.c_len = nb * v3 - coff;
-        SHIP(gemm_nt(g, Prec::F64, sl->s));
+    for (long long t0 = 0; t0 < nb; t0 += vb) {
+      const long long nt = std::min(vb, nb - t0);  // blocks of this chunk
+      if (views && !once) RCK_(build_views(sl, t0, nt));
+      for (int term = 0; term < 3; ++term) {
+        // panel rows (y,z) = (a0 + r / v, r % v): offset of the output by a0 along y
+        const long long coff = t0 * v3 + (cn[term].inner == 0 ? (long long)a0 * v * cn[term].s_lo : (long long)a0 * cn[term].s_hi);
+        if (lp) {
+          NtLpArgs g{};
+          g.M = (int)(nb * v); g.N = (int)prow; g.K = (int)v2; g.batch = 1;
+          g.A = (const char*)sl->views + (size_t)term * nb * v3 * 4; g.lda = v2; g.a_plane = nb * v3;
+          g.B = sl->Wl; g.ldb = v2; g.b_plane = prow * v2;
+          g.C = sl->r3 + coff; g.cm = cm[term]; g.cn = cn[term];
+          g.alpha = 1.0; g.beta = 1.0;
+          g.a_len = nb * v3; g.b_len = prow * v2; g.c_len = nb * v3 - coff;
+          g.il = ladder_fmt(sl) == OUT_BF16X2I;
+          SHIP(gemm_nt_lp(g, sl->prec, sl->s));
+        } else if (views) {
+          const long long kp = sl->v2p, len = vb * v * kp;
+          const bool stored = term == 2 && kp == v2;
+          NtArgs g{};
+          g.M = (int)(nt * v); g.N = (int)prow; g.K = (int)kp; g.batch = 1;
+          g.A = stored ? sl->t3 + t0 * v3 : (const double*)sl->views + term * len; g.lda = kp;
+          g.B = sl->Wp; g.ldb = kp;
+          g.C = sl->r3 + coff; g.cm = cm[term]; g.cn = cn[term];
+          g.alpha = 1.0; g.beta = 1.0;
+          g.a_len = nt * v * kp; g.b_len = prow * kp; g.c_len = nb * v3 - coff;
+          SHIP(gemm_nt(g, Prec::F64, sl->s));
+        } else {
+          const Idx2 am[3] = {idx2(v, v3, 1), idx2(v, v3, v), idx2(v, v3, v2)};
+          const Idx2 ak[3] = {idx1(v), idx2(v, v2, 1), idx1(1)};
+          GemmArgs g{};
+          g.M = (int)(nb * v); g.N = (int)prow; g.K = (int)v2; g.batch = 1;
+          g.A = sl->t3; g.am = am[term]; g.ak = ak[term];
+          g.B = sl->Wp; g.bk = idx1(1); g.bn = idx1(sl->v2p);
+          g.C = sl->r3 + coff; g.cm = cm[term]; g.cn = cn[term];
+          g.alpha = 1.0; g.beta = 1.0;
+          g.a_len = nb * v3; g.b_len = prow * sl->v2p; g.c_len = nb * v3 - coff;
+          SHIP(gemm(g, Prec::F64, sl->s));
+        }
       }
     }
     if (sl->timers) {
@@ -440,6 +464,67 @@ std::vector<SegItem> driver_items(const cct_slab* sl) {
   return items;
 }
 
+// The two buffers whose size is a choice, after all others.
+// W panel: the rows asked for; else 8, or as many more as 1 GiB holds (wide
+// panels fill the chip and rebuild W in fewer launches: count 24, o = 12, v = 96
+// split-BF16 ladder and rebuild 8.7 -> 5.1 ms).
+// FP64 views: where padded rows ask for three copies of T3, at most 4 GiB of them
+// (or, for even v, the two unpadded copies' worth), a chunk of blocks at a time.
+// Where the memory is refused: 8 rows, then a sixteenth of the views, the views
+// of one block, and none.
+int panel_and_views(cct_slab* sl) {
+  const int v = sl->v;
+  const long long v2 = (long long)v * v, nb = sl->count;
+  const bool lp = lp_ok(sl), given = sl->panel > 0;
+  const long long gib = 1LL << 30;
+  const long long row_bytes = v * (lp ? v2 * 12 : sl->v2p * 8);  // FP64 panel and its low-precision copy
+  const int narrow = given ? sl->panel : std::min(v, 8);
+  const int wide = given ? sl->panel : (int)std::min<long long>(v, std::max<long long>(8, gib / row_bytes));
+  // blocks per chunk, at most m: those that leave the fewest rounds of the
+  // ladder's 128 x 192 tiles over 256 compute units (v = 151, 60 blocks: 511 ms in
+  // two chunks of 30, rounds 84 % full; 451 so chosen; 437 all at once)
+  auto chunk = [&](long long m) {
+    const long long tn = (std::min(wide, v) * (long long)v + 191) / 192;
+    auto rounds = [&](long long b) { return ((b * v + 127) / 128 * tn + 255) / 256; };
+    long long best = std::min(m, nb), least = LLONG_MAX;
+    for (long long b = best; best < nb && b >= std::max(1LL, m / 4); --b) {
+      const long long r = nb / b * rounds(b) + rounds(nb % b);
+      if (r < least) { least = r; best = b; }
+    }
+    return best;
+  };
+  const long long view_bytes = view_areas(sl) * v * sl->v2p * 8;  // of one block
+  long long most = nb;
+  if (view_areas(sl) == 3) most = std::max(4 * gib, v % 2 ? 0 : 2 * nb * sl->v3 * 8) / view_bytes;
+  most = lp ? 0 : chunk(std::min(nb, std::max(most, 1LL)));
+  // the next call's own scratch (cct_slab_set_intermediates) must find room beside them
+  void* spare = nullptr;
+  RCK_(sdev_alloc(sl, &spare, (size_t)sl->naux * sl->o * v * 8));
+  const std::pair<int, long long> plans[5] = {
+      {wide, most}, {narrow, most}, {narrow, chunk(most / 16)}, {narrow, std::min(most, 1LL)}, {narrow, 0}};
+  int rc = CCT_ENOMEM;
+  for (int i = 0; i < 5 && rc == CCT_ENOMEM; ++i) {
+    if (i > 0 && plans[i] == plans[i - 1]) continue;
+    void *wp = nullptr, *wl = nullptr, *vw = nullptr;
+    sl->panel = plans[i].first;
+    sl->vblk = (int)plans[i].second;
+    rc = sdev_alloc(sl, &wp, (size_t)sl->panel * v * (lp ? v2 : sl->v2p) * 8);
+    if (rc == CCT_OK && lp) rc = sdev_alloc(sl, &wl, (size_t)sl->panel * sl->v3 * 4);
+    if (rc == CCT_OK && sl->vblk > 0) rc = sdev_alloc(sl, &vw, (size_t)(sl->vblk * view_bytes));
+    for (void* p : {wp, wl, vw}) {
+      if (rc == CCT_OK && p) sl->owned.push_back(p);
+      else sdev_free(sl, p);
+    }
+    if (rc == CCT_OK) {
+      sl->Wp = (double*)wp;
+      sl->Wl = wl;
+      if (!lp) sl->views = vw;
+    }
+  }
+  sdev_free(sl, spare);
+  return rc;
+}
+
 }  // namespace
 
 extern "C" {
@@ -501,7 +586,6 @@ int cct_slab_create(int nocc, int nvir, int naux, int first, int count, cct_prec
   const bool lp = lp_ok(sl);
   sl->v2p = (v2 + 15) / 16 * 16;
   sl->op = (o + 1) / 2 * 2;
-  const size_t view_bytes = lp ? (size_t)3 * nb * v3 * 4 : (size_t)(sl->v2p > v2 ? 3 : 2) * nb * v * sl->v2p * 8;
   if (rc == CCT_OK) rc = sallocd(sl, &sl->BvvT, v2 * naux);
   if (rc == CCT_OK) rc = sallocd(sl, &sl->t2T, v2 * o2);
   if (rc == CCT_OK) rc = sallocd(sl, &sl->VoT, v2 * o2);
@@ -512,7 +596,7 @@ int cct_slab_create(int nocc, int nvir, int naux, int first, int count, cct_prec
   if (rc == CCT_OK) rc = sallocd(sl, &sl->drv, 6 * nb);
   if (rc == CCT_OK) rc = sallocd(sl, &sl->t3, nb * v3);
   if (rc == CCT_OK) rc = sallocd(sl, &sl->r3, nb * v3);
-  if (rc == CCT_OK) rc = salloc(sl, &sl->views, view_bytes);
+  if (rc == CCT_OK && lp) rc = salloc(sl, &sl->views, (size_t)3 * nb * v3 * 4);
   if (lp) {
     const int w = sl->prec == Prec::F32 ? 4 : 8;
     sl->ka = ((long long)naux + w - 1) / w * w;
@@ -521,32 +605,11 @@ int cct_slab_create(int nocc, int nvir, int naux, int first, int count, cct_prec
     if (rc == CCT_OK) rc = salloc(sl, &sl->t2L, (size_t)(v2 * sl->ko) * 4);
     if (rc == CCT_OK) rc = salloc(sl, &sl->VoL, (size_t)(v2 * sl->ko) * 4);
   }
-  // W panel: the rows asked for; else 8, or as many more as 1 GiB holds (wide
-  // panels fill the chip and rebuild W in fewer launches: count 24, o = 12, v =
-  // 96 split-BF16 ladder and rebuild 8.7 -> 5.1 ms), 8 again when that is not to be had
-  const size_t row_bytes = (size_t)v * (lp ? v2 * 12 : sl->v2p * 8);
-  const bool given = sl->panel > 0;
-  if (!given) sl->panel = std::min<int>(v, std::max<long long>(8, (long long)(((size_t)1 << 30) / row_bytes)));
-  while (rc == CCT_OK) {
-    void *wp = nullptr, *wl = nullptr;
-    rc = sdev_alloc(sl, &wp, (size_t)sl->panel * v * (lp ? v2 : sl->v2p) * 8);
-    if (rc == CCT_OK && lp) rc = sdev_alloc(sl, &wl, (size_t)sl->panel * v3 * 4);
-    if (rc == CCT_OK) {
-      sl->owned.push_back(wp);
-      if (wl) sl->owned.push_back(wl);
-      sl->Wp = (double*)wp;
-      sl->Wl = wl;
-      break;
-    }
-    sdev_free(sl, wp);
-    if (given || sl->panel <= 8) break;
-    sl->panel = std::min(v, 8);
-    rc = CCT_OK;
-  }
   if (rc == CCT_OK) rc = sallocd(sl, &sl->eps0, n);
   if (rc == CCT_OK) rc = sallocd(sl, &sl->tri, nb);
   sl->red_n = 2048 + 64LL * nb;
   if (rc == CCT_OK) rc = sallocd(sl, &sl->red, sl->red_n);
+  if (rc == CCT_OK) rc = panel_and_views(sl);
   if (rc == CCT_OK && hipMemcpy(sl->tri, sl->tri_h.data(), sizeof(int4) * nb, hipMemcpyHostToDevice) != hipSuccess)
     rc = CCT_EDEVICE;
   if (rc == CCT_OK) {
@@ -653,8 +716,8 @@ int cct_slab_residual(cct_slab* sl, unsigned term_mask, double* r3slab, double* 
   }
   const long long v3 = sl->v3, nb = sl->count;
   for (double& m : sl->ms) m = 0.0;
+  SHIP(fill(sl->r3, 0.0, nb * v3, sl->s));
   if (term_mask & CCT_TERM_PP) RCK_(slab_pp(sl));
-  else SHIP(fill(sl->r3, 0.0, nb * v3, sl->s));
   mark(sl, 2);
   if (term_mask & CCT_TERM_F1) RCK_(slab_f1(sl));
   mark(sl, 3);

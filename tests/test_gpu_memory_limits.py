@@ -285,3 +285,40 @@ def test_q_on_two_threads():
         assert len(got[k]) == 20
         for x in got[k]:
             assert np.array_equal(x, want[k])
+
+
+def _slab_bytes_unrelabelled(o, v, naux, count):
+    """An FP64 slab's buffers with T3 read in place and eight rows of W, exactly
+    (rows of W padded to 16, o to even), and 256 kB for the small ones."""
+    v2, op = v * v, (o + 1) // 2 * 2
+    rows = min(v, 8) * v * ((v2 + 15) // 16 * 16)
+    n = v2 * naux + 3 * v2 * o * o + v2 + o * v ** 3 + v * o * o * op + 2 * count * v ** 3 + rows
+    return 8 * (n + 64 * count) + 6 * count * 208 + (256 << 10)
+
+
+# v^2 odd, even without whole K tiles, and of whole K tiles
+@pytest.mark.parametrize("o,v,count", [(5, 33, 35), (5, 30, 30), (4, 32, 20), (1, 1, 1), (3, 47, 9)])
+def test_slab_relabels_in_parts_where_memory_is_short(o, v, count):
+    say(f"[memory limits] FP64 slab o={o} v={v} count={count} under an allocator's limit")
+    naux = 2 * v
+    inputs = _slab_inputs(o, v, naux, count, 11)
+    want = _slab_residual(inputs, o, v, naux, count)
+    least = _slab_bytes_unrelabelled(o, v, naux, count)
+    block = 3 * v * ((v * v + 15) // 16 * 16) * 8
+    full = LimitedAllocator()
+    _slab_residual(inputs, o, v, naux, count, allocator=full.pair())
+    for limit in (full.most, full.most - 1, least + count // 2 * block, least + 2 * block, least + block, least):
+        al = LimitedAllocator()
+        al.limit = limit
+        got = _slab_residual(inputs, o, v, naux, count, allocator=al.pair())
+        assert np.abs(got - want).max() <= 1e-11 * max(float(np.abs(want).max()), 1e-300)
+        assert not al.live
+        say(f"  {limit / 1e6:.2f} MB allowed, {al.most / 1e6:.2f} taken")
+
+
+def test_slab_copies_of_t3_are_bounded():
+    o, v, count = 9, 111, 165
+    say(f"[memory limits] FP64 slab o={o} v={v} count={count}: 5.3 GB of padded copies")
+    al = LimitedAllocator()
+    with binding.Slab(o, v, 20, 0, count, allocator=al.pair()):
+        assert al.most <= _slab_bytes_unrelabelled(o, v, 20, count) + (5 << 30)
