@@ -1607,15 +1607,15 @@ bool qo_plan(int o, int v, const std::vector<int4>& tasks, const QoOperands& w, 
     return m == 3 || m == 12 ? 0 : (m == 5 || m == 10 ? 1 : 2);
   };
   bool ok = true;
-  auto seg = [&](SegItem& it, const double* a, const double* abase, long long alen, long long areach, int rs0, int rs1,
-                 int rs2, const double* b, const double* bbase, long long blen, long long ldb, int K, long long N,
+  auto seg = [&](const QoLaunch& l, SegItem& it, const double* a, const double* abase, long long alen, long long areach,
+                 int rs0, int rs1, int rs2, const double* b, const double* bbase, long long blen, long long ldb,
                  double coef) {
-    ok = ok && it.nseg < SEG_MAX && a >= abase && (a - abase) + areach + K <= alen && b >= bbase &&
-         (b - bbase) + (K - 1) * ldb + N <= blen;
+    ok = ok && it.nseg < SEG_MAX && a >= abase && b >= bbase;
     if (!ok) return;
     SegOp& sg = it.seg[it.nseg++];
     sg.a = a; sg.b = b; sg.ldb = ldb; sg.coef = coef;
     sg.rs0 = rs0; sg.rs1 = rs1; sg.rs2 = rs2;
+    ok = seg_fits(l.g, sg, areach, alen - (a - abase), blen - (b - bbase));
   };
   const long long n_vvvo = o * v3, n_t3 = o2 * o * v3, n_t2 = o2 * v2, n_wo = o2 * o2 * v2;
   // stabiliser of a task on the axes, and whether the ordered pair (p, q) is
@@ -1669,7 +1669,7 @@ bool qo_plan(int o, int v, const std::vector<int4>& tasks, const QoOperands& w, 
   auto pair_map = [&](int a, int b) { return Idx4{1, 1, v, st[a], 0, 0, st[b]}; };
   auto trip_map = [&](int a, int b, int c) { return Idx4{1, v, v, st[a], 0, st[b], st[c]}; };
   const bool ev = v % 2 == 0, eo = ev && o % 2 == 0;
-  const long long m2 = (v2 - 1);
+  const long long m2 = v2 - 1;
   for (int pr = 0; pr < 3; ++pr) {
     const int x = PAIR[pr][0], y = PAIR[pr][1], z = PAIR[pr][2], u = PAIR[pr][3];
     // X1 = 1/2 sum_e v^{ab}_{e,o_b} t_{o_a o_c o_d}^{e c d}
@@ -1682,7 +1682,7 @@ bool qo_plan(int o, int v, const std::vector<int4>& tasks, const QoOperands& w, 
       auto add = [&](int a, int b, const double* A, const double* abase, long long alen, const double* B,
                      const double* bbase, long long blen) {
         const double c = weight(gs[t], a, b, pair_rank);
-        if (c != 0.0) seg(it, A, abase, alen, m2 * v, v, 0, 0, B, bbase, blen, v2, v, v2, c);
+        if (c != 0.0) seg(l, it, A, abase, alen, m2 * v, v, 0, 0, B, bbase, blen, v2, c);
       };
       add(x, y, w.VVVO + oc[y] * v3, w.VVVO, n_vvvo, T3(oc[x], oc[z], oc[u]), w.T3u, n_t3);
       add(y, x, w.VVVOt + oc[x] * v3, w.VVVOt, n_vvvo, T3(oc[y], oc[z], oc[u]), w.T3u, n_t3);
@@ -1718,8 +1718,8 @@ bool qo_plan(int o, int v, const std::vector<int4>& tasks, const QoOperands& w, 
           B = w.T3u + oc[r[1]] * o2 * v3 + oc[r[0]] * v3;  // t_{o_x o_y m}
           ld = (long long)o * v3;
         }
-        seg(it, w.VOOO + (oc[a] * o + oc[r[k]]) * v * o, w.VOOO, o2 * o * v, (long long)(v - 1) * o, o, 0, 0, B, w.T3u,
-            n_t3, ld, o, v3, -c);
+        seg(l, it, w.VOOO + (oc[a] * o + oc[r[k]]) * v * o, w.VOOO, o2 * o * v, (long long)(v - 1) * o, o, 0, 0, B,
+            w.T3u, n_t3, ld, -c);
       }
       if (it.nseg > 0) items.push_back(it);
     }
@@ -1736,7 +1736,7 @@ bool qo_plan(int o, int v, const std::vector<int4>& tasks, const QoOperands& w, 
       auto add = [&](int c, int d, const double* A, const double* abase, long long alen, const double* B,
                      const double* bbase, long long blen, long long ld) {
         const double wt = weight(gs[t], c, d, pair_rank);
-        if (wt != 0.0) seg(it, A, abase, alen, m2 * o, o, 0, 0, B, bbase, blen, ld, o, v2, -wt);
+        if (wt != 0.0) seg(l, it, A, abase, alen, m2 * o, o, 0, 0, B, bbase, blen, ld, -wt);
       };
       auto W3 = [&](const double* p, int i, int j, int k) { return p + ((oc[i] * o + oc[j]) * o + oc[k]) * o * v2; };
       add(z, u, W3(w.Wo, x, y, z), w.Wo, n_wo, w.t2 + oc[u] * v2, w.t2, n_t2, o * v2);
@@ -1765,8 +1765,8 @@ bool qo_plan(int o, int v, const std::vector<int4>& tasks, const QoOperands& w, 
         rs[k] = (int)v3;
         rs[b1] = (int)v2;
         rs[c1] = v;
-        seg(it, w.Wv + qo_pair(o, oc[r[b1]], oc[r[c1]]) * v4, w.Wv, qo_pair(o, o, o) * v4,
-            (long long)(v - 1) * (v3 + v2 + v), rs[0], rs[1], rs[2], w.t2 + (oc[r[k]] * o + oc[d]) * v2, w.t2, n_t2, v, v, v, c);
+        seg(l, it, w.Wv + qo_pair(o, oc[r[b1]], oc[r[c1]]) * v4, w.Wv, qo_pair(o, o, o) * v4,
+            (long long)(v - 1) * (v3 + v2 + v), rs[0], rs[1], rs[2], w.t2 + (oc[r[k]] * o + oc[d]) * v2, w.t2, n_t2, v, c);
       }
       if (it.nseg > 0) items.push_back(it);
     }
@@ -1951,7 +1951,7 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
         it.seg[0].rs0 = v;
       }
   HIPCK(hipMemcpyAsync(wv_items, wvh.data(), sizeof(SegItem) * wvh.size(), hipMemcpyHostToDevice, s));
-  for (int w = 0; w < 2; ++w) {
+  for (int w = 0; w < 2; ++w) {  // (operands: all of VVVV, one v^2 block of T2 each)
     SegGemm ga{};
     ga.M = (int)v3; ga.N = v; ga.K = ga.kb = v; ga.n1 = ga.n2 = 1; ga.nitems = (int)npair;
     ga.vec = (v % 2) == 0; ga.swap = true;
@@ -1960,6 +1960,10 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
     ga.cm = Idx4{1, v, v, v3, 0, w == 0 ? v2 : (long long)v, 1};
     ga.cn = Idx4{1, 1, 1, w == 0 ? (long long)v : v2, 0, 0, 0};
     ga.accumulate = w;
+    ga.c_last = (npair - 1) * v4;
+    ga.c_len = npair * v4;
+    for (long long k = 0; k < npair; ++k)
+      if (!seg_fits(ga, wvh[(size_t)(w * npair + k)].seg[0], (v3 - 1) * v, v4, v2)) { ctx->err = "energy_q: operand out of range"; return CCT_EDEVICE; }
     HIPCK(seg_gemm(ga, s));
   }
   // Wbar_ijk^abm (Eq. q_w_vvo_ooo) as Wo[i][j][k][a][b][m]
@@ -2023,6 +2027,8 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
       SegGemm ga = l.g;
       ga.items = d_items + l.first;
       ga.C = l.y ? YS : XS;
+      ga.c_last = ((long long)th.size() - 1) * v4;
+      ga.c_len = ntb * v4;
       HIPCK(seg_gemm(ga, s));
     }
     HIPCK(qo_energy(XS, YS, VVOO, ctx->t2, ctx->eps, d_tasks, d_at, (int)th.size(), orbits, o, v, part, et, s));

@@ -367,6 +367,9 @@ struct Idx4 {
   long long s0, s1, s2, s3;
 };
 
+// The largest offset of indices 0..n-1 (strides >= 0).
+long long idx4_max(const Idx4& d, long long n);
+
 // --- segmented products over a table of items ----------------------------------
 //   C_z(m, n) (+)= sum_s coef_s sum_{k < K} A_s(m, k) B_s(k, n)
 // A_s is K-contiguous, row m = (d0 n1 + d1) n2 + d2 at a + d0 rs0 + d1 rs1 +
@@ -387,14 +390,23 @@ struct SegItem {
 };
 struct SegGemm {
   int M, N, K, kb, n1, n2, nitems;
-  bool vec;   // every segment allows 16-byte loads (even K, N, strides; aligned bases)
+  bool vec;   // 16-byte loads: K, N and every stride of the segments even, their bases aligned
   bool swap;  // the unit-stride axis of C lies in the rows
   const SegItem* items;  // device
   double* C;
   Idx4 cm, cn;
   int accumulate;
+  long long c_last, c_len;  // the largest SegItem::c, the doubles at C
 };
+// Refuses (hipErrorInvalidValue) what would reach past C.  The items are device
+// memory: whoever writes them checks each segment with seg_fits.
 hipError_t seg_gemm(const SegGemm& g, hipStream_t s);
+// Whether a segment's operands (rows of A up to areach from s.a) lie within the
+// alen doubles at s.a and the blen at s.b, and allow g.vec.
+inline bool seg_fits(const SegGemm& g, const SegOp& s, long long areach, long long alen, long long blen) {
+  if (areach + g.K > alen || (long long)(g.kb - 1) * s.ldb + g.N > blen) return false;
+  return !g.vec || !((((uintptr_t)s.a | (uintptr_t)s.b) & 15) || ((s.rs0 | s.rs1 | s.rs2 | s.ldb) & 1));
+}
 
 // --- perturbative quadruples in the occupied-tuple order ----------------------
 // Energies of ntasks occupied tuples (i, j, k, l) = tasks[y] from their

@@ -805,30 +805,10 @@ hipError_t qcheck(const QGemmArgs& g, long long& batch, bool& vec) {
   {
     // largest offset of a four-level map over [0, n): the digits of n - 1,
     // or a smaller leading part with every later digit at its maximum
-    auto mx = [](const Idx4& d, long long n) {
-      const long long r[4] = {0, d.n1, d.n2, d.n3}, st[4] = {d.s0, d.s1, d.s2, d.s3};
-      long long dg[4], x = n - 1;
-      for (int k = 3; k >= 1; --k) {
-        dg[k] = x % r[k];
-        x /= r[k];
-      }
-      dg[0] = x;
-      long long best = 0;
-      for (int k = 0; k < 4; ++k) best += dg[k] * st[k];
-      for (int k = 0; k < 4; ++k) {
-        if (dg[k] == 0) continue;
-        long long alt = 0;
-        for (int j = 0; j < k; ++j) alt += dg[j] * st[j];
-        alt += (dg[k] - 1) * st[k];
-        for (int j = k + 1; j < 4; ++j) alt += (r[j] - 1) * st[j];
-        best = std::max(best, alt);
-      }
-      return best;
-    };
     for (const Idx4* d : {&g.cm, &g.cn})
       if (d->n1 < 1 || d->n2 < 1 || d->n3 < 1 || d->s0 < 0 || d->s1 < 0 || d->s2 < 0 || d->s3 < 0)
         return hipErrorInvalidValue;
-    long long hi = mx(g.cm, g.M) + mx(g.cn, g.N);
+    long long hi = idx4_max(g.cm, g.M) + idx4_max(g.cn, g.N);
     for (int d = 0; d < g.nd; ++d) hi += (long long)(g.rad[d] - 1) * g.sc[d];
     if (g.c_len > 0 && hi >= g.c_len) return hipErrorInvalidValue;
   }

@@ -274,9 +274,35 @@ hipError_t seg_launch(const SegGemm& g, bool vec, hipStream_t s) {
 
 }  // namespace
 
+long long idx4_max(const Idx4& d, long long n) {
+  const long long r[4] = {0, d.n1, d.n2, d.n3}, st[4] = {d.s0, d.s1, d.s2, d.s3};
+  long long dg[4], x = n - 1;
+  for (int k = 3; k >= 1; --k) {
+    dg[k] = x % r[k];
+    x /= r[k];
+  }
+  dg[0] = x;
+  long long best = 0;
+  for (int k = 0; k < 4; ++k) best += dg[k] * st[k];
+  for (int k = 0; k < 4; ++k) {
+    if (dg[k] == 0) continue;
+    long long alt = 0;
+    for (int j = 0; j < k; ++j) alt += dg[j] * st[j];
+    alt += (dg[k] - 1) * st[k];
+    for (int j = k + 1; j < 4; ++j) alt += (r[j] - 1) * st[j];
+    best = std::max(best, alt);
+  }
+  return best;
+}
+
 hipError_t seg_gemm(const SegGemm& g, hipStream_t s) {
   if (g.M <= 0 || g.N <= 0 || g.nitems <= 0) return hipSuccess;
-  if (g.K <= 0 || g.kb > g.K || !g.items || g.n1 < 1 || g.n2 < 1 ) return hipErrorInvalidValue;
+  if (g.K <= 0 || g.kb < 1 || g.kb > g.K || !g.items || g.n1 < 1 || g.n2 < 1) return hipErrorInvalidValue;
+  if (g.vec && ((g.K | g.N) & 1)) return hipErrorInvalidValue;
+  for (const Idx4* d : {&g.cm, &g.cn})
+    if (d->n1 < 1 || d->n2 < 1 || d->n3 < 1 || d->s0 < 0 || d->s1 < 0 || d->s2 < 0 || d->s3 < 0)
+      return hipErrorInvalidValue;
+  if (g.c_last < 0 || g.c_last + idx4_max(g.cm, g.M) + idx4_max(g.cn, g.N) >= g.c_len) return hipErrorInvalidValue;
   const bool vec = g.vec;
   // A skinny side (the v labels of one axis) takes the narrowest tile of 32,
   // 48 or 64 that wastes least, against 64 of the long side: the update of C

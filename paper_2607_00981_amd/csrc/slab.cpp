@@ -395,35 +395,37 @@ int slab_f1(cct_slab* sl) {
 // item; every block is an item of the launch for that axis, so the drivers are
 // six launches, each reading and writing R once (one launch per block and
 // permutation: count 24, o = 12, v = 96 288 launches, 5.6 -> 1.5 ms).
-int slab_drivers(cct_slab* sl, bool d1, bool d2) {
-  const int v = sl->v;
+SegGemm driver_launch(const cct_slab* sl, int which, int ax) {
+  const int v = sl->v, u = ax == 0 ? 1 : 0, w = ax == 2 ? 1 : 2;
   const long long st[3] = {(long long)v * v, v, 1};
-  for (int which = 0; which < 2; ++which) {
-    if (!(which == 0 ? d1 : d2)) continue;
-    for (int ax = 0; ax < 3; ++ax) {
-      const int u = ax == 0 ? 1 : 0, w = ax == 2 ? 1 : 2;
-      const Idx4 pair{1, 1, v, st[u], 0, 0, st[w]}, one{1, 1, 1, st[ax], 0, 0, 0};
-      SegGemm g{};
-      g.M = which == 0 ? v * v : v;
-      g.N = which == 0 ? v : v * v;
-      g.K = which == 0 ? v : (int)sl->op;
-      g.kb = which == 0 ? v : sl->o;
-      g.n1 = 1; g.n2 = which == 0 ? v : 1;
-      g.nitems = sl->count;
-      g.vec = v % 2 == 0;
-      g.swap = which == 0 ? ax != 2 : ax == 2;
-      g.items = sl->drv + (size_t)(which * 3 + ax) * sl->count;
-      g.C = sl->r3;
-      g.cm = which == 0 ? pair : one;
-      g.cn = which == 0 ? one : pair;
-      g.accumulate = 1;
-      SHIP(seg_gemm(g, sl->s));
-    }
-  }
+  const Idx4 pair{1, 1, v, st[u], 0, 0, st[w]}, one{1, 1, 1, st[ax], 0, 0, 0};
+  SegGemm g{};
+  g.M = which == 0 ? v * v : v;
+  g.N = which == 0 ? v : v * v;
+  g.K = which == 0 ? v : (int)sl->op;
+  g.kb = which == 0 ? v : sl->o;
+  g.n1 = 1; g.n2 = which == 0 ? v : 1;
+  g.nitems = sl->count;
+  g.vec = v % 2 == 0;
+  g.swap = which == 0 ? ax != 2 : ax == 2;
+  g.items = sl->drv + (size_t)(which * 3 + ax) * sl->count;
+  g.C = sl->r3;
+  g.c_last = (long long)(sl->count - 1) * sl->v3;
+  g.c_len = (long long)sl->count * sl->v3;
+  g.cm = which == 0 ? pair : one;
+  g.cn = which == 0 ? one : pair;
+  g.accumulate = 1;
+  return g;
+}
+int slab_drivers(cct_slab* sl, bool d1, bool d2) {
+  for (int which = 0; which < 2; ++which)
+    for (int ax = 0; ax < 3; ++ax)
+      if (which == 0 ? d1 : d2) SHIP(seg_gemm(driver_launch(sl, which, ax), sl->s));
   return CCT_OK;
 }
 
-// The items of slab_drivers (every address is fixed once the buffers are).
+// The items of slab_drivers (every address is fixed once the buffers are);
+// empty if an operand would be read out of range.
 std::vector<SegItem> driver_items(const cct_slab* sl) {
   const int o = sl->o, v = sl->v;
   const long long v2 = (long long)v * v, v3 = sl->v3, op = sl->op;
@@ -431,6 +433,7 @@ std::vector<SegItem> driver_items(const cct_slab* sl) {
   for (int which = 0; which < 2; ++which)
     for (int ax = 0; ax < 3; ++ax) {
       const int u = ax == 0 ? 1 : 0, w = ax == 2 ? 1 : 2;
+      const SegGemm launch = driver_launch(sl, which, ax);
       for (int t = 0; t < sl->count; ++t) {
         const int4 tr = sl->tri_h[t];
         const long long oc[3] = {tr.x, tr.y, tr.z};
@@ -457,6 +460,8 @@ std::vector<SegItem> driver_items(const cct_slab* sl) {
             sg.ldb = k == 0 ? o * v2 : v2;
             sg.coef = -1.0;
           }
+          const long long alen = which == 0 ? sl->Wt + o * v3 - sg.a : sl->Wvooo + o * o * v * op - sg.a;
+          if (!seg_fits(launch, sg, (v - 1) * (which == 0 ? v2 + v : op), alen, sl->t2 + o * o * v2 - sg.b)) return {};
         }
         items.push_back(it);
       }
@@ -614,7 +619,8 @@ int cct_slab_create(int nocc, int nvir, int naux, int first, int count, cct_prec
     rc = CCT_EDEVICE;
   if (rc == CCT_OK) {
     const std::vector<SegItem> items = driver_items(sl);
-    if (hipMemcpy(sl->drv, items.data(), sizeof(SegItem) * items.size(), hipMemcpyHostToDevice) != hipSuccess)
+    if (items.empty() ||
+        hipMemcpy(sl->drv, items.data(), sizeof(SegItem) * items.size(), hipMemcpyHostToDevice) != hipSuccess)
       rc = CCT_EDEVICE;
   }
   if (rc == CCT_OK && fill(sl->eps0, 0.0, n, sl->s) != hipSuccess) rc = CCT_EDEVICE;
