@@ -2007,8 +2007,6 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
   const QoOperands ops{VVVO, VVVOt, VVVOk, VVVOkt, VOOO, Wv, Wo, g, T3u, ctx->t2, T2r, T2l};
   std::vector<int4> th;
   std::vector<int> ah;
-  std::vector<SegItem> ih;
-  bool first = true;
   auto flush = [&]() -> int {
     if (th.empty()) return CCT_OK;
     std::vector<SegItem> items;
@@ -2017,10 +2015,7 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
       ctx->err = "energy_q: operand out of range";
       return CCT_EDEVICE;
     }
-    if (!first) HIPCK(hipStreamSynchronize(s));  // the host tables of the previous batch have been read
-    first = false;
-    ih.swap(items);
-    HIPCK(hipMemcpyAsync(d_items, ih.data(), sizeof(SegItem) * ih.size(), hipMemcpyHostToDevice, s));
+    HIPCK(hipMemcpyAsync(d_items, items.data(), sizeof(SegItem) * items.size(), hipMemcpyHostToDevice, s));
     HIPCK(hipMemcpyAsync(d_tasks, th.data(), sizeof(int4) * th.size(), hipMemcpyHostToDevice, s));
     HIPCK(hipMemcpyAsync(d_at, ah.data(), sizeof(int) * ah.size(), hipMemcpyHostToDevice, s));
     for (const QoLaunch& l : ls) {
@@ -2032,7 +2027,7 @@ int energy_q(cct_ctx* ctx, double* e_q, double* e_tasks, long long cap, char* re
       HIPCK(seg_gemm(ga, s));
     }
     HIPCK(qo_energy(XS, YS, VVOO, ctx->t2, ctx->eps, d_tasks, d_at, (int)th.size(), orbits, o, v, part, et, s));
-    HIPCK(hipStreamSynchronize(s));
+    HIPCK(hipStreamSynchronize(s));  // the host tables have been read
     th.clear();
     ah.clear();
     return CCT_OK;

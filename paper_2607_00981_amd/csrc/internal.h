@@ -318,16 +318,13 @@ hipError_t gather_rows(const double* in, long long ld_in, const int* rows, int n
 // Y[b*sb + f*sf + b*sp + q*sq] += alpha * X[f*xf + q] for b < nb, f < nf, q < nq.
 hipError_t add_diag_rows(double* Y, const double* X, int nb, int nf, int nq, long long sb, long long sf, long long sp,
                          long long sq, long long xf, double alpha, hipStream_t s);
-// out[i] += sum_r in[r * n + i] for r = 0..rows-1 (fixed order).
-hipError_t add_rows(const double* in, int rows, long long n, double* out, hipStream_t s);
 // DIIS on the device.  The history holds M slots of L doubles (vecs, errs);
 // the first n12 elements of a vector are T1/T2 (weight 1), the rest packed T3
 // blocks of bs elements (weight tri[t].w, the orderings of block t).
-// st (DIIS_STATE ints): [0] next slot, [1] vectors held, [2] slot of the newest,
-// [3] 1 if the last step extrapolated, [4] vectors in that solve, [5..] their
-// slots, oldest first.
+// st (DIIS_STATE ints): [0] next slot, [1] vectors held, [2] 1 if the last step
+// extrapolated, [3] vectors in that solve, [4..] their slots, oldest first.
 constexpr int DIIS_MAX = 64;
-constexpr int DIIS_STATE = 5 + DIIS_MAX;
+constexpr int DIIS_STATE = 4 + DIIS_MAX;
 struct DiisArgs {
   long long L, n12, bs;
   const int4* tri;

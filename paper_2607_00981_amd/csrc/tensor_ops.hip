@@ -477,14 +477,6 @@ __global__ void convert_kernel(const double* __restrict__ in, OutSpec out, long 
     put_out(out, i, in[i]);
 }
 
-__global__ void add_rows_kernel(const double* __restrict__ in, int rows, long long n, double* __restrict__ out) {
-  for (long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (long long)gridDim.x * blockDim.x) {
-    double acc = out[i];
-    for (int r = 0; r < rows; ++r) acc += in[(long long)r * n + i];
-    out[i] = acc;
-  }
-}
-
 __global__ void jacobi_kernel(double* __restrict__ t1, const double* __restrict__ r1, double* __restrict__ t2,
                               const double* __restrict__ r2, const double* __restrict__ eps, int o, int v) {
   const long long n1 = (long long)o * v, n2 = n1 * n1;
@@ -721,12 +713,6 @@ hipError_t swap01_batched(const double* in, OutSpec out, long long batch, int n0
 hipError_t convert(const double* in, OutSpec out, long long n, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   hipLaunchKernelGGL(convert_kernel, dim3(blocks_for(n, TPB * 4)), dim3(TPB), 0, s, in, out, n);
-  return hipGetLastError();
-}
-
-hipError_t add_rows(const double* in, int rows, long long n, double* out, hipStream_t s) {
-  if (n <= 0 || rows <= 0) return hipSuccess;
-  hipLaunchKernelGGL(add_rows_kernel, dim3(blocks_for(n, TPB)), dim3(TPB), 0, s, in, rows, n, out);
   return hipGetLastError();
 }
 
@@ -1270,9 +1256,8 @@ __global__ void diis_solve_kernel(const double* __restrict__ d, double* __restri
   }
   st[0] = (k + 1) % M;
   st[1] = n_new;
-  st[2] = k;
+  st[2] = 0;
   st[3] = 0;
-  st[4] = 0;
   if (n_new < start) return;
   int first = 0;
   while (true) {
@@ -1325,10 +1310,10 @@ __global__ void diis_solve_kernel(const double* __restrict__ d, double* __restri
     if (!singular) {
       for (int idx = 0; idx < m; ++idx) {
         coef[idx] = x[idx];
-        st[5 + idx] = order[first + idx];
+        st[4 + idx] = order[first + idx];
       }
-      st[4] = m;
-      st[3] = 1;
+      st[3] = m;
+      st[2] = 1;
       return;
     }
     if (m <= 1) return;
@@ -1342,8 +1327,8 @@ __global__ void diis_solve_kernel(const double* __restrict__ d, double* __restri
 __global__ __launch_bounds__(TPB) void diis_extrapolate_kernel(DiisAmps t, const double* __restrict__ vecs, DiisArgs a,
                                                                const int* __restrict__ st,
                                                                const double* __restrict__ coef) {
-  if (st[3] == 0) return;
-  const int m = st[4];
+  if (st[2] == 0) return;
+  const int m = st[3];
   long long lo, hi;
   double w;
   diis_chunk(a, blockIdx.x, lo, hi, w);
@@ -1354,7 +1339,7 @@ __global__ __launch_bounds__(TPB) void diis_extrapolate_kernel(DiisAmps t, const
   for (int u = 0; u < DIIS_U; ++u) acc[u] = 0.0;
   for (int idx = 0; idx < m; ++idx) {
     const double cf = coef[idx];
-    const double* y = vecs + (long long)st[5 + idx] * a.L + lo;
+    const double* y = vecs + (long long)st[4 + idx] * a.L + lo;
 #pragma unroll
     for (int u = 0; u < DIIS_U; ++u) {
       const long long r = threadIdx.x + u * TPB;
