@@ -3044,10 +3044,16 @@ int cct_create(int nocc, int nvir, int naux, cct_precision prec, const char* opt
   // operands, pair products and one relabelled copy (about 3 v^3)
   const long long vp = (long long)v * (v + 1) / 2, ntri_l = (long long)o * (o + 1) * (o + 2) / 6;
   const long long lad_w = vp * (2 * vp + 16), lad_blk = (long long)v * (2 * vp + 16) + 2 * (long long)v * vp + v3;
+  // the feedback of one slot: integral slices and both layouts, every run padded
+  // to 16, and its partial sums where R3 does not hold them (many occupied and few
+  // virtual orbitals: the padding counts)
+  const long long v2p = feed_pad((long long)v * v), ovp = feed_pad(ov), nf = v + o;
+  const long long part = std::max((long long)o * ov, ov * v) * nf;
+  const long long feed = nf * o * (v2p + ovp) + o2v2 + o * ov * v2p + ov * v * ovp + (part > t3n ? part + 64 : 0) + 5 * 32;
   const long long ws_min =
-      std::max(6 * (long long)o * v3 + 2 * o2v3, lad_w + 2 * lad_blk) + (1 << 22);
+      std::max({6 * (long long)o * v3 + 2 * o2v3 + (1 << 22), lad_w + 2 * lad_blk + (1 << 22), feed});
   const long long need_ws =
-      std::max(6 * (long long)o * v3 + 2 * o2v3 * o, lad_w + ntri_l * lad_blk) + (1 << 22);
+      std::max(ws_min, std::max(6 * (long long)o * v3 + 2 * o2v3 * o, lad_w + ntri_l * lad_blk) + (1 << 22));
   size_t free_b = 0, total_b = 0;
   if (device_mem_info(&free_b, &total_b) != hipSuccess) {
     ctx->err = "hipMemGetInfo failed (no HIP device?)";

@@ -322,3 +322,20 @@ def test_slab_copies_of_t3_are_bounded():
     al = LimitedAllocator()
     with binding.Slab(o, v, 20, 0, count, allocator=al.pair()):
         assert al.most <= _slab_bytes_unrelabelled(o, v, 20, count) + (5 << 30)
+
+
+@pytest.mark.parametrize("o,v", [(50, 25), (50, 22), (1, 9)])
+def test_the_smallest_workspace_holds_the_feedback(o, v):
+    say(f"[memory limits] feedback in the smallest workspace o={o} v={v}")
+    s = ci.make_system(o, v, 12, 5, sigma=0.02)
+    got = []
+    for gb in (1e-6, 2.0):
+        with binding.Engine(o, v, 12, opts={"diis": False, "workspace_gb": gb}) as eng:
+            eng.set_fock(s["f"])
+            eng.set_eri_df(s["B"])
+            eng.init_mp2()
+            eng.update()
+            got.append(eng.residual(want_r3=False))
+    for a, b in zip(got[0], got[1]):
+        if a is not None:
+            assert np.abs(a - b).max() <= 1e-11 * np.abs(b).max()
