@@ -324,6 +324,16 @@ __global__ void splitk_reduce_kernel(const double* __restrict__ part, int splits
   }
 }
 
+// Ranges that K is split into where the product has `tiles` output tiles (of at
+// most 64 x 64): as many as fill the chip, of at least four K tiles each.
+int k_splits(const GemmArgs& g, long long tiles) {
+  if (!g.split_ws || tiles >= 128 || g.K < 8 * BK) return 1;
+  const long long mn = (long long)g.M * g.N * g.batch;
+  long long z = std::min<long long>((256 + tiles - 1) / tiles, g.K / (4 * BK));
+  z = std::min<long long>(z, g.split_cap / std::max<long long>(mn, 1));
+  return (int)std::max<long long>(1, std::min<long long>(z, 64));
+}
+
 template <int BM, int BN>
 hipError_t launch(const GemmArgs& g, Prec prec, hipStream_t s) {
   const int tiles_m = (g.M + BM - 1) / BM, tiles_n = (g.N + BN - 1) / BN;
@@ -332,14 +342,8 @@ hipError_t launch(const GemmArgs& g, Prec prec, hipStream_t s) {
   dim3 grid((unsigned)grid_x);
   if (prec == Prec::F64) {
     // few output tiles and a long K: split K so that the chip fills
-    int splits = 1;
-    const long long tiles = (long long)tiles_m * tiles_n * g.batch;
+    int splits = BM <= 64 ? k_splits(g, (long long)tiles_m * tiles_n * g.batch) : 1;
     const long long mn = (long long)g.M * g.N * g.batch;
-    if (BM <= 64 && g.split_ws && tiles < 128 && g.K >= 8 * BK) {
-      splits = (int)std::min<long long>((256 + tiles - 1) / tiles, g.K / (4 * BK));
-      splits = (int)std::min<long long>(splits, g.split_cap / std::max<long long>(mn, 1));
-      splits = std::min(splits, 64);
-    }
     // each split covers whole K tiles
     const long long unit = BK;
     if (splits >= 2 && unit < g.K) {
@@ -386,8 +390,17 @@ hipError_t gemm(const GemmArgs& g, Prec prec, hipStream_t s) {
     return launch<128, 128>(g, prec, s);
   // fewer 64 x 64 tiles than compute units: 32 x 32, four times the workgroups
   // and a quarter of the matrix-core time in each step of K (o = 4, v = 20: 38
-  // launches per iteration from 11.4 to 7.1 us each)
-  if (tiles64 < 256) return launch<32, 32>(g, prec, s);
+  // launches per iteration from 11.4 to 7.1 us each), unless splitting K fills the
+  // chip with 64 x 64 tiles as well.  Measured: 0.125 us per element of a
+  // workgroup's K range with 64 x 64 tiles, 0.063 with 32 x 32, and 0.3 us per
+  // range to add up.  (M = N = 180: K = 2048 26.4 us with 64 x 64, 24.8 with 32 x 32;
+  // 16384 91 and 146.  M = N = 400, K = 4096: 98 and 235.)
+  auto t32 = [](int n) { return (long long)(n + 31) / 32; };
+  auto us = [&](long long tiles, double step) {
+    const int z = k_splits(g, tiles);
+    return (double)((g.K + z - 1) / z) * step + (z > 1 ? 0.3 * z : 0.0);
+  };
+  if (tiles64 < 256 && us(t32(g.M) * t32(g.N) * g.batch, 0.063) < us(tiles64, 0.125)) return launch<32, 32>(g, prec, s);
   return launch<64, 64>(g, prec, s);
 }
 
