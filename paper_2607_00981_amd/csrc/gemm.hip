@@ -870,7 +870,11 @@ hipError_t gemm_nt(const NtArgs& g, Prec prec, hipStream_t s) {
     // tiles of 128 x 128, two rounds of 512, at 36 TF/s (176 of 192 x 256: 45),
     // and 7320 x 1891 580 tiles of 128 x 192, three rounds of 256, at 47 (464
     // of 128 x 256: 50).  32 x 32 is for the products that fill no shape's
-    // round: 400 x 210 x 224 from 16 to 9 us.
+    // round: 400 x 210 x 224 from 16 to 9 us.  The small tiles lose nothing by a last
+    // round of fewer workgroups per compute unit once one round is full (1280 of
+    // 64 x 64, K = 1024: 201 us, 1024 161, 2048 311), so that only whole units count
+    // then: 900 x 900 x 900 in a batch of 5 (1125 of 64 x 64) takes 1.41 ms for the
+    // quadruples ladder o = 2, v = 30 with them, 1.88 in 128 x 128 tiles.
     struct Cand { int var, bm, bn, slots; double speed; };
     const Cand cands[10] = {{9, 128, 256, 256, 1.10}, {10, 192, 256, 256, 1.10}, {11, 128, 192, 256, 1.10},
                            {1, 128, 256, 256, 1.00}, {2, 256, 128, 256, 1.00},  {4, 128, 128, 512, 0.96},
@@ -881,8 +885,10 @@ hipError_t gemm_nt(const NtArgs& g, Prec prec, hipStream_t s) {
       if (c.var >= 9 && !dl_ok) continue;
       const long long tm = (g.M + c.bm - 1) / c.bm, tn = (g.N + c.bn - 1) / c.bn;
       const double used = ((double)g.M / (double)(tm * c.bm)) * ((double)g.N / (double)(tn * c.bn));
-      const long long tiles = tm * tn * g.batch, rounds = (tiles + c.slots - 1) / c.slots;
-      const double score = used * ((double)tiles / (double)(rounds * c.slots)) * c.speed;
+      const long long tiles = tm * tn * g.batch;
+      const int round = c.bm <= 64 && c.bn <= 64 && tiles > c.slots ? 256 : c.slots;
+      const long long rounds = (tiles + round - 1) / round;
+      const double score = used * ((double)tiles / (double)(rounds * round)) * c.speed;
       if (score > best) { best = score; variant = c.var; }
     }
   }
