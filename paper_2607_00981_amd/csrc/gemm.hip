@@ -437,7 +437,8 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_nt_f64_kernel(NtArgs g
   const int tid = threadIdx.x;
   const double* A = g.A + (long long)b * g.a_batch;
   const double* B = g.B + (long long)b * g.b_batch;
-  // per-thread source rows (clamped) and validity
+  // per-thread source rows and first k (both clamped to the matrix: masked units
+  // are loaded too) and validity
   const double* pa[C::SA];
   const double* pb[C::SB];
   int ka[C::SA], kb[C::SB];
@@ -449,7 +450,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_nt_f64_kernel(NtArgs g
     ka[i] = 2 * (seg % (BK / 2));
     const int m = tm * BM + row;
     va[i] = m < g.M;
-    pa[i] = A + (long long)(va[i] ? m : 0) * g.lda + ka[i];
+    pa[i] = A + (long long)(va[i] ? m : 0) * g.lda + (ka[i] < g.K ? ka[i] : 0);
   }
 #pragma unroll
   for (int i = 0; i < C::SB; ++i) {
@@ -459,13 +460,13 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_nt_f64_kernel(NtArgs g
       kb[i] = seg / (BN / 2);
       const int n = tn * BN + 2 * (seg % (BN / 2));
       vb[i] = n < g.N;
-      pb[i] = B + (long long)kb[i] * g.ldb + (vb[i] ? (g.b_map ? map2(g.bnm, n) : (long long)n) : 0);
+      pb[i] = B + (long long)(kb[i] < g.K ? kb[i] : 0) * g.ldb + (vb[i] ? (g.b_map ? map2(g.bnm, n) : (long long)n) : 0);
     } else {
       const int row = seg / (BK / 2);
       kb[i] = 2 * (seg % (BK / 2));
       const int n = tn * BN + row;
       vb[i] = n < g.N;
-      pb[i] = B + (long long)(vb[i] ? n : 0) * g.ldb + kb[i];
+      pb[i] = B + (long long)(vb[i] ? n : 0) * g.ldb + (kb[i] < g.K ? kb[i] : 0);
     }
   }
   const int wave = tid / 64, lane = tid & 63;
@@ -948,7 +949,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_lp_f32_kernel(NtLpArgs
     ka[i] = 4 * (seg % (KB / 4));
     const int m = tm * BM + row;
     va[i] = m < g.M;
-    pa[i] = A + (long long)(va[i] ? m : 0) * g.lda + ka[i];
+    pa[i] = A + (long long)(va[i] ? m : 0) * g.lda + (ka[i] < g.K ? ka[i] : 0);  // masked units are loaded too
   }
 #pragma unroll
   for (int i = 0; i < SB; ++i) {
@@ -956,7 +957,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_lp_f32_kernel(NtLpArgs
     kb[i] = 4 * (seg % (KB / 4));
     const int n = tn * BN + row;
     vb[i] = n < g.N;
-    pb[i] = B + (long long)(vb[i] ? n : 0) * g.ldb + kb[i];
+    pb[i] = B + (long long)(vb[i] ? n : 0) * g.ldb + (kb[i] < g.K ? kb[i] : 0);
   }
   const int wave = tid / 64, lane = tid & 63;
   const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
@@ -1226,7 +1227,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_lp_bf16x3_kernel(NtLpA
     ka[i] = 8 * (seg % (KB / 8));
     const int m = tm * BM + rowa[i];
     va[i] = m < g.M;
-    pa[i] = A + (long long)(va[i] ? m : 0) * g.lda + ka[i];
+    pa[i] = A + (long long)(va[i] ? m : 0) * g.lda + (ka[i] < g.K ? ka[i] : 0);  // masked units are loaded too
   }
 #pragma unroll
   for (int i = 0; i < SB; ++i) {
@@ -1235,7 +1236,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_lp_bf16x3_kernel(NtLpA
     kb[i] = 8 * (seg % (KB / 8));
     const int n = tn * BN + rowb[i];
     vb[i] = n < g.N;
-    pb[i] = B + (long long)(vb[i] ? n : 0) * g.ldb + kb[i];
+    pb[i] = B + (long long)(vb[i] ? n : 0) * g.ldb + (kb[i] < g.K ? kb[i] : 0);
   }
   const int wave = tid / 64, lane = tid & 63;
   const int wm0 = (wave / WN) * (BM / WM), wn0 = (wave % WN) * (BN / WN);
