@@ -24,7 +24,9 @@
  *     t2   [o][o][v][v]      t_ij^ab, must satisfy t_ij^ab == t_ji^ba
  *     t3p  [ntri][v][v][v]   packed T3, ntri = o(o+1)(o+2)/6, triples i<=j<=k in
  *                            lexicographic order (cct_packed_index), block
- *                            (i,j,k) holds t_ijk^abc for all a,b,c
+ *                            (i,j,k) holds t_ijk^abc for all a,b,c; must satisfy
+ *                            t_iik^abc == t_iik^bac, t_ikk^abc == t_ikk^acb (the
+ *                            (Q) corrections rely on it, and on t2's symmetry)
  *   The library owns its device memory (allocated at cct_create) and works on
  *   the HIP stream passed at creation (NULL = the default stream).
  *
@@ -248,10 +250,10 @@ int cct_gather_t3(cct_ctx* ctx, const int64_t* idx, int64_t n, double* out);
  * length of both arrays provided; writes min(cap, 19). */
 int cct_get_counters(cct_ctx* ctx, double* macs_by_term, double* ms_by_phase, int cap);
 
-/* Tile autotuner: times every tile variant of the particle-particle ladder
- * GEMM (on a truncated M of this context's shape, scratch output) and of the
- * ring GEMM (one batch of occupied pairs) in the context's precision and uses
- * the fastest from then on (results are the same to rounding in every
+/* Tile autotuner: times the tile variants for large products on the
+ * particle-particle ladder GEMM (on a truncated M of this context's shape,
+ * scratch output) and on the ring GEMM (one batch of occupied pairs) in the
+ * context's precision and uses the fastest from then on (results are the same to rounding in every
  * variant).  budget_ms bounds the timing (at least one variant per class is
  * timed).  The choice is also stored in the flat JSON file named by the
  * CCT_TUNE_CACHE environment variable (if set; keys "o<o>_v<v>_<prec>_ladder"
@@ -327,7 +329,10 @@ typedef struct cct_slab cct_slab;
 /* first + count <= nocc(nocc+1)(nocc+2)/6, count <= 65535.  opts_json:
  * "panel" (rows a per W panel, 1..nvir; default 8, or more while a panel
  * takes at most 1 GiB), "timers" (true: per-phase times
- * in cct_slab_get_counters).  alloc/free_fn/alloc_user: as for cct_create.
+ * in cct_slab_get_counters).  Relabelled copies of T3 take, beside the inputs,
+ * T3, R3 and the W panel, up to 4 GiB in FP64 (two times T3 where v is even and
+ * that is more), less or none where memory is refused, and 12 v^3 bytes per
+ * block in the mixed modes.  alloc/free_fn/alloc_user: as for cct_create.
  * Errors: CCT_EINVAL, CCT_ENOMEM. */
 int cct_slab_create(int nocc, int nvir, int naux, int first, int count, cct_precision prec, const char* opts_json,
                     cct_alloc_fn alloc, cct_free_fn free_fn, void* alloc_user, void* hip_stream, cct_slab** out);

@@ -308,7 +308,7 @@ hipError_t seg_gemm(const SegGemm& g, hipStream_t s) {
   // 48 or 64 that wastes least, against 64 of the long side: the update of C
   // and the short K want workgroups in flight more than operand reuse (o = 6,
   // v = 48, whole evaluation: 128 x 48 tiles 65.2 ms, 64 x 48 61.7, 256 x 48
-  // 73.1).  The square products take 128 x 128 with eight waves of 32 x 64
+  // 73.1; not measured anew at other v).  The square products take 128 x 128 with eight waves of 32 x 64
   // where those tiles are filled (four waves of 64 x 64 65.2 ms, eight 58.5,
   // 64 x 64 tiles 59.6), else 64 x 64.
   auto pad = [](int n, int b) { return (n + b - 1) / b * b; };
